@@ -70,7 +70,10 @@ enum {
     CKKS_OP_HROT_HOISTED = 7
 };
 
-/* Pipeline stages that can be timed with ckks_trace_begin / ckks_trace_end. */
+/* Pipeline stages that can be timed with ckks_trace_begin / ckks_trace_end.
+ * INTT_COLS, BCONV_UP and NTT_COLS_UP are one kernel (ModUp's column stages), as
+ * are INTT_COLS_P, BCONV_DOWN and NTT_COLS_DOWN (ModDown's): each of the three
+ * names times that kernel. */
 enum {
     CKKS_STAGE_INTT_BLOCKS = 1,     /* K1: INTT block pass of the switched polynomial */
     CKKS_STAGE_INTT_COLS = 2,       /* K2: INTT column pass + BConv pre-multiply */
@@ -281,25 +284,26 @@ int ckks_rescale(const ckks_ctx *ctx, const uint32_t *ct, int L, uint32_t *out, 
 /*
  * Kernel schedule of a context's key-switching pipeline (the limb-tile and
  * work-group shapes that do not change any result):
- *   bconv_up_rows    ModUp BConv output rows per work-group: 2, 4, 6 or 12
- *                    (a work-group re-reads its digit's inputs once)
- *   bconv_down_rows  ModDown BConv output rows per work-group: 2, 4, 6 or 12
+ *   bconv_up_rows    2, 4, 6 or 12: a work-group of ModUp's column kernel
+ *                    computes at most eight times as many output rows
+ *                    (each work-group transforms its digit's inputs once)
+ *   bconv_down_rows  the same for ModDown's column kernel
  *   small_grid       inner-product launches of at most this many
  *                    work-groups use one thread group per digit tile
  *                    (0: never)
  *   ntt_shape        NTT tile / radix choices (Sec. III-C1 NTT kernels),
- *                    a bit mask: 1 = forward column passes with 8 elements
- *                    per thread in radix-8 phases (else 16, radix-16);
- *                    2 = inverse column passes with 16 elements per thread
- *                    in radix-16 phases (else 8, radix-8); 4 = the ModUp
- *                    INTT block pass with 16 elements per thread on 256
- *                    threads (else 8 on 512); 8 = at N = 2^12, the whole
- *                    key-switch as two kernels that hold whole limbs in
- *                    LDS (ModUp + inner product per row and digit group,
- *                    ModDown + epilogue per output row) instead of the
- *                    nine-kernel pipeline (hoisted rotations and batch
- *                    plans with a split inner product keep the nine
- *                    kernels).  Small grids keep their own shapes.  0..15.
+ *                    a bit mask: 1 = the rescale's forward column pass with
+ *                    8 elements per thread in radix-8 phases (else 16,
+ *                    radix-16); 2 = its inverse column pass with 16 elements
+ *                    per thread in radix-16 phases (else 8, radix-8); 4 =
+ *                    accepted, without effect (the ModUp INTT block pass has
+ *                    one shape); 8 = at N = 2^12, the whole key-switch as two
+ *                    kernels that hold whole limbs in LDS (ModUp + inner
+ *                    product per row and digit group, ModDown + epilogue per
+ *                    output row) instead of the five-kernel pipeline (hoisted
+ *                    rotations and batch plans with a split inner product
+ *                    keep the five kernels).  Small grids keep their own
+ *                    shapes.  0..15.
  * Default {12, 6, 128, 0}; {12, 6, 128, 8} for N = 2^12.  The schedule is read when work is enqueued (and when
  * a graph batch is captured); changing it must not overlap calls on the
  * context.  Every schedule gives bitwise the same results.
@@ -332,7 +336,7 @@ int ckks_ctx_tune(ckks_ctx *ctx, int L, int reps, void *stream, ckks_schedule *b
  * Batches (Sec. IV-A batching; Sec. IV-C one submission per static graph).
  * A batch is a fixed list of independent jobs, each at its own level, run
  * together: every pipeline kernel covers all jobs of a launch group at once
- * (nine kernels for the key-switching jobs of a group, four for all rescale
+ * (five kernels for the key-switching jobs of a group, four for all rescale
  * jobs; groups as in ckks_batch_plan below), and with use_graph != 0 the
  * whole launch sequence is captured once into a hipGraph at creation, so
  * ckks_batch_launch is a single graph submission.
@@ -385,7 +389,7 @@ int ckks_batch_launch(ckks_batch *batch, void *stream);
  * results.  Default {0, 1, 1}; {0, 1, 0} for a batch of one key-switching
  * job, and at N = 2^12 under the whole-limb schedule (ntt_shape bit 8) while
  * (L + k) * min(beta, 4) * jobs <= 800 for its largest level L (split runs
- * the nine-kernel pipeline, which pays off only past that).  A batch created with use_graph runs one
+ * the five-kernel pipeline, which pays off only past that).  A batch created with use_graph runs one
  * branch (streams = 1): a multi-branch launch sequence is not captured.
  */
 typedef struct ckks_batch_plan {

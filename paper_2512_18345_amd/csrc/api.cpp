@@ -1052,6 +1052,10 @@ int ckks_trace_begin(ckks_ctx* ctx, int stage, int capacity) {
     }
   }
   c.trace.count = 0;
+  // the column stages around a base conversion are one kernel, traced under
+  // any of their names
+  if (stage == CKKS_STAGE_BCONV_UP || stage == CKKS_STAGE_NTT_COLS_UP) stage = CKKS_STAGE_INTT_COLS;
+  if (stage == CKKS_STAGE_BCONV_DOWN || stage == CKKS_STAGE_NTT_COLS_DOWN) stage = CKKS_STAGE_INTT_COLS_P;
   c.trace.stage = stage;
   return CKKS_OK;
 }

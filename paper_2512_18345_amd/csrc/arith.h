@@ -82,6 +82,11 @@ __device__ __forceinline__ uint4 ld4(const uint32_t* p) {
   const u32x4 v = *(const __attribute__((address_space(1))) u32x4*)p;
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+__device__ __forceinline__ uint2 ld2(const uint32_t* p) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 v = *(const __attribute__((address_space(1))) u32x2*)p;
+  return make_uint2(v.x, v.y);
+}
 // Streaming load: the non-temporal hint marks the line for early eviction
 // (data read once, such as evaluation-key words).
 __device__ __forceinline__ uint4 ld4nt(const uint32_t* p) {

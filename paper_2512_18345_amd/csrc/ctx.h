@@ -25,6 +25,8 @@ struct ModC {
   uint32_t mu32;        // floor(2^32 / q)
   uint32_t mu_hi, mu_lo;  // floor(2^64 / q)
   uint32_t ninv, ninv_s;  // N^-1 mod q and its Shoup companion
+  uint32_t qn;            // -q^-1 mod 2^32 (Montgomery)
+  uint32_t pad;
 };
 
 // What a kernel needs to find a prime's tables.  Every twiddle is stored as
@@ -67,6 +69,29 @@ struct DevTab {
   __device__ const uint2* full_itw(int pi) const { return fitw + ((size_t)pi << logN); }
 };
 
+// Tables of the Montgomery transforms (mont_ntt.h), one word w 2^32 mod q per
+// entry, indexed as their Shoup forms above:
+//  * col / icol [nprimes][N1], blk / iblk [nprimes][256];
+//  * row / irow [nprimes][N1][32]: the first four block-pass stages of row b
+//    with its own twiddles, entry 2^s + g < 16 -> psi^(+-brv_logN((N1 + b) 2^s + g)),
+//    and entry 16 + j -> rho_b^(+-j), which is all of the twist that remains
+//    for the last four stages;
+//  * the base-conversion constants: pre-multipliers and T times 2^32.
+struct MontTab {
+  const uint32_t *col, *icol, *blk, *iblk, *row, *irow;
+  const uint32_t *modup_scale, *modup_T, *moddown_scale, *moddown_T, *pinv;
+  __device__ const uint32_t* col_tw(const DevTab& T, int pi) const { return col + ((size_t)pi << T.logN1()); }
+  __device__ const uint32_t* col_itw(const DevTab& T, int pi) const { return icol + ((size_t)pi << T.logN1()); }
+  __device__ const uint32_t* blk_tw(int pi) const { return blk + ((size_t)pi << 8); }
+  __device__ const uint32_t* blk_itw(int pi) const { return iblk + ((size_t)pi << 8); }
+  __device__ const uint32_t* row_tw(const DevTab& T, int pi, int b) const {
+    return row + ((((size_t)pi << T.logN1()) + b) << 5);
+  }
+  __device__ const uint32_t* row_itw(const DevTab& T, int pi, int b) const {
+    return irow + ((((size_t)pi << T.logN1()) + b) << 5);
+  }
+};
+
 // Rows of a launch: row r of the data is prime index pidx(r).
 struct RowMap {
   int L;       // rows [0, L) are q_0..q_{L-1}
@@ -106,6 +131,9 @@ struct Ctx {
   uint2* d_pinv = nullptr;            // [L_max]
   // Rescale at level L: q_{L-1}^-1 mod q_i (Shoup), i < L - 1.
   uint2* d_rescale_inv = nullptr;     // [L_max + 1][L_max]
+
+  MontTab mont{};
+  uint32_t* d_mont = nullptr;         // every table of `mont`, one allocation
 
   // kernel tracing (ckks_trace_begin / ckks_trace_end)
   struct Trace {

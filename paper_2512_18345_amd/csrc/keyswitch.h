@@ -2,7 +2,7 @@
 //
 // A launch sequence processes up to 65535 independent jobs (grid.z = job);
 // each job is a key-switch, an HMult, an HRot, or one rotation of a hoisted
-// group, at its own level L.  The same nine kernels serve a single call and a
+// group, at its own level L.  The same five kernels serve a single call and a
 // batch, so batching adds work-groups to every launch instead of launches.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -44,12 +44,11 @@ struct __align__(16) RsJob {
 
 constexpr int kInlineJobs = 16;
 
-// NTT shape bits of Ctx::Sched::ntt_shape (whole-line column tiles and the
-// ModUp INTT block pass; small grids keep their own shapes):
-constexpr int kShapeFwdRadix8 = 1;   // forward column passes: 8 elements / thread, radix-8 phases (else 16, radix-16)
-constexpr int kShapeInvRadix16 = 2;  // inverse column passes: 16 elements / thread, radix-16 phases (else 8, radix-8)
-constexpr int kShapeK1Radix16 = 4;   // ModUp INTT block pass: 16 elements / thread on 256 threads (else 8 on 512)
-constexpr int kShapeWholeLimb = 8;   // N = 2^kSrLog: two kernels with whole limbs in LDS instead of nine
+// NTT shape bits of Ctx::Sched::ntt_shape (small grids keep their own shapes):
+constexpr int kShapeFwdRadix8 = 1;   // rescale's forward column pass: 8 elements / thread, radix-8 phases (else 16, radix-16)
+constexpr int kShapeInvRadix16 = 2;  // rescale's inverse column pass: 16 elements / thread, radix-16 phases (else 8, radix-8)
+// 4: accepted, without effect
+constexpr int kShapeWholeLimb = 8;   // N = 2^kSrLog: two kernels with whole limbs in LDS instead of five
 constexpr int kShapeAll = 15;
 constexpr int kSrGroups = 4;  // whole-limb key-switch: digit groups of its first kernel, at most
 
@@ -90,7 +89,7 @@ size_t rs_ws_words(const Ctx& c, int L);
 // is KS_HOIST.
 hipError_t ks_launch(const Ctx& c, const Ctx::Sched& sc, const JobArg<KsJob>& jobs, int njobs, int Lmax,
                      bool with_modup, bool with_hoist, hipStream_t st, const KsSplit& sp = KsSplit{});
-// Enqueue the ModUp of njobs KS_MODUP jobs (K1-K4 and the block pass of the
+// Enqueue the ModUp of njobs KS_MODUP jobs (K1, KC and the block pass of the
 // new rows: M ends fully in the evaluation domain, canonical).
 hipError_t ks_modup_launch(const Ctx& c, const Ctx::Sched& sc, const JobArg<KsJob>& jobs, int njobs, int Lmax,
                            hipStream_t st);

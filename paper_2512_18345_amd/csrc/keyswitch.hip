@@ -1,23 +1,23 @@
 // Fused key-switching pipeline over a job table (see keyswitch.h).
 //
 // Key-switching has three stages (Fig. keysw): ModUp of every digit, the
-// inner product with the evaluation key, ModDown of both components.  The NTT
-// is row-parallel and BConv column-parallel, so they cannot share a kernel
-// (Sec. III-D); what does fuse here is everything element-wise around them:
+// inner product with the evaluation key, ModDown of both components, here in
+// five kernels:
 //
-//  K1  INTT block pass of the input (loader forms d: d, c1*c1', or sigma(c1))
-//  K2  INTT column pass + N^-1 (D_j/q_i)^-1 pre-multiply            -> y
-//  K3  ModUp BConv, every digit in one launch                        -> z
-//  K4  NTT column pass of every digit's new rows                     -> z
+//  K1  INTT block pass of the input (loader forms d: d, c1*c1', or sigma(c1)) -> y
+//  KC  (up) INTT column pass of each digit's limbs, N^-1 (D_j/q_i)^-1, ModUp
+//      BConv, NTT column pass of the new rows                        -> z
 //  K5  NTT block pass fused with the inner product over the digits
 //      (digit rows come straight from the loader; hoisted jobs gather
 //      sigma(M) instead of transforming), then, for the P rows, the first
 //      INTT pass of ModDown                                          -> acc
-//  K6  INTT column pass of the P rows, N^-1 (P/p_m)^-1 pre-multiply  -> x
-//  K7  ModDown BConv P -> Q, both components                        -> w
-//  K8  NTT column pass of w
+//  KC  (down) INTT column pass of the P rows, N^-1 (P/p_m)^-1, ModDown BConv,
+//      NTT column pass, both components                              -> w
 //  K9  NTT block pass fused with (acc - w) P^-1 plus the epilogue
 //      term (d0 / d1 of HMult, sigma(c0) of HRot)                    -> out
+//
+// The NTT's block pass is row-parallel; its column pass works down the columns
+// as BConv does, which is why the three column stages are one kernel.
 //
 // Every launch covers all jobs (grid.z) and all rows of a stage, which is
 // what gives small levels enough work-groups (the batching argument of
@@ -30,6 +30,7 @@
 #include "arith.h"
 #include "ctx.h"
 #include "keyswitch.h"
+#include "mont_ntt.h"
 #include "ntt_tile.h"
 
 namespace ckks {
@@ -46,11 +47,12 @@ struct KsConst {
   const uint32_t* moddown_T;
   const uint2* pinv;
   const uint2* rescale_inv;
+  MontTab M;
 };
 
 KsConst make_const(const Ctx& c) {
   return KsConst{c.tab(), c.k, c.alpha, c.beta_max(), c.d_modup_scale, c.d_modup_T,
-                 c.d_modup_T_off, c.d_moddown_scale, c.d_moddown_T, c.d_pinv, c.d_rescale_inv};
+                 c.d_modup_T_off, c.d_moddown_scale, c.d_moddown_T, c.d_pinv, c.d_rescale_inv, c.mont};
 }
 
 // Scratch layout of one job (rows of N words): acc [2][R], x [2][k], w [2][L],
@@ -94,35 +96,34 @@ __device__ __forceinline__ uint32_t mulmod(uint32_t a, uint32_t b, const ModC& m
   return reduce64((uint64_t)a * b, m.q, m.mu_hi, m.mu_lo);
 }
 
-// The QPT quads (words base + blk_elem(kk) .. +3) of row r of the polynomial
-// a job key-switches: d (PLAIN), c1 c1' (HMULT), sigma(c1) (HROT / HOIST).
-// Every load of a quad is issued before any of them is used.
-template <int QPT = 4, int T = kWG>
-__device__ __forceinline__ void load_d16(const KsJob& J, int r, uint32_t base, size_t N, int logN,
-                                         const ModC& m, uint4 d[QPT]) {
+// The four quads (words n0 + 64 kk .. + 3) of row r of the polynomial a job
+// key-switches: d (PLAIN), c1 c1' (HMULT), sigma(c1) (HROT).  Every load is
+// issued before any of them is used.
+__device__ __forceinline__ void load_d16(const KsJob& J, int r, uint32_t n0, size_t N, int logN,
+                                         const ModC& m, uint4 d[4]) {
   if (J.kind == KS_PLAIN || J.kind == KS_MODUP) {
 #pragma unroll
-    for (int kk = 0; kk < QPT; ++kk) d[kk] = ld4(J.a + (size_t)r * N + base + blk_elem<T>(kk));
+    for (int kk = 0; kk < 4; ++kk) d[kk] = ld4(J.a + (size_t)r * N + n0 + 64 * kk);
     return;
   }
   const size_t row1 = (size_t)(J.L + r) * N;
   if (J.kind == KS_HMULT) {
-    uint4 x[QPT], y[QPT];
+    uint4 x[4], y[4];
 #pragma unroll
-    for (int kk = 0; kk < QPT; ++kk) {
-      x[kk] = ld4(J.a + row1 + base + blk_elem<T>(kk));
-      y[kk] = ld4(J.b + row1 + base + blk_elem<T>(kk));
+    for (int kk = 0; kk < 4; ++kk) {
+      x[kk] = ld4(J.a + row1 + n0 + 64 * kk);
+      y[kk] = ld4(J.b + row1 + n0 + 64 * kk);
     }
 #pragma unroll
-    for (int kk = 0; kk < QPT; ++kk)
+    for (int kk = 0; kk < 4; ++kk)
       d[kk] = make_uint4(mulmod(x[kk].x, y[kk].x, m), mulmod(x[kk].y, y[kk].y, m),
                          mulmod(x[kk].z, y[kk].z, m), mulmod(x[kk].w, y[kk].w, m));
     return;
   }
   const uint32_t* src = J.a + row1;
 #pragma unroll
-  for (int kk = 0; kk < QPT; ++kk) {
-    const uint32_t n = base + blk_elem<T>(kk);
+  for (int kk = 0; kk < 4; ++kk) {
+    const uint32_t n = n0 + 64 * kk;
     d[kk] = make_uint4(ld1(src + auto_src(n, J.gal, logN)), ld1(src + auto_src(n + 1, J.gal, logN)),
                        ld1(src + auto_src(n + 2, J.gal, logN)), ld1(src + auto_src(n + 3, J.gal, logN)));
   }
@@ -132,161 +133,179 @@ __device__ __forceinline__ void load_d16(const KsJob& J, int r, uint32_t base, s
 // Stage 1: ModUp
 // ============================================================================
 
-// BPW blocks per work-group: 16 (a 4096-word tile, radix-16 phases) or, for
-// small grids, 4 (a quarter tile, one quad per thread, radix-4 phases).
-template <int LOGN1, int BPW, int EPT = (BPW == 16 ? 16 : 4)>
-__global__ __launch_bounds__(BPW * 256 / EPT) void k1_intt_blks(KsConst K, JobArg<KsJob> JA) {
+// One work-group per 16-row group of a limb (four waves, four rows each).
+// Bound: the loads' and stores' latency of one round of work-groups; the
+// transform is in-wave, so the only barrier is the one before the row-group
+// store, whose quads cross the waves' rows.
+__global__ __launch_bounds__(kWG) void k1_intt_blks(KsConst K, JobArg<KsJob> JA) {
   const KsJob J = JA.get(blockIdx.z);
   const int r = blockIdx.y;
   if (J.kind == KS_HOIST || r >= J.L) return;
-  __shared__ __align__(16) uint32_t s[kLds];
+  __shared__ __align__(16) uint32_t s[kBlkTile];
   const int logN = K.T.logN;
   const size_t N = (size_t)1 << logN;
-  const ModC m = ldc(K.T.mod + r);
-  const uint32_t q = m.q, q2 = 2 * q;
-  __shared__ uint2 stw[256];
-  const uint2 tww = tw_fetch(K.T.blk_itw(r), 256);  // (T >= 256)
-  constexpr int T = BPW * 256 / EPT;  // threads
-  constexpr int QPT = EPT / 4;        // quads per thread
-  const int blk0 = blockIdx.x * BPW;
-  const uint32_t base = blk0 * 256;
+  const ModC mc = ldc(K.T.mod + r);
+  const MontQ m = mont_q(mc);
+  const uint32_t base = blockIdx.x * kTile;
   const KsView V = ks_view(J, K, N);
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  const uint32_t n0 = base + line * 256 + 4 * (lane & 15);
   // the switched polynomial in the evaluation domain, kept for K5's digit
   // rows (a ModUp-only job keeps it as the digit row of its output M)
-  uint32_t* de = J.kind == KS_MODUP ? V.z + ((size_t)(r / K.alpha) * V.R + r) * N + base
-                                    : V.de + (size_t)r * N + base;
-  // all loads first: a store to de could alias the next quad's source; the
-  // twist factors of the epilogue are requested with them
-  uint4 d[QPT];
-  load_d16<QPT, T>(J, r, base, N, logN, m, d);
-  Twist4 tfi[QPT];
+  uint32_t* de = J.kind == KS_MODUP ? V.z + ((size_t)(r / K.alpha) * V.R + r) * N : V.de + (size_t)r * N;
+  // all loads first: a store to de could alias the next quad's source
+  BlkTw tw;
+  uint4 d[4];
+  load_d16(J, r, n0, N, logN, mc, d);
+  tw.load(K.M.row_itw(K.T, r, blockIdx.x * 16 + line), K.M.blk_itw(r), lane);
 #pragma unroll
-  for (int kk = 0; kk < QPT; ++kk) {
-    const int e = blk_elem<T>(kk);
-    tfi[kk] = twist4_load(K.T.blk_itwist(r, blk0 + (e >> 8)), e & 255);
+  for (int kk = 0; kk < 4; ++kk) {
+    blk_quad_store(s, line, 4 * (lane & 15) + 64 * kk, d[kk]);
+    if (J.kind != KS_PLAIN) st4(de + n0 + 64 * kk, d[kk]);  // HMULT, HROT, MODUP
   }
-#pragma unroll
-  for (int kk = 0; kk < QPT; ++kk) {
-    const int e = blk_elem<T>(kk);
-    lds_blk4_store(s, e, d[kk]);
-    if (J.kind != KS_PLAIN) st4(de + e, d[kk]);  // HMULT, HROT, MODUP
-  }
-  if constexpr (EPT == 16)
-    tw_put_perm(stw, tww);
-  else
-    tw_put(stw, tww, 256);
-  __syncthreads();
-  if constexpr (EPT == 16)
-    blk_stages<true>(s, PermTw{stw}, q, q2);
-  else if constexpr (EPT == 8)
-    blk_stages_r8<true, const uint2*, T>(s, stw, q, q2);
-  else
-    blk_stages_r4<true, const uint2*, T>(s, stw, q, q2);
+  wave_sync();
+  blk_inv_a(s, line, lane, tw, m);
+  wave_sync();
+  blk_inv_b(s, line, lane, tw, m);
   __syncthreads();
   uint32_t* y = V.y + (size_t)r * N + base;
 #pragma unroll
-  for (int kk = 0; kk < QPT; ++kk) st4(y + blk_elem<T>(kk), twist4(lds_blk4(s, blk_elem<T>(kk)), tfi[kk], q));
+  for (int kk = 0; kk < 4; ++kk)
+    st4(y + RowGroup<16>::word(threadIdx.x, kk, 0), RowGroup<16>::from_lds(s, threadIdx.x, kk));
 }
 
-template <int LOGN1, int CW, int T>
-__global__ __launch_bounds__(T) void k2_intt_cols(KsConst K, JobArg<KsJob> JA) {
-  const KsJob J = JA.get(blockIdx.z);
-  const int r = blockIdx.y;
-  if (J.kind == KS_HOIST || r >= J.L) return;
-  __shared__ __align__(16) uint32_t s[ColGeom<LOGN1, CW, T>::LDS];
-  constexpr int C = ColGeom<LOGN1, CW, T>::C;
-  const size_t N = (size_t)1 << K.T.logN;
-  const uint32_t q = ldc(K.T.mod + r).q, q2 = 2 * q;
-  __shared__ uint2 stw[ColGeom<LOGN1, CW, T>::N1];
-  const uint2 tww = tw_fetch(K.T.col_itw(r), ColGeom<LOGN1, CW, T>::N1);
-  const uint2 sc = ldc(K.modup_scale + (size_t)J.L * K.T.L_max + r);
-  const int col0 = blockIdx.x * C;
-  uint32_t* row = ks_view(J, K, N).y + (size_t)r * N;
-  load_cols<LOGN1, CW, T>(s, row, col0);
-  tw_put(stw, tww, ColGeom<LOGN1, CW, T>::N1);
-  __syncthreads();
-  col_stages<LOGN1, true, CW, T>(s, stw, q, q2);
-  __syncthreads();
-#pragma unroll
-  for (int kk = 0; kk < ColGeom<LOGN1, CW, T>::QUADS; ++kk) {
-    const int lin = (threadIdx.x + kk * T) * 4;
-    const int pos = lin / C, c = lin & (C - 1);
-    uint4 v = *reinterpret_cast<const uint4*>(s + lidx_col(pos, c, C));
-    v.x = csub(mul_shoup(v.x, sc.x, sc.y, q), q);
-    v.y = csub(mul_shoup(v.y, sc.x, sc.y, q), q);
-    v.z = csub(mul_shoup(v.z, sc.x, sc.y, q), q);
-    v.w = csub(mul_shoup(v.w, sc.x, sc.y, q), q);
-    st4(row + pos * 256 + col0 + c, v);
-  }
-}
+// Column stages of a base conversion, one work-group per (column tile, group
+// of output rows): every input limb's INTT column pass, its scaling, the
+// conversion to each output row and that row's NTT column pass.  All three
+// work down the columns, so a tile of 512 words per limb needs nothing from
+// outside it: between the two transforms nothing goes through memory (three
+// kernels wrote and read the scaled inputs and the converted rows before).
+//   CONV_UP:   digit blockIdx.y / groups of y -> its ModUp rows z
+//   CONV_DOWN: component blockIdx.y / groups: the P rows of acc -> w
+// A wave takes two limbs at a time, one per half.  The waves first share out
+// the input limbs, whose scaled columns stay in LDS, then draw the output rows
+// from a counter, so that an odd number of rows or waves per SIMD does not
+// leave one idle.  Each group of output rows repeats the input transforms, so
+// a launch uses one group unless its work-groups would not fill the chip
+// (conv_groups).  Bound: vector arithmetic, about 900 instructions a wave for
+// a pair of rows (a multiply-add per input limb and half a transform a word)
+// and 650 for a pair of inputs: 78% of the issue slots at 16 rotations.
+// N = 2^16, L = 36, 12 + 12 limbs: ModUp 43.5 us in three kernels -> 28.4,
+// ModDown 32.1 -> 19.9; ModDown of 16 rotations 274 -> 202.  Two limbs a wave
+// instead of one (tiles of 1024 words, half the work-groups, so twice the
+// groups): 34.8 -> 28.4 and 24.1 -> 19.9.
+enum ConvMode : int { CONV_UP = 0, CONV_DOWN = 1 };
+constexpr int kConvWaves = 8;
 
-// ModUp BConv of digit j: z[j][r] = sum_i y[j alpha + i] T_{L,j}[r][i] mod prime(r) for every
-// row r outside the digit.  Rows of a block: [g * RB, g * RB + RB); blockIdx.y = j * groups + g.
-// Table columns past a partial digit are zero, so every input load is unconditional.
-template <int ALPHA, int RB>
-__global__ __launch_bounds__(kWG) void k3_bconv_up(KsConst K, JobArg<KsJob> JA, int groups) {
+template <int LOGN1, int MODE, int NY>
+__global__ __launch_bounds__(64 * kConvWaves, 4) void kc_conv(KsConst K, JobArg<KsJob> JA, int groups) {
+  using CH = ColHalf<LOGN1>;
+  static_assert(NY % 4 == 0, "base conversion in steps of four limbs");
   const KsJob J = JA.get(blockIdx.z);
-  if (J.kind == KS_HOIST) return;
-  const int j = blockIdx.y / groups, g = blockIdx.y % groups;
   const size_t N = (size_t)1 << K.T.logN;
   const KsView V = ks_view(J, K, N);
-  if (j >= V.beta || g * RB >= V.R) return;
-  const int lo = j * ALPHA, hi = min(lo + ALPHA, V.L);
-  const size_t n = ((size_t)blockIdx.x * kWG + threadIdx.x) * 4;  // four coefficients per thread
-  uint4 x[ALPHA];
+  const int tile = blockIdx.x;
+  const int jd = blockIdx.y / groups, g = blockIdx.y % groups;
+  int lo = 0, nin, nout;  // first input limb, inputs, output rows
+  if (MODE == CONV_UP) {
+    if (J.kind == KS_HOIST || jd >= V.beta) return;
+    lo = jd * K.alpha;
+    nin = min(K.alpha, V.L - lo);
+    nout = V.R - nin;
+  } else {
+    nin = K.k;
+    nout = V.L;
+  }
+  const int per = (nout + groups - 1) / groups;
+  const int o0 = g * per, o1 = min(o0 + per, nout);
+  if (o0 >= o1) return;
+  __shared__ __align__(16) uint32_t y[NY * 512];
+  __shared__ __align__(16) uint32_t xch[kConvWaves * 2 * CH::XCH];
+  __shared__ __align__(16) uint32_t Ts[kMaxPrimes * NY];  // the group's rows of the table, zero past nin
+  __shared__ int next;
+  const int lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t* x = xch + (2 * w + half) * CH::XCH;
+  auto row_of = [&](int o) { return MODE == CONV_UP && o >= lo ? o + nin : o; };
+
+  const uint32_t* T = MODE == CONV_UP ? K.M.modup_T + ldc(K.modup_T_off + (size_t)V.L * K.beta_max + jd) : K.M.moddown_T;
+  const int stride = MODE == CONV_UP ? K.alpha : K.k;
+  for (int e = threadIdx.x; e < (o1 - o0) * NY; e += 64 * kConvWaves) {
+    const int o = e / NY, i = e % NY;
+    Ts[e] = i < nin ? ld1(T + (size_t)row_of(o0 + o) * stride + i) : 0;
+  }
+  if (threadIdx.x == 0) next = 2 * kConvWaves;
+  for (int i0 = 2 * w; i0 < nin; i0 += 2 * kConvWaves) {
+    const int i = min(i0 + half, nin - 1);  // an odd last limb: both halves, the same words
+    const int pi = MODE == CONV_UP ? lo + i : K.T.L_max + i;
+    const uint32_t* src = MODE == CONV_UP ? V.y + (size_t)(lo + i) * N
+                                          : V.acc + ((size_t)jd * V.R + V.L + i) * N;
+    uint32_t v[16];
+    typename CH::Tw tw;
+    CH::load(v, src, tile, n);
+    tw.load(K.M.col_itw(K.T, pi), n);
+    const MontQ m = mont_q_load(K.T.mod + pi);
+    const uint32_t sc = ld1(MODE == CONV_UP ? K.M.modup_scale + (size_t)V.L * K.T.L_max + pi
+                                            : K.M.moddown_scale + i);
+    CH::inverse(v, x, tw, m, n);
 #pragma unroll
-  for (int i = 0; i < ALPHA; ++i) x[i] = ld4(V.y + (size_t)min(lo + i, V.L - 1) * N + n);
-  const uint32_t* Tt = K.modup_T + ldc(K.modup_T_off + (size_t)V.L * K.beta_max + j);
-  const int r1 = min(g * RB + RB, V.R);
-  for (int r = g * RB; r < r1; ++r) {
-    if (r >= lo && r < hi) continue;
-    const ModC m = ldc(K.T.mod + ks_pidx(r, V.L, K.T.L_max));
-    const uint32_t* t = Tt + (size_t)r * ALPHA;
-    uint64_t a0 = 0, a1 = 0, a2 = 0, a3 = 0;
+    for (int k = 0; k < 16; ++k) v[k] = csub(mont_mul(v[k], sc, m), m.q);
 #pragma unroll
-    for (int i = 0; i < ALPHA; ++i) {
-      const uint64_t ti = ldc(t + i);
-      a0 += x[i].x * ti;
-      a1 += x[i].y * ti;
-      a2 += x[i].z * ti;
-      a3 += x[i].w * ti;
+    for (int k = 0; k < 4; ++k)
+      *reinterpret_cast<uint4*>(y + i * 512 + k * 128 + n * 4) =
+          make_uint4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+  }
+  __syncthreads();
+
+  for (int u = 2 * w; u < o1 - o0;) {
+    const int o = min(o0 + u + half, o1 - 1);
+    const int r = row_of(o);
+    const int pi = MODE == CONV_UP ? ks_pidx(r, V.L, K.T.L_max) : r;
+    typename CH::Tw tw;
+    tw.load(K.M.col_tw(K.T, pi), n);
+    const MontQ m = mont_q_load(K.T.mod + pi);
+    int un = 0;
+    if (lane == 0) un = atomicAdd(&next, 2);
+    const uint32_t* t = Ts + (o - o0) * NY;
+    uint64_t a[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) a[k] = 0;
+    for (int i0 = 0; i0 < nin; i0 += 4) {
+      const uint4 t4 = *reinterpret_cast<const uint4*>(t + i0);
+      const uint32_t ts[4] = {t4.x, t4.y, t4.z, t4.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint4 c = *reinterpret_cast<const uint4*>(y + (i0 + i) * 512 + k * 128 + n * 4);
+          a[4 * k] += (uint64_t)c.x * ts[i];
+          a[4 * k + 1] += (uint64_t)c.y * ts[i];
+          a[4 * k + 2] += (uint64_t)c.z * ts[i];
+          a[4 * k + 3] += (uint64_t)c.w * ts[i];
+        }
     }
-    st4(V.z + ((size_t)j * V.R + r) * N + n,
-        make_uint4(reduce64(a0, m.q, m.mu_hi, m.mu_lo), reduce64(a1, m.q, m.mu_hi, m.mu_lo),
-                   reduce64(a2, m.q, m.mu_hi, m.mu_lo), reduce64(a3, m.q, m.mu_hi, m.mu_lo)));
+    // Montgomery reduction of the sum (the table carries 2^32): with T < q and
+    // inputs below 2^30 its high word is below nin q / 4, so for up to 12
+    // inputs the result lies in (0, 4q) at once; past 12, one correction first.
+    uint32_t v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      uint32_t hi = (uint32_t)(a[k] >> 32);
+      if (NY > 12) hi = csub(hi, m.q2);
+      v[k] = hi + m.q - __umulhi((uint32_t)a[k] * (0u - m.qn), m.q);
+    }
+    CH::forward(v, x, tw, m, n);
+    uint32_t* dst = MODE == CONV_UP ? V.z + ((size_t)jd * V.R + r) * N : V.w + ((size_t)jd * V.L + r) * N;
+    CH::store(v, x, dst, tile, n, half == 0 || u + 1 < o1 - o0);
+    u = __builtin_amdgcn_readfirstlane(un);
   }
 }
 
-template <int LOGN1, int CW, int T>
-__global__ __launch_bounds__(T) void k4_ntt_cols(KsConst K, JobArg<KsJob> JA) {
-  const KsJob J = JA.get(blockIdx.z);
-  if (J.kind == KS_HOIST) return;
-  const size_t N = (size_t)1 << K.T.logN;
-  const KsView V = ks_view(J, K, N);
-  const int gr = blockIdx.y;
-  const int j = gr / V.R, r = gr % V.R;
-  if (j >= V.beta) return;
-  const int lo = j * K.alpha, hi = min(lo + K.alpha, V.L);
-  if (r >= lo && r < hi) return;
-  __shared__ __align__(16) uint32_t s[ColGeom<LOGN1, CW, T>::LDS];
-  const int pi = ks_pidx(r, V.L, K.T.L_max);
-  __shared__ uint2 stw[ColGeom<LOGN1, CW, T>::N1];
-  const uint2 tww = tw_fetch(K.T.col_tw(pi), ColGeom<LOGN1, CW, T>::N1);
-  const uint32_t q = ldc(K.T.mod + pi).q, q2 = 2 * q;
-  const int col0 = blockIdx.x * ColGeom<LOGN1, CW, T>::C;
-  uint32_t* row = V.z + (size_t)gr * N;
-  load_cols<LOGN1, CW, T>(s, row, col0);
-  tw_put(stw, tww, ColGeom<LOGN1, CW, T>::N1);
-  __syncthreads();
-  col_stages<LOGN1, false, CW, T>(s, stw, q, q2);
-  __syncthreads();
-  store_cols<LOGN1, CW, T>(s, row, col0);
-}
-
-// ModUp-only jobs: the block pass of the new rows of M (K4 left them after the
-// column pass), canonical output in place, so that M is wholly in the
-// evaluation domain for the hoisted rotations' gathers.
-template <int LOGN1>
+// ModUp-only jobs: the block pass of the new rows of M (left after the column
+// pass, in the row-group layout), canonical output in row order in place (a
+// work-group's rows are the same 16 KiB in both layouts), so that M is wholly in
+// the evaluation domain for the hoisted rotations' gathers.
 __global__ __launch_bounds__(kWG) void km_ntt_blks(KsConst K, JobArg<KsJob> JA) {
   const KsJob J = JA.get(blockIdx.z);
   if (J.kind != KS_MODUP) return;
@@ -297,36 +316,85 @@ __global__ __launch_bounds__(kWG) void km_ntt_blks(KsConst K, JobArg<KsJob> JA) 
   if (j >= V.beta) return;
   const int lo = j * K.alpha, hi = min(lo + K.alpha, V.L);
   if (r >= lo && r < hi) return;
-  __shared__ __align__(16) uint32_t s[kLds];
-  __shared__ uint2 stw[256];
+  __shared__ __align__(16) uint32_t s[kBlkTile];
   const int pi = ks_pidx(r, V.L, K.T.L_max);
-  const uint2 tww = tw_fetch(K.T.blk_tw(pi), 256);
-  const uint32_t q = ldc(K.T.mod + pi).q, q2 = 2 * q;
-  const int blk0 = blockIdx.x * 16;
-  uint32_t* row = V.z + (size_t)gr * N + blk0 * 256;
+  const MontQ m = mont_q(ldc(K.T.mod + pi));
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  uint32_t* row = V.z + (size_t)gr * N + blockIdx.x * kTile;
+  BlkTw tw;
+  uint4 raw[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) raw[kk] = ld4(row + RowGroup<16>::word(threadIdx.x, kk, 0));
+  tw.load(K.M.row_tw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_tw(pi), lane);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) RowGroup<16>::to_lds(s, threadIdx.x, kk, raw[kk]);
+  __syncthreads();
+  blk_fwd_a(s, line, lane, tw, m);
+  wave_sync();
+  blk_fwd_b(s, line, lane, tw, m);
+  wave_sync();
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
-    lds_blk4_store(s, e, twist4(ld4(row + e), K.T.blk_twist(pi, blk0 + (e >> 8)), e & 255, q));
-  }
-  tw_put_perm(stw, tww);
-  __syncthreads();
-  blk_stages<false>(s, PermTw{stw}, q, q2);
-  __syncthreads();
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
-    st4(row + e, canon4(lds_blk4(s, e), q, q2));
+    const int pos = 4 * (lane & 15) + 64 * kk;
+    st4(row + line * 256 + pos, canon4(blk_quad(s, line, pos), m.q, m.q2));
   }
 }
 
 // ============================================================================
 // Stage 2: NTT block pass + inner product (+ first INTT pass of ModDown on P rows)
 // ============================================================================
-// HOIST selects the variant for hoisted-rotation jobs (gather of sigma(M), no
-// transform; each rotation brings its own key, streamed with the
+
+// P rows of the inner product: the INTT block pass that ModDown starts with,
+// on both components (res0, res1: the lane's four quads of its line), in LDS
+// tiles s and s + kBlkTile that other waves may still be reading; stored in the
+// row-group layout for the column kernel.
+__device__ __forceinline__ void p_rows_intt(uint32_t* s, const KsConst& K, int pi, const MontQ& m,
+                                            const uint4 res0[4], const uint4 res1[4], uint32_t* acc0,
+                                            uint32_t* acc1) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  BlkTw tw;
+  tw.load(K.M.row_itw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_itw(pi), lane);
+  __syncthreads();
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    const int pos = 4 * (lane & 15) + 64 * kk;
+    blk_quad_store(s, line, pos, res0[kk]);
+    blk_quad_store(s + kBlkTile, line, pos, res1[kk]);
+  }
+  wave_sync();
+  blk_inv_a(s, line, lane, tw, m);
+  blk_inv_a(s + kBlkTile, line, lane, tw, m);
+  wave_sync();
+  blk_inv_b(s, line, lane, tw, m);
+  blk_inv_b(s + kBlkTile, line, lane, tw, m);
+  __syncthreads();
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    const int at = RowGroup<16>::word(threadIdx.x, kk, 0);
+    st4(acc0 + at, RowGroup<16>::from_lds(s, threadIdx.x, kk));
+    st4(acc1 + at, RowGroup<16>::from_lds(s + kBlkTile, threadIdx.x, kk));
+  }
+}
+
+// Reduction of four 64-bit sums.
+__device__ __forceinline__ uint4 reduce4(const uint64_t a[4], const ModC& m) {
+  return make_uint4(reduce64(a[0], m.q, m.mu_hi, m.mu_lo), reduce64(a[1], m.q, m.mu_hi, m.mu_lo),
+                    reduce64(a[2], m.q, m.mu_hi, m.mu_lo), reduce64(a[3], m.q, m.mu_hi, m.mu_lo));
+}
+__device__ __forceinline__ void mac4(uint64_t a[4], uint4 v, uint4 e) {
+  a[0] += (uint64_t)v.x * e.x;
+  a[1] += (uint64_t)v.y * e.y;
+  a[2] += (uint64_t)v.z * e.z;
+  a[3] += (uint64_t)v.w * e.w;
+}
+
+// Any digit count: the digits in turn through one tile, accumulators in
+// registers.  HOIST selects the variant for hoisted-rotation jobs (gather of
+// sigma(M), no transform; each rotation brings its own key, streamed with the
 // non-temporal hint); the other variant serves every other job kind.
-template <int LOGN1, bool HOIST>
+template <bool HOIST>
 __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> JA, int part) {
   const KsJob J = JA.get(blockIdx.z);
   const int logN = K.T.logN;
@@ -334,21 +402,22 @@ __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> J
   const KsView V = ks_view(J, K, N);
   const int r = blockIdx.y + (part == KS_PART_P ? V.L : 0);
   if (r >= V.R || (part == KS_PART_Q && r >= V.L) || (J.kind == KS_HOIST) != HOIST) return;
-  __shared__ __align__(16) uint32_t s[kLds];
+  __shared__ __align__(16) uint32_t s[2 * kBlkTile];
   const int pi = ks_pidx(r, V.L, K.T.L_max);
-  __shared__ uint2 stw[256], stwi[256];
-  // twiddles: requested now, stored to LDS after the first tile's loads
-  const uint2 tww = HOIST ? make_uint2(0, 0) : tw_fetch(K.T.blk_tw(pi), 256);
-  const uint2 twwi = r >= V.L ? tw_fetch(K.T.blk_itw(pi), 256) : make_uint2(0, 0);
-  bool tw_staged = false;
-  const ModC m = ldc(K.T.mod + pi);
-  const uint32_t q = m.q, q2 = 2 * q;
-  const int blk0 = blockIdx.x * 16;
-  const uint32_t base = blk0 * 256;
+  const ModC mc = ldc(K.T.mod + pi);
+  const MontQ m = mont_q(mc);
+  const uint32_t base = blockIdx.x * kTile;
   const size_t KR = (size_t)K.T.L_max + K.k;  // key rows
-  uint64_t a0[16], a1[16];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  const uint32_t n0 = base + line * 256 + 4 * (lane & 15);  // the lane's quads: n0 + 64 kk
+  BlkTw tw;
+  if (!HOIST) tw.load(K.M.row_tw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_tw(pi), lane);
+  uint64_t a0[4][4], a1[4][4];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) a0[i] = a1[i] = 0;
+  for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a0[kk][i] = a1[kk][i] = 0;
 
   for (int j = 0; j < V.beta; ++j) {
     const int lo = j * K.alpha, hi = min(lo + K.alpha, V.L);
@@ -358,105 +427,68 @@ __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> J
       const uint32_t* Mrow = J.b + ((size_t)j * V.R + r) * N;
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        const uint32_t n = base + blk_elem(kk);
+        const uint32_t n = n0 + 64 * kk;
         v[kk] = make_uint4(ld1(Mrow + auto_src(n, J.gal, logN)), ld1(Mrow + auto_src(n + 1, J.gal, logN)),
                            ld1(Mrow + auto_src(n + 2, J.gal, logN)), ld1(Mrow + auto_src(n + 3, J.gal, logN)));
       }
     } else if (r >= lo && r < hi) {
       // digit rows are the switched polynomial itself (kept by K1 unless it is the input)
-      const uint32_t* drow = (J.kind == KS_PLAIN ? J.a : V.de) + (size_t)r * N + base;
+      const uint32_t* drow = (J.kind == KS_PLAIN ? J.a : V.de) + (size_t)r * N + n0;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) v[kk] = ld4(drow + blk_elem(kk));
+      for (int kk = 0; kk < 4; ++kk) v[kk] = ld4(drow + 64 * kk);
     } else {
       const uint32_t* zrow = V.z + ((size_t)j * V.R + r) * N + base;
       __syncthreads();  // the previous digit's tile has been read
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const int e = blk_elem(kk);
-        lds_blk4_store(s, e, twist4(ld4(zrow + e),
-                                    K.T.blk_twist(pi, blk0 + (e >> 8)), e & 255, q));
-      }
-      if (!tw_staged) {
-        tw_put_perm(stw, tww);
-        tw_staged = true;
-      }
+      for (int kk = 0; kk < 4; ++kk)
+        RowGroup<16>::to_lds(s, threadIdx.x, kk, ld4(zrow + RowGroup<16>::word(threadIdx.x, kk, 0)));
       __syncthreads();
-      blk_stages<false>(s, PermTw{stw}, q, q2);
-      __syncthreads();
+      blk_fwd_a(s, line, lane, tw, m);
+      wave_sync();
+      blk_fwd_b(s, line, lane, tw, m);
+      wave_sync();
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) v[kk] = canon4(lds_blk4(s, blk_elem(kk)), q, q2);
+      for (int kk = 0; kk < 4; ++kk) v[kk] = canon4(blk_quad(s, line, 4 * (lane & 15) + 64 * kk), m.q, m.q2);
     }
-    const uint32_t* k0 = J.key + ((size_t)j * 2 * KR + pi) * N + base;
+    const uint32_t* k0 = J.key + ((size_t)j * 2 * KR + pi) * N + n0;
     const uint32_t* k1 = k0 + KR * N;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      const uint4 e0 = HOIST ? ld4nt(k0 + blk_elem(kk)) : ld4(k0 + blk_elem(kk));
-      a0[4 * kk + 0] += (uint64_t)v[kk].x * e0.x;
-      a0[4 * kk + 1] += (uint64_t)v[kk].y * e0.y;
-      a0[4 * kk + 2] += (uint64_t)v[kk].z * e0.z;
-      a0[4 * kk + 3] += (uint64_t)v[kk].w * e0.w;
-    }
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const uint4 e1 = HOIST ? ld4nt(k1 + blk_elem(kk)) : ld4(k1 + blk_elem(kk));
-      a1[4 * kk + 0] += (uint64_t)v[kk].x * e1.x;
-      a1[4 * kk + 1] += (uint64_t)v[kk].y * e1.y;
-      a1[4 * kk + 2] += (uint64_t)v[kk].z * e1.z;
-      a1[4 * kk + 3] += (uint64_t)v[kk].w * e1.w;
+      mac4(a0[kk], v[kk], HOIST ? ld4nt(k0 + 64 * kk) : ld4(k0 + 64 * kk));
+      mac4(a1[kk], v[kk], HOIST ? ld4nt(k1 + 64 * kk) : ld4(k1 + 64 * kk));
     }
     // Each product of canonical words is below q^2 < 2^60, so 16 of them fit
     // a 64-bit sum; chains of more digits (digit size 1 allows up to 63) fold
     // the sums back below q after every eighth digit.
     if ((j & 7) == 7) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        a0[i] = reduce64(a0[i], q, m.mu_hi, m.mu_lo);
-        a1[i] = reduce64(a1[i], q, m.mu_hi, m.mu_lo);
-      }
+      for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          a0[kk][i] = reduce64(a0[kk][i], mc.q, mc.mu_hi, mc.mu_lo);
+          a1[kk][i] = reduce64(a1[kk][i], mc.q, mc.mu_hi, mc.mu_lo);
+        }
     }
   }
 
   // one reduction per output (the overflow-free accumulation of Sec. III-C2)
-  uint32_t r0[16], r1[16];
+  uint4 r0[4], r1[4];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    r0[i] = reduce64(a0[i], q, m.mu_hi, m.mu_lo);
-    r1[i] = reduce64(a1[i], q, m.mu_hi, m.mu_lo);
+  for (int kk = 0; kk < 4; ++kk) {
+    r0[kk] = reduce4(a0[kk], mc);
+    r1[kk] = reduce4(a1[kk], mc);
   }
-  uint32_t* acc0 = V.acc + (size_t)r * N + base;
-  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N + base;
+  uint32_t* acc0 = V.acc + (size_t)r * N;
+  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
   if (r < V.L) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      const int e = blk_elem(kk);
-      st4(acc0 + e, make_uint4(r0[4 * kk], r0[4 * kk + 1], r0[4 * kk + 2], r0[4 * kk + 3]));
-      st4(acc1 + e, make_uint4(r1[4 * kk], r1[4 * kk + 1], r1[4 * kk + 2], r1[4 * kk + 3]));
+      st4(acc0 + n0 + 64 * kk, r0[kk]);
+      st4(acc1 + n0 + 64 * kk, r1[kk]);
     }
     return;
   }
-  // P rows: ModDown starts with an INTT; its block pass runs here on the tile
-  // (inverse twist factors requested before the transforms).
-  Twist4 tfi[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
-    tfi[kk] = twist4_load(K.T.blk_itwist(pi, blk0 + (e >> 8)), e & 255);
-  }
-  tw_put_perm(stwi, twwi);
-  for (int c = 0; c < 2; ++c) {
-    uint32_t* dst = c ? acc1 : acc0;
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const uint32_t* rr = c ? r1 : r0;
-      lds_blk4_store(s, blk_elem(kk), make_uint4(rr[4 * kk], rr[4 * kk + 1], rr[4 * kk + 2], rr[4 * kk + 3]));
-    }
-    __syncthreads();
-    blk_stages<true>(s, PermTw{stwi}, q, q2);
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) st4(dst + blk_elem(kk), twist4(lds_blk4(s, blk_elem(kk)), tfi[kk], q));
-  }
+  p_rows_intt(s, K, pi, m, r0, r1, acc0 + base, acc1 + base);
 }
 
 // Variant of K5 for contexts with at most NB digits: every digit's tile is
@@ -465,7 +497,7 @@ __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> J
 // 64-bit accumulators never hold more than four elements per component.
 // NT: the key words are read with the non-temporal hint (a launch of one
 // job reads its key once; batches whose jobs share a key keep it cached).
-template <int LOGN1, int NB, bool NT>
+template <int NB, bool NT>
 __global__ __launch_bounds__(kWG) void k5s_ntt_blks_ip(KsConst K, JobArg<KsJob> JA, int part) {
   const KsJob J = JA.get(blockIdx.z);
   const int logN = K.T.logN;
@@ -473,86 +505,78 @@ __global__ __launch_bounds__(kWG) void k5s_ntt_blks_ip(KsConst K, JobArg<KsJob> 
   const KsView V = ks_view(J, K, N);
   const int r = blockIdx.y + (part == KS_PART_P ? V.L : 0);
   if (r >= V.R || (part == KS_PART_Q && r >= V.L) || J.kind == KS_HOIST) return;
-  __shared__ __align__(16) uint32_t s[NB * kLds];
+  __shared__ __align__(16) uint32_t s[NB * kBlkTile];
   const int pi = ks_pidx(r, V.L, K.T.L_max);
-  const ModC m = ldc(K.T.mod + pi);
-  const uint32_t q = m.q, q2 = 2 * q;
-  const int blk0 = blockIdx.x * 16;
-  const uint32_t base = blk0 * 256;
+  const ModC mc = ldc(K.T.mod + pi);
+  const MontQ m = mont_q(mc);
+  const uint32_t base = blockIdx.x * kTile;
   const size_t KR = (size_t)K.T.L_max + K.k;  // key rows
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  const uint32_t n0 = base + line * 256 + 4 * (lane & 15);  // the lane's quads: n0 + 64 kk
 
   // Every load of the staging is issued before any of them is used, in
   // straight-line code (a branch between them would make the compiler wait
-  // for the earlier ones), in the order they are consumed (vmcnt counts in
-  // order): the block-pass twiddles for the pads of slots 0 and 1 (so the
-  // transforms issue no global load), the twist factors of the thread's
-  // quads (shared by all digits: they depend on the prime and the block),
-  // each digit's tile -- the digit row itself for the digit that holds r,
-  // else its ModUp row; digits past beta re-read the last digit's rows,
-  // unused -- and the key words of the first KPF quads, whose latency
-  // overlaps the transforms.
-  const uint2 tw_word = K.T.blk_tw(pi)[threadIdx.x];
-  Twist4 tf[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
-    tf[kk] = twist4_load(K.T.blk_twist(pi, blk0 + (e >> 8)), e & 255);
-  }
+  // for the earlier ones): each digit's tile -- the digit row itself, in row
+  // order, for the digit that holds r, else its ModUp row in the row-group
+  // layout; digits past beta re-read the last digit's rows, unused -- the
+  // twiddles, and the key words of the first KPF quads, whose latency overlaps
+  // the transforms.
   uint4 raw[NB][4];
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const int jj = min(j, V.beta - 1);
     const int lo = jj * K.alpha, hi = min(lo + K.alpha, V.L);
-    const uint32_t* src = (r >= lo && r < hi) ? (J.kind == KS_PLAIN ? J.a : V.de) + (size_t)r * N + base
-                                              : V.z + ((size_t)jj * V.R + r) * N + base;
+    const bool own = r >= lo && r < hi;
+    const uint32_t* src = own ? (J.kind == KS_PLAIN ? J.a : V.de) + (size_t)r * N
+                              : V.z + ((size_t)jj * V.R + r) * N + base;
+    const uint32_t at = own ? n0 : (uint32_t)RowGroup<16>::word(threadIdx.x, 0, 0);
+    const uint32_t step = own ? 64 : 1024;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) raw[j][kk] = ld4(src + blk_elem(kk));
+    for (int kk = 0; kk < 4; ++kk) raw[j][kk] = ld4(src + at + step * kk);
   }
-  // The inner product loads the key words of the quads past KPF itself: a
-  // third prefetched quad of three digits takes the registers past what three
-  // resident work-groups per CU leave (171 VGPRs against 168).
+  BlkTw tw;
+  tw.load(K.M.row_tw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_tw(pi), lane);
   constexpr int KPF = NB <= 2 ? 4 : 2;
   uint4 kpre0[4][NB], kpre1[4][NB];
   auto key_quad = [&](int kk) {
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const int jj = min(j, V.beta - 1);
-      const uint32_t* k0 = J.key + ((size_t)jj * 2 * KR + pi) * N + base + blk_elem(kk);
+      const uint32_t* k0 = J.key + ((size_t)min(j, V.beta - 1) * 2 * KR + pi) * N + n0 + 64 * kk;
       kpre0[kk][j] = NT ? ld4nt(k0) : ld4(k0);
       kpre1[kk][j] = NT ? ld4nt(k0 + KR * N) : ld4(k0 + KR * N);
     }
   };
 #pragma unroll
   for (int kk = 0; kk < KPF; ++kk) key_quad(kk);
-  stage_tw_pads_perm_word(s, tw_word);
-  // stage every digit's tile: the digit row as it is, a ModUp row twisted
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     if (j >= V.beta) break;
     const int lo = j * K.alpha, hi = min(lo + K.alpha, V.L);
-    uint32_t* slot = s + j * kLds;
+    uint32_t* slot = s + j * kBlkTile;
     if (r >= lo && r < hi) {
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) lds_blk4_store(slot, blk_elem(kk), raw[j][kk]);
+      for (int kk = 0; kk < 4; ++kk) blk_quad_store(slot, line, 4 * (lane & 15) + 64 * kk, raw[j][kk]);
     } else {
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) lds_blk4_store(slot, blk_elem(kk), twist4(raw[j][kk], tf[kk], q));
+      for (int kk = 0; kk < 4; ++kk) RowGroup<16>::to_lds(slot, threadIdx.x, kk, raw[j][kk]);
     }
   }
   __syncthreads();
-  // The block-pass transforms of all digit tiles, phase by phase: the tiles
-  // share the prime, so each phase's twiddles are fetched once for all of
-  // them, and there are two barrier intervals instead of two per tile.
-  const PadTwP tw{s};
+  // The block pass of all digit tiles, half by half; from here every wave
+  // works on its own four lines alone.
 #pragma unroll
-  for (int ph = 0; ph < 2; ++ph) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int lo = j * K.alpha, hi = min(lo + K.alpha, V.L);
-      if (j < V.beta && !(r >= lo && r < hi)) blk_phase<4, false>(s + j * kLds, ph ? 0 : 4, tw, q, q2);
-    }
-    __syncthreads();
+  for (int j = 0; j < NB; ++j) {
+    const int lo = j * K.alpha, hi = min(lo + K.alpha, V.L);
+    if (j < V.beta && !(r >= lo && r < hi)) blk_fwd_a(s + j * kBlkTile, line, lane, tw, m);
   }
+  wave_sync();
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int lo = j * K.alpha, hi = min(lo + K.alpha, V.L);
+    if (j < V.beta && !(r >= lo && r < hi)) blk_fwd_b(s + j * kBlkTile, line, lane, tw, m);
+  }
+  wave_sync();
 
   // inner product, one quad at a time (one reduction per output, Sec. III-C2).
   // No branch on the digit count: tiles past beta (never staged) are masked
@@ -560,79 +584,37 @@ __global__ __launch_bounds__(kWG) void k5s_ntt_blks_ip(KsConst K, JobArg<KsJob> 
   // The transformed words enter uncorrected: each lies in [0, 4q) and each
   // key word below q < 2^30, so a product is below 2^62 and the sum of at
   // most four (NB <= 4) stays below 2^64 for the single exact reduction.
-  static_assert(NB <= 4, "64-bit sum of lazy products");
+  static_assert(NB >= 2 && NB <= 4, "64-bit sum of lazy products; two slots for the P rows");
   uint4 res0[4], res1[4];
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
     uint64_t a0[4] = {0, 0, 0, 0}, a1[4] = {0, 0, 0, 0};
+    if (kk >= KPF) key_quad(kk);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const uint32_t msk = j < V.beta ? ~0u : 0u;
-      uint4 v = lds_blk4(s + j * kLds, e);
+      uint4 v = blk_quad(s + j * kBlkTile, line, 4 * (lane & 15) + 64 * kk);
       v.x &= msk;
       v.y &= msk;
       v.z &= msk;
       v.w &= msk;
-      if (kk >= KPF) {
-        const uint32_t* k0 = J.key + ((size_t)min(j, V.beta - 1) * 2 * KR + pi) * N + base + e;
-        kpre0[kk][j] = NT ? ld4nt(k0) : ld4(k0);
-        kpre1[kk][j] = NT ? ld4nt(k0 + KR * N) : ld4(k0 + KR * N);
-      }
-      const uint4 e0 = kpre0[kk][j], e1 = kpre1[kk][j];
-      a0[0] += (uint64_t)v.x * e0.x;
-      a0[1] += (uint64_t)v.y * e0.y;
-      a0[2] += (uint64_t)v.z * e0.z;
-      a0[3] += (uint64_t)v.w * e0.w;
-      a1[0] += (uint64_t)v.x * e1.x;
-      a1[1] += (uint64_t)v.y * e1.y;
-      a1[2] += (uint64_t)v.z * e1.z;
-      a1[3] += (uint64_t)v.w * e1.w;
+      mac4(a0, v, kpre0[kk][j]);
+      mac4(a1, v, kpre1[kk][j]);
     }
-    res0[kk] = make_uint4(reduce64(a0[0], q, m.mu_hi, m.mu_lo), reduce64(a0[1], q, m.mu_hi, m.mu_lo),
-                          reduce64(a0[2], q, m.mu_hi, m.mu_lo), reduce64(a0[3], q, m.mu_hi, m.mu_lo));
-    res1[kk] = make_uint4(reduce64(a1[0], q, m.mu_hi, m.mu_lo), reduce64(a1[1], q, m.mu_hi, m.mu_lo),
-                          reduce64(a1[2], q, m.mu_hi, m.mu_lo), reduce64(a1[3], q, m.mu_hi, m.mu_lo));
+    res0[kk] = reduce4(a0, mc);
+    res1[kk] = reduce4(a1, mc);
   }
-  uint32_t* acc0 = V.acc + (size_t)r * N + base;
-  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N + base;
+  uint32_t* acc0 = V.acc + (size_t)r * N;
+  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
   if (r < V.L) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      const int e = blk_elem(kk);
-      st4(acc0 + e, res0[kk]);
-      st4(acc1 + e, res1[kk]);
+      st4(acc0 + n0 + 64 * kk, res0[kk]);
+      st4(acc1 + n0 + 64 * kk, res1[kk]);
     }
     return;
   }
-  // P rows: the INTT block pass of ModDown on both components (slots 0 and 1),
-  // inverse twiddles in the same pads (the forward ones were last read before
-  // the barrier that ended the transforms); the inverse twist factors are
-  // requested first, so their latency overlaps the transforms
-  const uint2 twi_word = K.T.blk_itw(pi)[threadIdx.x];
-  Twist4 tfi[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
-    tfi[kk] = twist4_load(K.T.blk_itwist(pi, blk0 + (e >> 8)), e & 255);
-  }
-  __syncthreads();
-  stage_tw_pads_perm_word(s, twi_word);
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    lds_blk4_store(s, blk_elem(kk), res0[kk]);
-    lds_blk4_store(s + kLds, blk_elem(kk), res1[kk]);
-  }
-  __syncthreads();
-  blk_stages<true>(s, PadTwP{s}, q, q2);
-  blk_stages<true>(s + kLds, PadTwP{s}, q, q2);
-  __syncthreads();
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
-    st4(acc0 + e, twist4(lds_blk4(s, e), tfi[kk], q));
-    st4(acc1 + e, twist4(lds_blk4(s + kLds, e), tfi[kk], q));
-  }
+  p_rows_intt(s, K, pi, m, res0, res1, acc0 + base, acc1 + base);
 }
 
 // K5 for hoisted rotations of at most NB digits.  sigma_g maps each aligned
@@ -643,7 +625,7 @@ __global__ __launch_bounds__(kWG) void k5s_ntt_blks_ip(KsConst K, JobArg<KsJob> 
 // first KPF quads are requested with the tiles; the inner product and the
 // P-row INTT block pass follow as in k5s, on canonical words (M is fully
 // transformed).
-template <int LOGN1, int NB>
+template <int NB>
 __global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA, int part) {
   static_assert(NB >= 2 && NB <= 4, "slots for two to four digits");
   const KsJob J = JA.get(blockIdx.z);
@@ -652,14 +634,15 @@ __global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA
   const KsView V = ks_view(J, K, N);
   const int r = blockIdx.y + (part == KS_PART_P ? V.L : 0);
   if (r >= V.R || (part == KS_PART_Q && r >= V.L) || J.kind != KS_HOIST) return;
-  constexpr int WORDS = NB * kTile > 2 * kLds ? NB * kTile : 2 * kLds;
+  constexpr int WORDS = NB * kTile > 2 * kBlkTile ? NB * kTile : 2 * kBlkTile;
   __shared__ __align__(16) uint32_t s[WORDS];
   const int pi = ks_pidx(r, V.L, K.T.L_max);
-  const ModC m = ldc(K.T.mod + pi);
-  const uint32_t q = m.q;
-  const int blk0 = blockIdx.x * 16;
-  const uint32_t base = blk0 * 256;
+  const ModC mc = ldc(K.T.mod + pi);
+  const uint32_t base = blockIdx.x * kTile;
   const size_t KR = (size_t)K.T.L_max + K.k;  // key rows
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  const uint32_t n0 = base + line * 256 + 4 * (lane & 15);  // the lane's quads: n0 + 64 kk
   const uint32_t src0 = auto_src(base, J.gal, logN) & ~(uint32_t)(kTile - 1);
   // every digit's source tile (digits past beta re-read the last one, unused)
   uint4 raw[NB][4];
@@ -675,7 +658,7 @@ __global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA
   auto key_quad = [&](int kk) {
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const uint32_t* k0 = J.key + ((size_t)min(j, V.beta - 1) * 2 * KR + pi) * N + base + blk_elem(kk);
+      const uint32_t* k0 = J.key + ((size_t)min(j, V.beta - 1) * 2 * KR + pi) * N + n0 + 64 * kk;
       kpre0[kk][j] = ld4nt(k0);
       kpre1[kk][j] = ld4nt(k0 + KR * N);
     }
@@ -694,8 +677,7 @@ __global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA
   uint4 res0[4], res1[4];
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
-    const uint32_t n = base + e;
+    const uint32_t n = n0 + 64 * kk;
     const uint32_t p0 = auto_src(n, J.gal, logN) & (kTile - 1), p1 = auto_src(n + 1, J.gal, logN) & (kTile - 1),
                    p2 = auto_src(n + 2, J.gal, logN) & (kTile - 1), p3 = auto_src(n + 3, J.gal, logN) & (kTile - 1);
     if (kk >= KPF) key_quad(kk);
@@ -705,315 +687,156 @@ __global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA
       const uint32_t msk = j < V.beta ? ~0u : 0u;
       const uint32_t* sl = s + j * kTile;
       const uint4 v = make_uint4(sl[p0] & msk, sl[p1] & msk, sl[p2] & msk, sl[p3] & msk);
-      const uint4 e0 = kpre0[kk][j], e1 = kpre1[kk][j];
-      a0[0] += (uint64_t)v.x * e0.x;
-      a0[1] += (uint64_t)v.y * e0.y;
-      a0[2] += (uint64_t)v.z * e0.z;
-      a0[3] += (uint64_t)v.w * e0.w;
-      a1[0] += (uint64_t)v.x * e1.x;
-      a1[1] += (uint64_t)v.y * e1.y;
-      a1[2] += (uint64_t)v.z * e1.z;
-      a1[3] += (uint64_t)v.w * e1.w;
+      mac4(a0, v, kpre0[kk][j]);
+      mac4(a1, v, kpre1[kk][j]);
     }
-    res0[kk] = make_uint4(reduce64(a0[0], q, m.mu_hi, m.mu_lo), reduce64(a0[1], q, m.mu_hi, m.mu_lo),
-                          reduce64(a0[2], q, m.mu_hi, m.mu_lo), reduce64(a0[3], q, m.mu_hi, m.mu_lo));
-    res1[kk] = make_uint4(reduce64(a1[0], q, m.mu_hi, m.mu_lo), reduce64(a1[1], q, m.mu_hi, m.mu_lo),
-                          reduce64(a1[2], q, m.mu_hi, m.mu_lo), reduce64(a1[3], q, m.mu_hi, m.mu_lo));
+    res0[kk] = reduce4(a0, mc);
+    res1[kk] = reduce4(a1, mc);
   }
-  uint32_t* acc0 = V.acc + (size_t)r * N + base;
-  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N + base;
+  uint32_t* acc0 = V.acc + (size_t)r * N;
+  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
   if (r < V.L) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      const int e = blk_elem(kk);
-      st4(acc0 + e, res0[kk]);
-      st4(acc1 + e, res1[kk]);
+      st4(acc0 + n0 + 64 * kk, res0[kk]);
+      st4(acc1 + n0 + 64 * kk, res1[kk]);
     }
     return;
   }
-  // P rows: the INTT block pass of ModDown on both components, as in k5s
-  const uint32_t q2 = 2 * q;
-  const uint2 twi_word = K.T.blk_itw(pi)[threadIdx.x];
-  Twist4 tfi[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
-    tfi[kk] = twist4_load(K.T.blk_itwist(pi, blk0 + (e >> 8)), e & 255);
-  }
-  __syncthreads();  // the gathers have read the slots
-  stage_tw_pads_perm_word(s, twi_word);
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    lds_blk4_store(s, blk_elem(kk), res0[kk]);
-    lds_blk4_store(s + kLds, blk_elem(kk), res1[kk]);
-  }
-  __syncthreads();
-  blk_stages<true>(s, PadTwP{s}, q, q2);
-  blk_stages<true>(s + kLds, PadTwP{s}, q, q2);
-  __syncthreads();
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
-    st4(acc0 + e, twist4(lds_blk4(s, e), tfi[kk], q));
-    st4(acc1 + e, twist4(lds_blk4(s + kLds, e), tfi[kk], q));
-  }
+  p_rows_intt(s, K, pi, mont_q(mc), res0, res1, acc0 + base, acc1 + base);
 }
 
-// K5 for small grids (few tiles x rows, e.g. N = 2^12): one work-group per
-// (tile, row) of BPW blocks (16: a whole 4096-word tile, 1024 threads; 4: a
-// quarter tile, 256 threads, four times the work-groups for the same rows).
-// Thread group d = threadIdx.x / (16 BPW) stages and transforms digit tile d,
-// so the digits' transforms run side by side; then every thread forms the
-// inner product of one quad over all digits.  Every barrier below is reached
-// by all threads of the work-group.  The slots keep the full tile stride, so
-// the twiddle table fits the pads of slots 0 and 1 for either BPW.
-template <int BPW, int EPT>
-constexpr int k5p_threads() { return 4 * BPW * 256 / EPT; }
-template <int LOGN1, int NB, int BPW, int EPT>
-__global__ __launch_bounds__((k5p_threads<BPW, EPT>())) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJob> JA,
-                                                                           int part) {
-  static_assert(NB >= 2 && NB <= 4, "one thread group per digit tile");
-  static_assert((EPT == 16 && (BPW == 4 || BPW == 16)) || (EPT == 4 && (BPW == 2 || BPW == 4)),
-                "radix-16 phases on 16 elements per thread, radix-4 phases on 4");
-  constexpr int GS = BPW * 256 / EPT;  // threads per digit group
-  constexpr int QPG = EPT / 4;         // quads per thread in a group's tile
-  constexpr int TQ = BPW * 64;         // quads of the tile: one per inner-product thread
+// K5 for small grids (few tiles x rows): one work-group per four rows of a
+// limb, one wave per digit, so the digits' transforms run side by side; then
+// the threads share out the inner product's 256 quads, and for P rows waves 0
+// and 1 take a component each.  Four times the work-groups of k5s and a third
+// of its chain per wave.  Every barrier below is reached by all threads.
+template <int NB>
+__global__ __launch_bounds__(64 * NB) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJob> JA, int part) {
+  static_assert(NB >= 2 && NB <= 4, "one wave per digit");
+  constexpr int T = 64 * NB;
+  constexpr int QPT = (256 + T - 1) / T;  // quads per thread of the inner product, at most
+  constexpr int TILE4 = 4 * kBlkS;
   const KsJob J = JA.get(blockIdx.z);
   const int logN = K.T.logN;
   const size_t N = (size_t)1 << logN;
   const KsView V = ks_view(J, K, N);
   const int r = blockIdx.y + (part == KS_PART_P ? V.L : 0);
   if (r >= V.R || (part == KS_PART_Q && r >= V.L) || J.kind == KS_HOIST) return;
-  __shared__ __align__(16) uint32_t s[NB * kLds];
+  __shared__ __align__(16) uint32_t s[NB * TILE4];
   const int pi = ks_pidx(r, V.L, K.T.L_max);
-  const ModC m = ldc(K.T.mod + pi);
-  const uint32_t q = m.q, q2 = 2 * q;
-  const int blk0 = blockIdx.x * BPW;
-  const uint32_t base = blk0 * 256;
-  const size_t KR = (size_t)K.T.L_max + K.k;  // key rows
-  const int grp = threadIdx.x / GS, lt = threadIdx.x % GS;
-  // digit this thread group owns, and whether its tile needs the transform
-  const int lo = grp * K.alpha, hi = min(lo + K.alpha, V.L);
-  const bool have = grp < NB && grp < V.beta;
+  const ModC mc = ldc(K.T.mod + pi);
+  const MontQ m = mont_q(mc);
+  const int a4 = blockIdx.x & 3;                        // which four rows of the group of 16
+  const uint32_t group = (blockIdx.x >> 2) * kTile;     // the group's first word
+  const uint32_t base = blockIdx.x * 1024;              // the four rows' first word in row order
+  const size_t KR = (size_t)K.T.L_max + K.k;            // key rows
+  const int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int line = blk_line<4>(lane, 0);
+  const int lo = j * K.alpha, hi = min(lo + K.alpha, V.L);
   const bool own = r >= lo && r < hi;
-  if (have) {
-    uint32_t* slot = s + grp * kLds;
-    uint4 v[QPG];
+  uint32_t* slot = s + j * TILE4;
+  BlkTw tw;
+  tw.load(K.M.row_tw(K.T, pi, blockIdx.x * 4 + line), K.M.blk_tw(pi), lane);
+  if (j < V.beta) {
+    uint4 v[4];
     if (own) {
-      const uint32_t* drow = (J.kind == KS_PLAIN ? J.a : V.de) + (size_t)r * N + base;
+      const uint32_t* drow = (J.kind == KS_PLAIN ? J.a : V.de) + (size_t)r * N + base + line * 256 + 4 * (lane & 15);
 #pragma unroll
-      for (int kk = 0; kk < QPG; ++kk) v[kk] = ld4(drow + (lt + kk * GS) * 4);
+      for (int kk = 0; kk < 4; ++kk) v[kk] = ld4(drow + 64 * kk);
 #pragma unroll
-      for (int kk = 0; kk < QPG; ++kk) lds_blk4_store(slot, (lt + kk * GS) * 4, v[kk]);
+      for (int kk = 0; kk < 4; ++kk) blk_quad_store(slot, line, 4 * (lane & 15) + 64 * kk, v[kk]);
     } else {
-      const uint32_t* zrow = V.z + ((size_t)grp * V.R + r) * N + base;
+      const uint32_t* zrow = V.z + ((size_t)j * V.R + r) * N + group;
 #pragma unroll
-      for (int kk = 0; kk < QPG; ++kk) v[kk] = ld4(zrow + (lt + kk * GS) * 4);
+      for (int kk = 0; kk < 4; ++kk) v[kk] = ld4(zrow + RowGroup<4>::word(lane, kk, a4));
 #pragma unroll
-      for (int kk = 0; kk < QPG; ++kk) {
-        const int e = (lt + kk * GS) * 4;
-        lds_blk4_store(slot, e, twist4(v[kk], K.T.blk_twist(pi, blk0 + (e >> 8)), e & 255, q));
-      }
+      for (int kk = 0; kk < 4; ++kk) RowGroup<4>::to_lds(slot, lane, kk, v[kk]);
     }
   }
-  if (threadIdx.x < 256) {
-    if constexpr (EPT == 16)
-      stage_tw_pads_perm(s, K.T.blk_tw(pi), threadIdx.x);
-    else
-      stage_tw_pads(s, K.T.blk_tw(pi), threadIdx.x);
-  }
-  // key words of this thread's quad, requested before the transforms (the
-  // first TQ threads form the inner product: all of them when EPT = 16)
-  const bool ipt = EPT == 16 || (int)threadIdx.x < TQ;
-  const int e = ipt ? threadIdx.x * 4 : 0;
-  uint4 k0v[NB], k1v[NB];
+  // key words of this thread's quads, requested before the transforms (past
+  // the last quad or digit they repeat earlier ones, unused)
+  uint4 k0v[QPT][NB], k1v[QPT][NB];
 #pragma unroll
-  for (int jj = 0; jj < NB; ++jj) {
-    const uint32_t* k0 = J.key + ((size_t)min(jj, V.beta - 1) * 2 * KR + pi) * N + base + e;
-    k0v[jj] = ld4(k0);
-    k1v[jj] = ld4(k0 + KR * N);
-  }
-  __syncthreads();
-  const PadTw tw{s};
-  if constexpr (EPT == 16) {
-    const PadTwP twp{s};
-    if (have && !own) blk_phase<4, false>(s + grp * kLds, 4, twp, q, q2, lt);
-    __syncthreads();
-    if (have && !own) blk_phase<4, false>(s + grp * kLds, 0, twp, q, q2, lt);
-  } else {
+  for (int i = 0; i < QPT; ++i) {
+    const uint32_t e = 4 * min((int)threadIdx.x + i * T, 255);
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      if (p) __syncthreads();
-      if (have && !own) blk_phase<2, false, PadTw, 4, GS>(s + grp * kLds, 6 - 2 * p, tw, q, q2, lt);
+    for (int jj = 0; jj < NB; ++jj) {
+      const uint32_t* k0 = J.key + ((size_t)min(jj, V.beta - 1) * 2 * KR + pi) * N + base + e;
+      k0v[i][jj] = ld4(k0);
+      k1v[i][jj] = ld4(k0 + KR * N);
     }
+  }
+  if (j < V.beta && !own) {
+    wave_sync();
+    blk_fwd_a(slot, line, lane, tw, m);
+    wave_sync();
+    blk_fwd_b(slot, line, lane, tw, m);
   }
   __syncthreads();
 
-  // inner product of quad e over the digits (one reduction per output); the
-  // lazy words in [0, 4q) enter uncorrected, as in k5s (NB <= 4 products of
-  // at most 2^62 each)
-  uint64_t a0[4] = {0, 0, 0, 0}, a1[4] = {0, 0, 0, 0};
+  // inner product (one reduction per output); the lazy words in [0, 4q) enter
+  // uncorrected, as in k5s (NB <= 4 products of at most 2^62 each)
+  uint4 res0[QPT], res1[QPT];
 #pragma unroll
-  for (int jj = 0; jj < NB; ++jj) {
-    const uint32_t msk = jj < V.beta ? ~0u : 0u;
-    uint4 v = lds_blk4(s + jj * kLds, e);
-    v.x &= msk;
-    v.y &= msk;
-    v.z &= msk;
-    v.w &= msk;
-    a0[0] += (uint64_t)v.x * k0v[jj].x;
-    a0[1] += (uint64_t)v.y * k0v[jj].y;
-    a0[2] += (uint64_t)v.z * k0v[jj].z;
-    a0[3] += (uint64_t)v.w * k0v[jj].w;
-    a1[0] += (uint64_t)v.x * k1v[jj].x;
-    a1[1] += (uint64_t)v.y * k1v[jj].y;
-    a1[2] += (uint64_t)v.z * k1v[jj].z;
-    a1[3] += (uint64_t)v.w * k1v[jj].w;
+  for (int i = 0; i < QPT; ++i) {
+    const int e = 4 * min((int)threadIdx.x + i * T, 255);
+    uint64_t a0[4] = {0, 0, 0, 0}, a1[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int jj = 0; jj < NB; ++jj) {
+      const uint32_t msk = jj < V.beta ? ~0u : 0u;
+      uint4 v = blk_quad(s + jj * TILE4, e >> 8, e & 255);
+      v.x &= msk;
+      v.y &= msk;
+      v.z &= msk;
+      v.w &= msk;
+      mac4(a0, v, k0v[i][jj]);
+      mac4(a1, v, k1v[i][jj]);
+    }
+    res0[i] = reduce4(a0, mc);
+    res1[i] = reduce4(a1, mc);
   }
-  const uint4 res0 = make_uint4(reduce64(a0[0], q, m.mu_hi, m.mu_lo), reduce64(a0[1], q, m.mu_hi, m.mu_lo),
-                                reduce64(a0[2], q, m.mu_hi, m.mu_lo), reduce64(a0[3], q, m.mu_hi, m.mu_lo));
-  const uint4 res1 = make_uint4(reduce64(a1[0], q, m.mu_hi, m.mu_lo), reduce64(a1[1], q, m.mu_hi, m.mu_lo),
-                                reduce64(a1[2], q, m.mu_hi, m.mu_lo), reduce64(a1[3], q, m.mu_hi, m.mu_lo));
-  uint32_t* acc0 = V.acc + (size_t)r * N + base;
-  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N + base;
+  uint32_t* acc0 = V.acc + (size_t)r * N;
+  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
   if (r < V.L) {  // uniform over the work-group
-    if (ipt) {
-      st4(acc0 + e, res0);
-      st4(acc1 + e, res1);
+#pragma unroll
+    for (int i = 0; i < QPT; ++i) {
+      const int e = 4 * (threadIdx.x + i * T);
+      if (e < 1024) {
+        st4(acc0 + base + e, res0[i]);
+        st4(acc1 + base + e, res1[i]);
+      }
     }
     return;
   }
-  // P rows: the INTT block pass of ModDown, component c in slot c by thread
-  // group c; inverse twiddles in the same pads (the forward ones were last
-  // read before the previous barrier)
-  __syncthreads();
-  if (ipt) {
-    lds_blk4_store(s, e, res0);
-    lds_blk4_store(s + kLds, e, res1);
-  }
-  if (threadIdx.x < 256) {
-    if constexpr (EPT == 16)
-      stage_tw_pads_perm(s, K.T.blk_itw(pi), threadIdx.x);
-    else
-      stage_tw_pads(s, K.T.blk_itw(pi), threadIdx.x);
-  }
-  __syncthreads();
-  if constexpr (EPT == 16) {
-    if (grp < 2) blk_phase<4, true>(s + grp * kLds, 0, PadTwP{s}, q, q2, lt);
-    __syncthreads();
-    if (grp < 2) blk_phase<4, true>(s + grp * kLds, 4, PadTwP{s}, q, q2, lt);
-  } else {
+  __syncthreads();  // the inner product has read the tiles
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      if (p) __syncthreads();
-      if (grp < 2) blk_phase<2, true, PadTw, 4, GS>(s + grp * kLds, 2 * p, PadTw{s}, q, q2, lt);
+  for (int i = 0; i < QPT; ++i) {
+    const int e = 4 * (threadIdx.x + i * T);
+    if (e < 1024) {
+      blk_quad_store(s, e >> 8, e & 255, res0[i]);
+      blk_quad_store(s + TILE4, e >> 8, e & 255, res1[i]);
     }
   }
   __syncthreads();
-  if (grp < 2) {
-    uint32_t* dst = grp ? acc1 : acc0;
+  if (j < 2) {
+    tw.load(K.M.row_itw(K.T, pi, blockIdx.x * 4 + line), K.M.blk_itw(pi), lane);
+    blk_inv_a(slot, line, lane, tw, m);
+    wave_sync();
+    blk_inv_b(slot, line, lane, tw, m);
+    wave_sync();
+    uint32_t* dst = (j ? acc1 : acc0) + group;
 #pragma unroll
-    for (int kk = 0; kk < QPG; ++kk) {
-      const int ee = (lt + kk * GS) * 4;
-      st4(dst + ee, twist4(lds_blk4(s + grp * kLds, ee), K.T.blk_itwist(pi, blk0 + (ee >> 8)), ee & 255, q));
-    }
+    for (int kk = 0; kk < 4; ++kk) st4(dst + RowGroup<4>::word(lane, kk, a4), RowGroup<4>::from_lds(slot, lane, kk));
   }
 }
 
 // ============================================================================
-// Stage 3: ModDown of both components
+// Stage 3: ModDown of both components (after kc_conv<CONV_DOWN>)
 // ============================================================================
-
-// INTT column pass of the P rows (already through the block pass) -> x [2][k].
-template <int LOGN1, int CW, int T>
-__global__ __launch_bounds__(T) void k6_intt_cols_p(KsConst K, JobArg<KsJob> JA) {
-  const KsJob J = JA.get(blockIdx.z);
-  const size_t N = (size_t)1 << K.T.logN;
-  const KsView V = ks_view(J, K, N);
-  const int c = blockIdx.y / K.k, mm = blockIdx.y % K.k;
-  __shared__ __align__(16) uint32_t s[ColGeom<LOGN1, CW, T>::LDS];
-  constexpr int C = ColGeom<LOGN1, CW, T>::C;
-  const int pi = K.T.L_max + mm;
-  __shared__ uint2 stw[ColGeom<LOGN1, CW, T>::N1];
-  const uint2 tww = tw_fetch(K.T.col_itw(pi), ColGeom<LOGN1, CW, T>::N1);
-  const uint32_t q = ldc(K.T.mod + pi).q, q2 = 2 * q;
-  const uint2 sc = ldc(K.moddown_scale + mm);
-  const int col0 = blockIdx.x * C;
-  load_cols<LOGN1, CW, T>(s, V.acc + ((size_t)c * V.R + V.L + mm) * N, col0);
-  tw_put(stw, tww, ColGeom<LOGN1, CW, T>::N1);
-  __syncthreads();
-  col_stages<LOGN1, true, CW, T>(s, stw, q, q2);
-  __syncthreads();
-  uint32_t* row = V.x + ((size_t)c * K.k + mm) * N;
-#pragma unroll
-  for (int kk = 0; kk < ColGeom<LOGN1, CW, T>::QUADS; ++kk) {
-    const int lin = (threadIdx.x + kk * T) * 4;
-    const int pos = lin / C, cc = lin & (C - 1);
-    uint4 v = *reinterpret_cast<const uint4*>(s + lidx_col(pos, cc, C));
-    v.x = csub(mul_shoup(v.x, sc.x, sc.y, q), q);
-    v.y = csub(mul_shoup(v.y, sc.x, sc.y, q), q);
-    v.z = csub(mul_shoup(v.z, sc.x, sc.y, q), q);
-    v.w = csub(mul_shoup(v.w, sc.x, sc.y, q), q);
-    st4(row + pos * 256 + col0 + cc, v);
-  }
-}
-
-// w[c][i] = sum_m x[c][m] (P/p_m mod q_i) mod q_i; blockIdx.y = c * groups + g.
-template <int KP, int RB>
-__global__ __launch_bounds__(kWG) void k7_bconv_down(KsConst K, JobArg<KsJob> JA, int groups) {
-  const KsJob J = JA.get(blockIdx.z);
-  const size_t N = (size_t)1 << K.T.logN;
-  const KsView V = ks_view(J, K, N);
-  const int c = blockIdx.y / groups, g = blockIdx.y % groups;
-  if (g * RB >= V.L) return;
-  const size_t n = ((size_t)blockIdx.x * kWG + threadIdx.x) * 4;  // four coefficients per thread
-  uint4 x[KP];
-#pragma unroll
-  for (int mm = 0; mm < KP; ++mm) x[mm] = ld4(V.x + ((size_t)c * KP + mm) * N + n);
-  const int r1 = min(g * RB + RB, V.L);
-  for (int i = g * RB; i < r1; ++i) {
-    const ModC m = ldc(K.T.mod + i);
-    const uint32_t* t = K.moddown_T + (size_t)i * KP;
-    uint64_t a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-#pragma unroll
-    for (int mm = 0; mm < KP; ++mm) {
-      const uint64_t tm = ldc(t + mm);
-      a0 += x[mm].x * tm;
-      a1 += x[mm].y * tm;
-      a2 += x[mm].z * tm;
-      a3 += x[mm].w * tm;
-    }
-    st4(V.w + ((size_t)c * V.L + i) * N + n,
-        make_uint4(reduce64(a0, m.q, m.mu_hi, m.mu_lo), reduce64(a1, m.q, m.mu_hi, m.mu_lo),
-                   reduce64(a2, m.q, m.mu_hi, m.mu_lo), reduce64(a3, m.q, m.mu_hi, m.mu_lo)));
-  }
-}
-
-template <int LOGN1, int CW, int T>
-__global__ __launch_bounds__(T) void k8_ntt_cols_w(KsConst K, JobArg<KsJob> JA) {
-  const KsJob J = JA.get(blockIdx.z);
-  const size_t N = (size_t)1 << K.T.logN;
-  const KsView V = ks_view(J, K, N);
-  const int gr = blockIdx.y;
-  if (gr >= 2 * V.L) return;
-  const int i = gr % V.L;
-  __shared__ uint2 stw[ColGeom<LOGN1, CW, T>::N1];
-  const uint2 tww = tw_fetch(K.T.col_tw(i), ColGeom<LOGN1, CW, T>::N1);
-  __shared__ __align__(16) uint32_t s[ColGeom<LOGN1, CW, T>::LDS];
-  const uint32_t q = ldc(K.T.mod + i).q, q2 = 2 * q;
-  const int col0 = blockIdx.x * ColGeom<LOGN1, CW, T>::C;
-  uint32_t* row = V.w + (size_t)gr * N;
-  load_cols<LOGN1, CW, T>(s, row, col0);
-  tw_put(stw, tww, ColGeom<LOGN1, CW, T>::N1);
-  __syncthreads();
-  col_stages<LOGN1, false, CW, T>(s, stw, q, q2);
-  __syncthreads();
-  store_cols<LOGN1, CW, T>(s, row, col0);
-}
 
 // out[c][i] = (acc[c][i] - NTT(w)[c][i]) P^-1 (+ the job's epilogue term).
-// BPW blocks per work-group as in K1.
-template <int LOGN1, int BPW>
+// Bound: memory, near the copy rate (seven to ten rows in and out per row pair).
 __global__ __launch_bounds__(kWG) void k9_ntt_blks_combine(KsConst K, JobArg<KsJob> JA) {
   const KsJob J = JA.get(blockIdx.z);
   const int logN = K.T.logN;
@@ -1022,81 +845,69 @@ __global__ __launch_bounds__(kWG) void k9_ntt_blks_combine(KsConst K, JobArg<KsJ
   const int gr = blockIdx.y;
   if (gr >= 2 * V.L) return;
   const int c = gr / V.L, i = gr % V.L;
-  __shared__ uint2 stw[256];
-  const uint2 tww = tw_fetch(K.T.blk_tw(i), 256);
-  __shared__ __align__(16) uint32_t s[kLds];
-  const ModC m = ldc(K.T.mod + i);
-  const uint32_t q = m.q, q2 = 2 * q;
-  constexpr int QPT = BPW / 4;  // quads per thread
-  const int blk0 = blockIdx.x * BPW;
-  const uint32_t base = blk0 * 256;
+  __shared__ __align__(16) uint32_t s[kBlkTile];
+  const ModC mc = ldc(K.T.mod + i);
+  const MontQ m = mont_q(mc);
+  const uint32_t base = blockIdx.x * kTile;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  const uint32_t n0 = base + line * 256 + 4 * (lane & 15);  // the lane's quads: n0 + 64 kk
   const uint32_t* wrow = V.w + (size_t)gr * N + base;
+  BlkTw tw;
+  uint4 raw[4];
 #pragma unroll
-  for (int kk = 0; kk < QPT; ++kk) {
-    const int e = blk_elem(kk);
-    lds_blk4_store(s, e, twist4(ld4(wrow + e),
-                                K.T.blk_twist(i, blk0 + (e >> 8)), e & 255, q));
-  }
-  if constexpr (BPW == 16)
-    tw_put_perm(stw, tww);
-  else
-    tw_put(stw, tww, 256);
+  for (int kk = 0; kk < 4; ++kk) raw[kk] = ld4(wrow + RowGroup<16>::word(threadIdx.x, kk, 0));
+  tw.load(K.M.row_tw(K.T, i, blockIdx.x * 16 + line), K.M.blk_tw(i), lane);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) RowGroup<16>::to_lds(s, threadIdx.x, kk, raw[kk]);
   __syncthreads();
-  if constexpr (BPW == 16)
-    blk_stages<false>(s, PermTw{stw}, q, q2);
-  else
-    blk_stages_r4<false, const uint2*, kWG>(s, stw, q, q2);
-  __syncthreads();
-  const uint2 pv = ldc(K.pinv + i);
-  const uint32_t* accr = V.acc + ((size_t)c * V.R + i) * N + base;
-  uint32_t* out = J.out + ((size_t)c * V.L + i) * N + base;
+  blk_fwd_a(s, line, lane, tw, m);
+  wave_sync();
+  blk_fwd_b(s, line, lane, tw, m);
+  wave_sync();
+  const uint32_t pv = ldc(K.pinv + i).x, pvm = ldc(K.M.pinv + i);
+  const uint32_t* accr = V.acc + ((size_t)c * V.R + i) * N;
+  uint32_t* out = J.out + ((size_t)c * V.L + i) * N;
   const size_t L = V.L;
   const bool hmult = J.kind == KS_HMULT;
   const bool rot = (J.kind == KS_HROT || J.kind == KS_HOIST) && c == 0;
-  // Loads first (a store to out could alias a later load): the accumulator
-  // quads and the term this component adds — d0 = c0 c0' or d1 = c0 c1' + c1 c0'
-  // (HMULT, formed here from the inputs), sigma(c0) (rotations, c = 0), else 0.
-  // The term is formed as soon as its words arrive, so at most one quad's
-  // inputs are live at a time.
-  uint4 av[QPT], dv[QPT];
+  // w from [0, 4q) to [0, 2q): x = a + 2q - w < 3q < 2^32.  Loads first (a store
+  // to out could alias a later load): the accumulator quads and what this
+  // component adds -- d0 = c0 c0' or d1 = c0 c1' + c1 c0' (HMULT), sigma(c0)
+  // (rotations, c = 0), else nothing.  HMULT reduces x P^-1 and its products
+  // in one sum: at most 5 q^2 < 2^63.
+  uint4 res[4];
 #pragma unroll
-  for (int kk = 0; kk < QPT; ++kk) {
-    const int e = blk_elem(kk);
-    const uint32_t n = base + e;
-    av[kk] = ld4(accr + e);
-    dv[kk] = make_uint4(0, 0, 0, 0);
+  for (int kk = 0; kk < 4; ++kk) {
+    const uint32_t n = n0 + 64 * kk;
+    const uint4 a = ld4(accr + n);
+    const uint4 v = csub4(blk_quad(s, line, 4 * (lane & 15) + 64 * kk), m.q2);
+    const uint4 x = make_uint4(a.x + m.q2 - v.x, a.y + m.q2 - v.y, a.z + m.q2 - v.z, a.w + m.q2 - v.w);
     if (hmult) {
+      uint64_t t[4] = {(uint64_t)x.x * pv, (uint64_t)x.y * pv, (uint64_t)x.z * pv, (uint64_t)x.w * pv};
       const uint4 xa = ld4(J.a + i * N + n), ya = ld4(J.b + i * N + n);
       if (c == 0) {
-        dv[kk] = make_uint4(mulmod(xa.x, ya.x, m), mulmod(xa.y, ya.y, m), mulmod(xa.z, ya.z, m),
-                            mulmod(xa.w, ya.w, m));
+        mac4(t, xa, ya);
       } else {
-        const uint4 xb = ld4(J.a + (L + i) * N + n), yb = ld4(J.b + (L + i) * N + n);
-        dv[kk] = make_uint4(
-            reduce64((uint64_t)xa.x * yb.x + (uint64_t)xb.x * ya.x, q, m.mu_hi, m.mu_lo),
-            reduce64((uint64_t)xa.y * yb.y + (uint64_t)xb.y * ya.y, q, m.mu_hi, m.mu_lo),
-            reduce64((uint64_t)xa.z * yb.z + (uint64_t)xb.z * ya.z, q, m.mu_hi, m.mu_lo),
-            reduce64((uint64_t)xa.w * yb.w + (uint64_t)xb.w * ya.w, q, m.mu_hi, m.mu_lo));
+        mac4(t, xa, ld4(J.b + (L + i) * N + n));
+        mac4(t, ld4(J.a + (L + i) * N + n), ya);
       }
-    } else if (rot) {
-      const uint32_t* c0 = J.a + i * N;
-      dv[kk] = make_uint4(ld1(c0 + auto_src(n, J.gal, logN)), ld1(c0 + auto_src(n + 1, J.gal, logN)),
-                          ld1(c0 + auto_src(n + 2, J.gal, logN)), ld1(c0 + auto_src(n + 3, J.gal, logN)));
+      res[kk] = reduce4(t, mc);
+    } else {
+      uint4 d = make_uint4(0, 0, 0, 0);
+      if (rot) {
+        const uint32_t* c0 = J.a + i * N;
+        d = make_uint4(ld1(c0 + auto_src(n, J.gal, logN)), ld1(c0 + auto_src(n + 1, J.gal, logN)),
+                       ld1(c0 + auto_src(n + 2, J.gal, logN)), ld1(c0 + auto_src(n + 3, J.gal, logN)));
+      }
+      res[kk] = make_uint4(csub(csub(mont_mul(x.x, pvm, m), m.q) + d.x, m.q),
+                           csub(csub(mont_mul(x.y, pvm, m), m.q) + d.y, m.q),
+                           csub(csub(mont_mul(x.z, pvm, m), m.q) + d.z, m.q),
+                           csub(csub(mont_mul(x.w, pvm, m), m.q) + d.w, m.q));
     }
   }
 #pragma unroll
-  for (int kk = 0; kk < QPT; ++kk) {
-    const int e = blk_elem(kk);
-    // w from [0, 4q) to [0, 2q): a + 2q - w < 3q < 2^32 goes straight into
-    // the Shoup product
-    const uint4 w = csub4(lds_blk4(s, e), q2);
-    const uint4 a = av[kk], d = dv[kk];
-    const uint32_t o0 = csub(mul_shoup(a.x + q2 - w.x, pv.x, pv.y, q), q);
-    const uint32_t o1 = csub(mul_shoup(a.y + q2 - w.y, pv.x, pv.y, q), q);
-    const uint32_t o2 = csub(mul_shoup(a.z + q2 - w.z, pv.x, pv.y, q), q);
-    const uint32_t o3 = csub(mul_shoup(a.w + q2 - w.w, pv.x, pv.y, q), q);
-    st4(out + e, make_uint4(csub(o0 + d.x, q), csub(o1 + d.y, q), csub(o2 + d.z, q), csub(o3 + d.w, q)));
-  }
+  for (int kk = 0; kk < 4; ++kk) st4(out + n0 + 64 * kk, res[kk]);
 }
 
 // ============================================================================
@@ -1252,7 +1063,7 @@ __global__ __launch_bounds__(kWG) void r4_ntt_blks_combine(KsConst K, JobArg<RsJ
 
 // ============================================================================
 // Small rings (N = 2^kSrLog = 4096): a whole limb fits one work-group's LDS,
-// so the two-pass NTT split -- and with it the nine-kernel pipeline -- is not
+// so the two-pass NTT split -- and with it the five-kernel pipeline -- is not
 // needed.  A key-switch runs as two kernels of 1024-thread work-groups:
 //   S1  per (ModUp row t, group of digits): each non-digit limb of a digit
 //       transformed back whole in LDS, scaled, converted to row t (BConv),
@@ -1261,7 +1072,7 @@ __global__ __launch_bounds__(kWG) void r4_ntt_blks_combine(KsConst K, JobArg<RsJ
 //   S2  per (Q row i, component): the partials summed; ModDown -- the P rows'
 //       INTT whole in LDS, their conversion to q_i, its NTT -- combined with
 //       the accumulator, plus the job's epilogue term.
-// The arithmetic is that of the nine kernels (exact: the same residues).
+// The arithmetic is that of the five kernels (exact: the same residues).
 // Scratch of a job: the partials [groups][2][L + k][N] (at most kSrGroups = 4).
 // ============================================================================
 constexpr int kSrN = 1 << kSrLog;
@@ -1624,19 +1435,6 @@ size_t ks_hoist_ws_words(const Ctx& c, int L) {
 size_t rs_ws_words(const Ctx& c, int L) { return (2 + 2 * (size_t)L) * c.N; }
 
 namespace {
-// BConv output rows per work-group (Ctx::Sched): a group re-reads its
-// inputs once, so more rows per group mean fewer re-reads but fewer groups.
-template <template <int, int> class KERN, int A>
-void launch_bconv(const Ctx& c, int stage, int rows, dim3 g, hipStream_t st, const KsConst& K,
-                  const JobArg<KsJob>& J, int gr) {
-  switch (rows) {
-    case 2: klaunch(c, stage, KERN<A, 2>::fn, g, st, K, J, gr); break;
-    case 4: klaunch(c, stage, KERN<A, 4>::fn, g, st, K, J, gr); break;
-    case 6: klaunch(c, stage, KERN<A, 6>::fn, g, st, K, J, gr); break;
-    default: klaunch(c, stage, KERN<A, 12>::fn, g, st, K, J, gr); break;
-  }
-}
-
 // Launch of a pipeline kernel; when its stage is traced, the trace events
 // are attached to the dispatch itself.
 template <typename F, typename... A>
@@ -1650,44 +1448,6 @@ void klaunch(const Ctx& c, int stage, F kern, dim3 g, hipStream_t st, A... args)
   klaunch_b(c, stage, kern, g, kWG, st, args...);
 }
 
-// Dispatch a small compile-time count (digit size or special-prime count, 1..16).
-template <int A, int RB>
-struct K3fn {
-  static constexpr auto fn = k3_bconv_up<A, RB>;
-};
-template <int A, int RB>
-struct K7fn {
-  static constexpr auto fn = k7_bconv_down<A, RB>;
-};
-template <int A>
-struct K3 {
-  static void run(const Ctx& c, dim3 g, hipStream_t st, const KsConst& K, const JobArg<KsJob>& J,
-                  int gr, int rows) {
-    launch_bconv<K3fn, A>(c, CKKS_STAGE_BCONV_UP, rows, g, st, K, J, gr);
-  }
-};
-template <int A>
-struct K7 {
-  static void run(const Ctx& c, dim3 g, hipStream_t st, const KsConst& K, const JobArg<KsJob>& J,
-                  int gr, int rows) {
-    launch_bconv<K7fn, A>(c, CKKS_STAGE_BCONV_DOWN, rows, g, st, K, J, gr);
-  }
-};
-
-template <template <int> class F, int V>
-hipError_t small_dispatch(int v, const Ctx& c, dim3 g, hipStream_t st, const KsConst& K,
-                          const JobArg<KsJob>& J, int gr, int rows) {
-  if constexpr (V > kMaxAlpha) {
-    return hipErrorInvalidValue;
-  } else {
-    if (v == V) {
-      F<V>::run(c, g, st, K, J, gr, rows);
-      return hipSuccess;
-    }
-    return small_dispatch<F, V + 1>(v, c, g, st, K, J, gr, rows);
-  }
-}
-
 // Column passes with fewer work-groups than this (half a work-group per CU)
 // use the narrowest column tiles, which double the work-groups at N = 2^16:
 // for such a grid every CU that joins shortens the pass (the rescale's INTT
@@ -1699,14 +1459,6 @@ constexpr int kNarrowBelow = 128;
 template <int L1>
 constexpr int kColThreads = ColGeom<L1>::ELEMS / 16;
 
-template <int L1, int CW, int T>
-struct K2c { static constexpr auto fn = k2_intt_cols<L1, CW, T>; };
-template <int L1, int CW, int T>
-struct K4c { static constexpr auto fn = k4_ntt_cols<L1, CW, T>; };
-template <int L1, int CW, int T>
-struct K6c { static constexpr auto fn = k6_intt_cols_p<L1, CW, T>; };
-template <int L1, int CW, int T>
-struct K8c { static constexpr auto fn = k8_ntt_cols_w<L1, CW, T>; };
 template <int L1, int CW, int T>
 struct R2c { static constexpr auto fn = r2_intt_cols<L1, CW, T>; };
 template <int L1, int CW, int T>
@@ -1753,29 +1505,42 @@ inline bool col_radix8(bool sparse, int shape) {
   return sparse ? !(shape & kShapeInvRadix16) : (shape & kShapeFwdRadix8) != 0;
 }
 
-// Stage 1 (ModUp): K1-K4.
+// Groups of output rows of a column-conversion launch whose work-groups number
+// `base` at one group each (column tiles x digits or components x jobs), with
+// at most `rows` output rows: enough to have a work-group per CU (a group more
+// repeats the input transforms, a third of the work at 12 inputs and 36 rows,
+// and a second work-group on a CU only shares its vector units), none with
+// less than a pair of rows, and at most 8 `cap` rows in a group, `cap` being
+// the schedule's BConv rows.
+int conv_groups(long base, int rows, int cap) {
+  constexpr long kFill = 256;
+  const long fill = std::min<long>((kFill + base - 1) / base, (rows + 1) / 2);
+  const long need = (rows + 8 * cap - 1) / (8 * cap);
+  return (int)std::max({1l, fill, need});
+}
+
+template <int L1, int MODE>
+hipError_t conv_launch(const Ctx& c, int stage, int nin, dim3 g, hipStream_t st, const KsConst& K,
+                       const JobArg<KsJob>& jobs, int groups) {
+  auto go = [&](auto kern) { klaunch_b(c, stage, kern, g, 64 * kConvWaves, st, K, jobs, groups); };
+  if (nin <= 4)
+    go(kc_conv<L1, MODE, 4>);
+  else if (nin <= 12)
+    go(kc_conv<L1, MODE, 12>);
+  else
+    go(kc_conv<L1, MODE, 16>);
+  return hipGetLastError();
+}
+
+// Stage 1 (ModUp): the block pass and the column kernel.
 template <int L1>
 hipError_t modup_stage_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, const JobArg<KsJob>& jobs,
                          int njobs, int Lmax, hipStream_t st) {
-  const int Rmax = Lmax + c.k;
-  const int tiles = c.N / kTile;
-  const int cols = c.N / (4 * kWG);  // BConv: four coefficients per thread
-  const int bmax = c.beta(Lmax);
-  const int up_rows = sc.up_rows == 2 || sc.up_rows == 4 || sc.up_rows == 6 ? sc.up_rows : 12;
-  const int up_groups = (Rmax + up_rows - 1) / up_rows;
-  if (4 * tiles * Lmax * njobs <= 256)  // quarter tiles still one work-group per CU
-    klaunch(c, CKKS_STAGE_INTT_BLOCKS, k1_intt_blks<L1, 4>, dim3(4 * tiles, Lmax, njobs), st, K, jobs);
-  else if (sc.ntt_shape & kShapeK1Radix16)
-    klaunch(c, CKKS_STAGE_INTT_BLOCKS, k1_intt_blks<L1, 16, 16>, dim3(tiles, Lmax, njobs), st, K, jobs);
-  else
-    klaunch_b(c, CKKS_STAGE_INTT_BLOCKS, k1_intt_blks<L1, 16, 8>, dim3(tiles, Lmax, njobs), 512, st, K, jobs);
-  col_launch<K2c, L1>(c, CKKS_STAGE_INTT_COLS, Lmax, njobs, true, st, K, jobs, col_radix8(true, sc.ntt_shape));
-  const hipError_t e =
-      small_dispatch<K3, 1>(c.alpha, c, dim3(cols, bmax * up_groups, njobs), st, K, jobs, up_groups, up_rows);
-  if (e != hipSuccess) return e;
-  col_launch<K4c, L1>(c, CKKS_STAGE_NTT_COLS_UP, bmax * Rmax, njobs, false, st, K, jobs,
-                      col_radix8(false, sc.ntt_shape));
-  return hipSuccess;
+  const int beta = c.beta(Lmax), tiles = c.N / 512;
+  klaunch(c, CKKS_STAGE_INTT_BLOCKS, k1_intt_blks, dim3(c.N / kTile, Lmax, njobs), st, K, jobs);
+  const int groups = conv_groups((long)tiles * beta * njobs, Lmax + c.k - 1, sc.up_rows);
+  return conv_launch<L1, CONV_UP>(c, CKKS_STAGE_INTT_COLS, c.alpha, dim3(tiles, beta * groups, njobs), st, K, jobs,
+                                  groups);
 }
 
 template <int L1>
@@ -1783,7 +1548,7 @@ hipError_t ks_modup_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& 
                              int njobs, int Lmax, hipStream_t st) {
   const hipError_t e = modup_stage_t<L1>(c, sc, K, jobs, njobs, Lmax, st);
   if (e != hipSuccess) return e;
-  klaunch(c, -1, km_ntt_blks<L1>, dim3(c.N / kTile, c.beta(Lmax) * (Lmax + c.k), njobs), st, K, jobs);
+  klaunch(c, -1, km_ntt_blks, dim3(c.N / kTile, c.beta(Lmax) * (Lmax + c.k), njobs), st, K, jobs);
   return hipGetLastError();
 }
 
@@ -1793,9 +1558,6 @@ hipError_t ks_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, con
                        const KsSplit& sp) {
   const int Rmax = Lmax + c.k;
   const int tiles = c.N / kTile;
-  const int cols = c.N / (4 * kWG);  // BConv: four coefficients per thread
-  const int down_rows = sc.down_rows == 2 || sc.down_rows == 4 || sc.down_rows == 6 ? sc.down_rows : 12;
-  const int down_groups = (Lmax + down_rows - 1) / down_rows;
   hipError_t e;
   if constexpr (L1 + kBlockLog == kSrLog) {
     // small ring: two kernels on whole limbs (plain, HMult and HRot jobs)
@@ -1817,33 +1579,11 @@ hipError_t ks_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, con
     const dim3 g5(tiles, rows, njobs);
     const int nb = std::max(c.beta(Lmax), 2);  // slots for the launch's own largest digit count
     if (tiles * rows * njobs <= sc.small_grid && nb <= 4) {  // too few work-groups to fill the CUs
-      // eighth tiles (radix-4 phases) while eight times the work-groups still
-      // fit one per CU, else quarter tiles while four times do
-      if (8 * tiles * rows * njobs <= 256) {
-        const dim3 g8(8 * tiles, rows, njobs);
-        constexpr int T8 = k5p_threads<2, 4>();
-        switch (nb) {
-          case 2: klaunch_b(c, stage, k5p_ntt_blks_ip<L1, 2, 2, 4>, g8, T8, s5, K, jobs, part); break;
-          case 3: klaunch_b(c, stage, k5p_ntt_blks_ip<L1, 3, 2, 4>, g8, T8, s5, K, jobs, part); break;
-          default: klaunch_b(c, stage, k5p_ntt_blks_ip<L1, 4, 2, 4>, g8, T8, s5, K, jobs, part); break;
-        }
-        return;
-      }
-      if (4 * tiles * rows * njobs <= 256) {
-        const dim3 g4(4 * tiles, rows, njobs);
-        constexpr int T4 = k5p_threads<4, 16>();
-        switch (nb) {
-          case 2: klaunch_b(c, stage, k5p_ntt_blks_ip<L1, 2, 4, 16>, g4, T4, s5, K, jobs, part); break;
-          case 3: klaunch_b(c, stage, k5p_ntt_blks_ip<L1, 3, 4, 16>, g4, T4, s5, K, jobs, part); break;
-          default: klaunch_b(c, stage, k5p_ntt_blks_ip<L1, 4, 4, 16>, g4, T4, s5, K, jobs, part); break;
-        }
-        return;
-      }
-      constexpr int T16 = k5p_threads<16, 16>();
+      const dim3 g4(4 * tiles, rows, njobs);
       switch (nb) {
-        case 2: klaunch_b(c, stage, k5p_ntt_blks_ip<L1, 2, 16, 16>, g5, T16, s5, K, jobs, part); break;
-        case 3: klaunch_b(c, stage, k5p_ntt_blks_ip<L1, 3, 16, 16>, g5, T16, s5, K, jobs, part); break;
-        default: klaunch_b(c, stage, k5p_ntt_blks_ip<L1, 4, 16, 16>, g5, T16, s5, K, jobs, part); break;
+        case 2: klaunch_b(c, stage, k5p_ntt_blks_ip<2>, g4, 128, s5, K, jobs, part); break;
+        case 3: klaunch_b(c, stage, k5p_ntt_blks_ip<3>, g4, 192, s5, K, jobs, part); break;
+        default: klaunch_b(c, stage, k5p_ntt_blks_ip<4>, g4, 256, s5, K, jobs, part); break;
       }
       return;
     }
@@ -1852,27 +1592,27 @@ hipError_t ks_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, con
     const bool nt = njobs == 1;
     switch (nb) {
       case 2:
-        if (nt) klaunch(c, stage, k5s_ntt_blks_ip<L1, 2, true>, g5, s5, K, jobs, part);
-        else klaunch(c, stage, k5s_ntt_blks_ip<L1, 2, false>, g5, s5, K, jobs, part);
+        if (nt) klaunch(c, stage, k5s_ntt_blks_ip<2, true>, g5, s5, K, jobs, part);
+        else klaunch(c, stage, k5s_ntt_blks_ip<2, false>, g5, s5, K, jobs, part);
         break;
       case 3:
-        if (nt) klaunch(c, stage, k5s_ntt_blks_ip<L1, 3, true>, g5, s5, K, jobs, part);
-        else klaunch(c, stage, k5s_ntt_blks_ip<L1, 3, false>, g5, s5, K, jobs, part);
+        if (nt) klaunch(c, stage, k5s_ntt_blks_ip<3, true>, g5, s5, K, jobs, part);
+        else klaunch(c, stage, k5s_ntt_blks_ip<3, false>, g5, s5, K, jobs, part);
         break;
       case 4:
-        if (nt) klaunch(c, stage, k5s_ntt_blks_ip<L1, 4, true>, g5, s5, K, jobs, part);
-        else klaunch(c, stage, k5s_ntt_blks_ip<L1, 4, false>, g5, s5, K, jobs, part);
+        if (nt) klaunch(c, stage, k5s_ntt_blks_ip<4, true>, g5, s5, K, jobs, part);
+        else klaunch(c, stage, k5s_ntt_blks_ip<4, false>, g5, s5, K, jobs, part);
         break;
-      default: klaunch(c, stage, k5_ntt_blks_ip<L1, false>, g5, s5, K, jobs, part); break;
+      default: klaunch(c, stage, k5_ntt_blks_ip<false>, g5, s5, K, jobs, part); break;
     }
   };
   auto k5h = [&](int stage, int part, hipStream_t s5, int rows) {
     const dim3 gh(tiles, rows, njobs);
     switch (std::max(c.beta(Lmax), 2)) {  // slots for the launch's own largest digit count
-      case 2: klaunch(c, stage, k5h_gather_ip<L1, 2>, gh, s5, K, jobs, part); break;
-      case 3: klaunch(c, stage, k5h_gather_ip<L1, 3>, gh, s5, K, jobs, part); break;
-      case 4: klaunch(c, stage, k5h_gather_ip<L1, 4>, gh, s5, K, jobs, part); break;
-      default: klaunch(c, stage, k5_ntt_blks_ip<L1, true>, gh, s5, K, jobs, part); break;
+      case 2: klaunch(c, stage, k5h_gather_ip<2>, gh, s5, K, jobs, part); break;
+      case 3: klaunch(c, stage, k5h_gather_ip<3>, gh, s5, K, jobs, part); break;
+      case 4: klaunch(c, stage, k5h_gather_ip<4>, gh, s5, K, jobs, part); break;
+      default: klaunch(c, stage, k5_ntt_blks_ip<true>, gh, s5, K, jobs, part); break;
     }
   };
   const bool split = sp.side != nullptr;
@@ -1900,18 +1640,12 @@ hipError_t ks_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, con
     if (with_hoist) k5h(CKKS_STAGE_NTT_IP, KS_PART_ALL, st, Rmax);
   }
   if (split && (e = hipEventRecord(sp.join, sp.side)) != hipSuccess) return e;
-  col_launch<K6c, L1>(c, CKKS_STAGE_INTT_COLS_P, 2 * c.k, njobs, true, st, K, jobs, col_radix8(true, sc.ntt_shape));
-  e = small_dispatch<K7, 1>(c.k, c, dim3(cols, 2 * down_groups, njobs), st, K, jobs, down_groups,
-                            down_rows);
+  const int groups = conv_groups((long)(c.N / 512) * 2 * njobs, Lmax, sc.down_rows);
+  e = conv_launch<L1, CONV_DOWN>(c, CKKS_STAGE_INTT_COLS_P, c.k, dim3(c.N / 512, 2 * groups, njobs), st, K, jobs,
+                                 groups);
   if (e != hipSuccess) return e;
-  col_launch<K8c, L1>(c, CKKS_STAGE_NTT_COLS_DOWN, 2 * Lmax, njobs, false, st, K, jobs,
-                      col_radix8(false, sc.ntt_shape));
   if (split && (e = hipStreamWaitEvent(st, sp.join, 0)) != hipSuccess) return e;
-  if (4 * tiles * 2 * Lmax * njobs <= 256)
-    klaunch(c, CKKS_STAGE_NTT_COMBINE, k9_ntt_blks_combine<L1, 4>, dim3(4 * tiles, 2 * Lmax, njobs), st, K,
-            jobs);
-  else
-    klaunch(c, CKKS_STAGE_NTT_COMBINE, k9_ntt_blks_combine<L1, 16>, dim3(tiles, 2 * Lmax, njobs), st, K, jobs);
+  klaunch(c, CKKS_STAGE_NTT_COMBINE, k9_ntt_blks_combine, dim3(tiles, 2 * Lmax, njobs), st, K, jobs);
   return hipGetLastError();
 }
 

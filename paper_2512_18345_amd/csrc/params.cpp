@@ -53,6 +53,7 @@ bool is_prime(u64 n) {
 
 uint32_t brv(uint32_t x, int bits) { return __builtin_bitreverse32(x) >> (32 - bits); }
 
+uint32_t mont(u64 w, u64 q) { return (uint32_t)((w << 32) % q); }
 uint2 shoup(u64 w, u64 q) { return make_uint2((uint32_t)w, (uint32_t)((w << 32) / q)); }
 
 // Smallest primitive 2N-th root of unity mod q: take any element of order
@@ -110,48 +111,65 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
   std::vector<uint2> tw((size_t)nP * N1), itw((size_t)nP * N1);
   std::vector<uint2> ctw((size_t)nP * 256), ictw((size_t)nP * 256);
   std::vector<uint2> twist((size_t)nP * N1 * 32), itwist((size_t)nP * N1 * 32);
+  std::vector<uint32_t> mrow((size_t)nP * N1 * 32, 0), mirow((size_t)nP * N1 * 32, 0);
   // whole-limb tables of small rings: all N entries of the bit-reversed table
   const bool small_ring = c.logN == kSrLog;
   std::vector<uint2> ftw(small_ring ? (size_t)nP * N : 0), fitw(small_ring ? (size_t)nP * N : 0);
   for (int i = 0; i < nP; ++i) {
     const u64 qi = c.primes[i];
-    const u64 psi = min_root(qi, N), psii = invm(psi, qi);
+    const u64 psi = min_root(qi, N);
+    std::vector<uint32_t> pw(2 * N);  // psi^e for every exponent a table needs
+    pw[0] = 1;
+    for (u64 e = 1; e < 2 * N; ++e) pw[e] = (uint32_t)(pw[e - 1] * psi % qi);
+    auto P = [&](u64 e) -> u64 { return pw[e & (2 * N - 1)]; };
+    auto PI = [&](u64 e) -> u64 { return pw[(0 - e) & (2 * N - 1)]; };
     const u64 mu64 = ~0ull / qi;
     const u64 ninv = invm(N % qi, qi);
     const uint2 ns = shoup(ninv, qi);
+    uint32_t qinv = (uint32_t)qi;  // q^-1 mod 2^32: q is right to 3 bits, each step doubles them
+    for (int t = 0; t < 4; ++t) qinv *= 2u - (uint32_t)qi * qinv;
     mod[i] = ModC{(uint32_t)qi, (uint32_t)((1ull << 32) / qi), (uint32_t)(mu64 >> 32),
-                  (uint32_t)mu64, ns.x, ns.y};
+                  (uint32_t)mu64, ns.x, ns.y, 0u - qinv, 0};
     // column pass: the first N1 entries of the bit-reversed table
     for (u64 e = 0; e < N1; ++e) {
       const uint32_t b = brv((uint32_t)e, c.logN);
-      tw[(size_t)i * N1 + e] = shoup(powm(psi, b, qi), qi);
-      itw[(size_t)i * N1 + e] = shoup(powm(psii, b, qi), qi);
+      tw[(size_t)i * N1 + e] = shoup(P(b), qi);
+      itw[(size_t)i * N1 + e] = shoup(PI(b), qi);
     }
     if (small_ring)
       for (u64 e = 0; e < N; ++e) {
         const uint32_t b = brv((uint32_t)e, c.logN);
-        ftw[(size_t)i * N + e] = shoup(powm(psi, b, qi), qi);
-        fitw[(size_t)i * N + e] = shoup(powm(psii, b, qi), qi);
+        ftw[(size_t)i * N + e] = shoup(P(b), qi);
+        fitw[(size_t)i * N + e] = shoup(PI(b), qi);
       }
     // block pass (twisted): index 2^s + g -> psi^((N / 2^s) brv_s(g))
     ctw[(size_t)i * 256] = ictw[(size_t)i * 256] = shoup(1, qi);
     for (int s = 0; s < 8; ++s)
       for (u64 g = 0; g < (1ull << s); ++g) {
         const u64 ex = (N >> s) * (s ? brv((uint32_t)g, s) : 0);
-        ctw[(size_t)i * 256 + (1u << s) + g] = shoup(powm(psi, ex, qi), qi);
-        ictw[(size_t)i * 256 + (1u << s) + g] = shoup(powm(psii, ex, qi), qi);
+        ctw[(size_t)i * 256 + (1u << s) + g] = shoup(P(ex), qi);
+        ictw[(size_t)i * 256 + (1u << s) + g] = shoup(PI(ex), qi);
       }
     // twist of block b: rho_b = psi^(2 brv(b) + 1)
     for (u64 b = 0; b < N1; ++b) {
-      const u64 rho = powm(psi, 2 * (u64)brv((uint32_t)b, logN1) + 1, qi);
-      const u64 rhoi = invm(rho, qi);
+      const u64 rho = 2 * (u64)brv((uint32_t)b, logN1) + 1;  // rho_b = psi^rho
       uint2* t = &twist[((size_t)i * N1 + b) * 32];
       uint2* ti = &itwist[((size_t)i * N1 + b) * 32];
+      uint32_t* mr = &mrow[((size_t)i * N1 + b) * 32];
+      uint32_t* mri = &mirow[((size_t)i * N1 + b) * 32];
+      for (int s = 0; s < 4; ++s)
+        for (u64 g = 0; g < (1ull << s); ++g) {
+          const uint32_t ex = brv((uint32_t)(((N1 + b) << s) + g), c.logN);
+          mr[(1u << s) + g] = mont(P(ex), qi);
+          mri[(1u << s) + g] = mont(PI(ex), qi);
+        }
       for (u64 j = 0; j < 16; ++j) {
-        t[j] = shoup(powm(rho, j, qi), qi);
-        ti[j] = shoup(powm(rhoi, j, qi), qi);
-        t[16 + j] = shoup(powm(rho, 16 * j, qi), qi);
-        ti[16 + j] = shoup(powm(rhoi, 16 * j, qi), qi);
+        mr[16 + j] = mont(P(rho * j), qi);
+        mri[16 + j] = mont(PI(rho * j), qi);
+        t[j] = shoup(P(rho * j), qi);
+        ti[j] = shoup(PI(rho * j), qi);
+        t[16 + j] = shoup(P(rho * 16 * j), qi);
+        ti[16 + j] = shoup(PI(rho * 16 * j), qi);
       }
     }
   }
@@ -235,7 +253,48 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
       rinv[(size_t)L * c.L_max + i] = shoup(invm(c.primes[L - 1] % qi, qi), qi);
     }
 
+  // Montgomery tables: the words of the Shoup tables times 2^32, the rows'
+  // own tables and the base-conversion constants, in one allocation
+  std::vector<uint32_t> all;
+  std::vector<size_t> at;  // offset of each table, 64-word aligned
+  auto begin = [&]() {
+    all.resize((all.size() + 63) / 64 * 64, 0);
+    at.push_back(all.size());
+  };
+  auto per_prime = [&](const std::vector<uint2>& t, size_t n) {  // [nP][n]
+    begin();
+    for (size_t e = 0; e < t.size(); ++e) all.push_back(mont(t[e].x, c.primes[e / n]));
+  };
+  per_prime(tw, N1);
+  per_prime(itw, N1);
+  per_prime(ctw, 256);
+  per_prime(ictw, 256);
+  for (const std::vector<uint32_t>* t : {&mrow, &mirow}) {
+    begin();
+    all.insert(all.end(), t->begin(), t->end());
+  }
+  begin();  // ModUp pre-multipliers [L_max + 1][L_max]
+  for (size_t e = 0; e < mscale.size(); ++e) all.push_back(mont(mscale[e].x, c.primes[e % c.L_max]));
+  begin();  // ModUp tables: [r][alpha] for each level and digit, in order
+  {
+    size_t e = 0;
+    for (int L = 1; L <= c.L_max; ++L)
+      for (int j = 0; j < c.beta(L); ++j)
+        for (int r = 0; r < L + c.k; ++r)
+          for (int ii = 0; ii < c.alpha; ++ii) all.push_back(mont(mT[e++], c.primes[c.rows(L).pidx(r)]));
+  }
+  begin();
+  for (int m = 0; m < c.k; ++m) all.push_back(mont(dscale[m].x, c.primes[c.L_max + m]));
+  begin();
+  for (size_t e = 0; e < dT.size(); ++e) all.push_back(mont(dT[e], c.primes[e / c.k]));
+  begin();
+  for (int i = 0; i < c.L_max; ++i) all.push_back(mont(pinv[i].x, c.primes[i]));
+
   std::string err;
+  if (!(err = upload(&c.d_mont, all, code)).empty()) return err;
+  const uint32_t* d = c.d_mont;
+  c.mont = MontTab{d + at[0], d + at[1], d + at[2], d + at[3], d + at[4],  d + at[5],
+                   d + at[6], d + at[7], d + at[8], d + at[9], d + at[10]};
   if (!(err = upload(&c.d_mod, mod, code)).empty()) return err;
   if (!(err = upload(&c.d_tw, tw, code)).empty()) return err;
   if (!(err = upload(&c.d_itw, itw, code)).empty()) return err;
@@ -261,7 +320,7 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
 
 void free_tables(Ctx& c) {
   void* ptrs[] = {c.d_mod, c.d_tw, c.d_itw, c.d_ctw, c.d_ictw, c.d_twist, c.d_itwist, c.d_ftw, c.d_fitw,
-                  c.d_modup_scale, c.d_modup_T, c.d_modup_T_off,
+                  c.d_mont, c.d_modup_scale, c.d_modup_T, c.d_modup_T_off,
                   c.d_moddown_scale, c.d_moddown_T, c.d_pinv, c.d_rescale_inv};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);

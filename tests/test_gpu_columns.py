@@ -1,0 +1,43 @@
+"""GPU parity of the fused column kernels (INTT columns, base conversion, NTT
+columns of ModUp and ModDown) at the sizes where their split can go wrong:
+digit sizes on both sides of a step of four limbs, of an even count and of the
+12 past which the sum takes one more correction; one limb, a full digit, one
+limb past it and every limb; every ring degree's tile width.
+
+Bit-exact against the oracle on every residue (tolerance 0)."""
+import pytest
+import torch
+
+import ckks_inputs as ci
+import oracle as O
+import paper_2512_18345_amd as P
+from gpu_helpers import dev, empty, first_mismatch, host
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+@pytest.mark.parametrize("logN,alpha", [(12, 1), (12, 3), (12, 16), (13, 2), (13, 5), (13, 13),
+                                        (14, 4), (14, 12), (15, 9), (16, 1), (16, 7)])
+def test_column_kernels_at_every_digit_size(logN, alpha):
+    spec = ci.chain_spec(f"a{alpha}", logN, 2 * alpha, alpha, 2, 100 + alpha)
+    par, ctx, rng = O.Params.from_spec(spec), P.Context.from_spec(spec), ci.Rng(spec.seed)
+    h, N = ctx.handle, spec.N
+    P.ckks_ctx_set_schedule(h)  # the pipeline at N = 2^12 too, not the whole-limb kernels
+    key = rng.evk(spec)
+    d_key = dev(key)
+    for L in sorted({1, alpha, alpha + 1, 2 * alpha}):
+        ct1, ct2 = rng.polys(2, spec.q[:L], N), rng.polys(2, spec.q[:L], N)
+        rot = rng.rotation(N)
+        out = empty(2, L, N)
+        P.ckks_hmult(h, dev(ct1), dev(ct2), L, d_key, out, ctx.workspace("HMULT", L))
+        msg = first_mismatch(host(out), O.hmult(par, ct1, ct2, L, key))
+        assert not msg, f"hmult N=2^{logN} digit {alpha} L={L}: {msg}"
+        P.ckks_hrot(h, dev(ct1), L, rot, d_key, out, ctx.workspace("HROT", L))
+        msg = first_mismatch(host(out), O.hrot(par, ct1, L, rot, key))
+        assert not msg, f"hrot N=2^{logN} digit {alpha} L={L}: {msg}"
+        outs = [empty(2, L, N) for _ in range(2)]
+        P.ckks_hrot_hoisted(h, dev(ct1), L, [rot, 1], [d_key, d_key], outs, ctx.workspace("HROT_HOISTED", L))
+        for o, w in zip(outs, O.hrot_hoisted(par, ct1, L, [rot, 1], [key, key])):
+            msg = first_mismatch(host(o), w)
+            assert not msg, f"hoisted N=2^{logN} digit {alpha} L={L}: {msg}"
