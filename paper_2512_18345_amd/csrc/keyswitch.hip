@@ -92,6 +92,24 @@ __device__ __forceinline__ uint32_t auto_src(uint32_t j, uint32_t g, int logN) {
   return __builtin_bitreverse32((e - 1u) >> 1) >> (32 - logN);
 }
 
+// sigma on an aligned quad.  auto_src takes an aligned group of 2^m indexes to
+// an aligned group (g is odd: the low bits of the index are the high bits of
+// brv), and g = 5^r is 1 mod 4, so four words are four words of one source
+// quad, rotated in bit-reversed order (x, z, y, w): one 16-byte load and eight
+// selects instead of four index chains and four 4-byte loads.
+struct AutoQuad {
+  uint32_t src;  // first word of the source quad
+  bool r1, r2;   // rotate by one, by two
+};
+__device__ __forceinline__ AutoQuad auto_quad(uint32_t n, uint32_t g, int logN) {
+  const uint32_t s = auto_src(n, g, logN);
+  return AutoQuad{s & ~3u, (s & 2) != 0, (s & 1) != 0};
+}
+__device__ __forceinline__ uint4 auto_turn(uint4 v, const AutoQuad& a) {
+  const uint4 u = a.r1 ? make_uint4(v.z, v.w, v.y, v.x) : v;
+  return a.r2 ? make_uint4(u.y, u.x, u.w, u.z) : u;
+}
+
 __device__ __forceinline__ uint32_t mulmod(uint32_t a, uint32_t b, const ModC& m) {
   return reduce64((uint64_t)a * b, m.q, m.mu_hi, m.mu_lo);
 }
@@ -121,12 +139,15 @@ __device__ __forceinline__ void load_d16(const KsJob& J, int r, uint32_t n0, siz
     return;
   }
   const uint32_t* src = J.a + row1;
+  AutoQuad aq[4];
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     const uint32_t n = n0 + 64 * kk;
-    d[kk] = make_uint4(ld1(src + auto_src(n, J.gal, logN)), ld1(src + auto_src(n + 1, J.gal, logN)),
-                       ld1(src + auto_src(n + 2, J.gal, logN)), ld1(src + auto_src(n + 3, J.gal, logN)));
+    aq[kk] = auto_quad(n, J.gal, logN);
+    d[kk] = ld4(src + aq[kk].src);
   }
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) d[kk] = auto_turn(d[kk], aq[kk]);
 }
 
 // ============================================================================
@@ -428,8 +449,8 @@ __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> J
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         const uint32_t n = n0 + 64 * kk;
-        v[kk] = make_uint4(ld1(Mrow + auto_src(n, J.gal, logN)), ld1(Mrow + auto_src(n + 1, J.gal, logN)),
-                           ld1(Mrow + auto_src(n + 2, J.gal, logN)), ld1(Mrow + auto_src(n + 3, J.gal, logN)));
+        const AutoQuad aq = auto_quad(n, J.gal, logN);
+        v[kk] = auto_turn(ld4(Mrow + aq.src), aq);
       }
     } else if (r >= lo && r < hi) {
       // digit rows are the switched polynomial itself (kept by K1 unless it is the input)
@@ -621,7 +642,8 @@ __global__ __launch_bounds__(kWG) void k5s_ntt_blks_ip(KsConst K, JobArg<KsJob> 
 // 4096-word tile of an evaluation-domain row onto one aligned source tile (g
 // is odd, so only the low 12 bits of the bit-reversed index are permuted), so
 // every digit's source tile of M is loaded whole and contiguously into its
-// own LDS slot and the permutation is a read from LDS.  The key words of the
+// own LDS slot and the permutation is a read from LDS, a rotated quad at a
+// time (auto_quad).  The key words of the
 // first KPF quads are requested with the tiles; the inner product and the
 // P-row INTT block pass follow as in k5s, on canonical words (M is fully
 // transformed).
@@ -678,15 +700,17 @@ __global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     const uint32_t n = n0 + 64 * kk;
-    const uint32_t p0 = auto_src(n, J.gal, logN) & (kTile - 1), p1 = auto_src(n + 1, J.gal, logN) & (kTile - 1),
-                   p2 = auto_src(n + 2, J.gal, logN) & (kTile - 1), p3 = auto_src(n + 3, J.gal, logN) & (kTile - 1);
+    const AutoQuad aq = auto_quad(n, J.gal, logN);
     if (kk >= KPF) key_quad(kk);
     uint64_t a0[4] = {0, 0, 0, 0}, a1[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const uint32_t msk = j < V.beta ? ~0u : 0u;
-      const uint32_t* sl = s + j * kTile;
-      const uint4 v = make_uint4(sl[p0] & msk, sl[p1] & msk, sl[p2] & msk, sl[p3] & msk);
+      uint4 v = auto_turn(*reinterpret_cast<const uint4*>(s + j * kTile + (aq.src & (kTile - 1))), aq);
+      v.x &= msk;
+      v.y &= msk;
+      v.z &= msk;
+      v.w &= msk;
       mac4(a0, v, kpre0[kk][j]);
       mac4(a1, v, kpre1[kk][j]);
     }
@@ -897,8 +921,8 @@ __global__ __launch_bounds__(kWG) void k9_ntt_blks_combine(KsConst K, JobArg<KsJ
       uint4 d = make_uint4(0, 0, 0, 0);
       if (rot) {
         const uint32_t* c0 = J.a + i * N;
-        d = make_uint4(ld1(c0 + auto_src(n, J.gal, logN)), ld1(c0 + auto_src(n + 1, J.gal, logN)),
-                       ld1(c0 + auto_src(n + 2, J.gal, logN)), ld1(c0 + auto_src(n + 3, J.gal, logN)));
+        const AutoQuad aq = auto_quad(n, J.gal, logN);
+        d = auto_turn(ld4(c0 + aq.src), aq);
       }
       res[kk] = make_uint4(csub(csub(mont_mul(x.x, pvm, m), m.q) + d.x, m.q),
                            csub(csub(mont_mul(x.y, pvm, m), m.q) + d.y, m.q),
@@ -1142,6 +1166,7 @@ __device__ __forceinline__ void sr_intt(uint32_t* s, const uint2* itw, uint32_t 
 // taken by sr_switched_finish where the quad is used.
 struct SrRaw {
   uint4 x, y;
+  AutoQuad aq;
 };
 // Branch-free (the kind selects addresses, every load is issued): a load in
 // a branch whose value merges after it makes the compiler wait for it there.
@@ -1154,15 +1179,13 @@ __device__ __forceinline__ SrRaw sr_switched_load(const KsJob& J, int r) {
   const uint32_t* src = J.a + (size_t)(J.kind == KS_PLAIN ? r : J.L + r) * N;
   const uint32_t* src2 = J.kind == KS_HMULT ? J.b + (size_t)(J.L + r) * N : src;
   SrRaw o;
-  o.x = make_uint4(ld1(src + (rot ? auto_src(n, J.gal, kSrLog) : n)),
-                   ld1(src + (rot ? auto_src(n + 1, J.gal, kSrLog) : n + 1)),
-                   ld1(src + (rot ? auto_src(n + 2, J.gal, kSrLog) : n + 2)),
-                   ld1(src + (rot ? auto_src(n + 3, J.gal, kSrLog) : n + 3)));
+  o.aq = rot ? auto_quad(n, J.gal, kSrLog) : AutoQuad{n, false, false};
+  o.x = ld4(src + o.aq.src);
   o.y = ld4(src2 + n);
   return o;
 }
 __device__ __forceinline__ uint4 sr_switched_finish(const KsJob& J, const SrRaw& v, const ModC& m) {
-  if (J.kind != KS_HMULT) return v.x;
+  if (J.kind != KS_HMULT) return auto_turn(v.x, v.aq);
   return make_uint4(mulmod(v.x.x, v.y.x, m), mulmod(v.x.y, v.y.y, m), mulmod(v.x.z, v.y.z, m),
                     mulmod(v.x.w, v.y.w, m));
 }
@@ -1357,10 +1380,8 @@ __global__ __launch_bounds__(kSrT) void s2_moddown(KsConst K, JobArg<KsJob> JA) 
   const uint32_t* rb = hm ? J.b + i * N : ra;
   const uint32_t* rc = hm ? J.a + (Lz + i) * N : ra;
   const uint32_t* rd = hm ? J.b + (Lz + i) * N : ra;
-  const uint4 ea = make_uint4(ld1(ra + (rot ? auto_src(n, J.gal, kSrLog) : n)),
-                              ld1(ra + (rot ? auto_src(n + 1, J.gal, kSrLog) : n + 1)),
-                              ld1(ra + (rot ? auto_src(n + 2, J.gal, kSrLog) : n + 2)),
-                              ld1(ra + (rot ? auto_src(n + 3, J.gal, kSrLog) : n + 3)));
+  const AutoQuad aq = rot ? auto_quad(n, J.gal, kSrLog) : AutoQuad{n, false, false};
+  const uint4 ea = ld4(ra + aq.src);
   const uint4 eb = ld4(rb + n), ec = ld4(rc + n), ed = ld4(rd + n);
   sr_put_tw(stw, fw);  // published by the first barrier below
   // ModDown: w = sum_m x_m [P / p_m]_{q_i}, x_m = INTT(acc P row m) N^-1 (P / p_m)^-1
@@ -1404,7 +1425,7 @@ __global__ __launch_bounds__(kSrT) void s2_moddown(KsConst K, JobArg<KsJob> JA) 
   sr_ntt(sd, stw, q);
   const uint4 w = csub4(*reinterpret_cast<const uint4*>(sd + n), q2);  // [0, 2q)
   const uint4 a = sr_partials_sum(pa, groups, q);
-  uint4 d = rot ? ea : make_uint4(0, 0, 0, 0);
+  uint4 d = rot ? auto_turn(ea, aq) : make_uint4(0, 0, 0, 0);
   if (hm) {
     if (c == 0) {
       d = make_uint4(mulmod(ea.x, eb.x, mi), mulmod(ea.y, eb.y, mi), mulmod(ea.z, eb.z, mi), mulmod(ea.w, eb.w, mi));

@@ -41,3 +41,24 @@ def test_column_kernels_at_every_digit_size(logN, alpha):
         for o, w in zip(outs, O.hrot_hoisted(par, ct1, L, [rot, 1], [key, key])):
             msg = first_mismatch(host(o), w)
             assert not msg, f"hoisted N=2^{logN} digit {alpha} L={L}: {msg}"
+
+
+@pytest.mark.parametrize("name,L", [("n12_l4", 4), ("toy_n12", 5), ("n16_l36", 13)])
+def test_rotations_of_a_ciphertext_at_a_four_byte_offset(name, L):
+    """The automorphism reads 16-byte quads; ciphertexts need only be 4-byte aligned."""
+    spec = ci.get(name)
+    par, ctx, rng = O.Params.from_spec(spec), P.Context.from_spec(spec), ci.Rng(77)
+    h, N = ctx.handle, spec.N
+    ct, key = rng.polys(2, spec.q[:L], N), rng.evk(spec)
+    room = torch.empty(1 + ct.size, dtype=torch.int32, device="cuda")
+    shifted = room[1:].view(2, L, N)
+    shifted.copy_(dev(ct))
+    assert shifted.data_ptr() % 16 == 4
+    for rot in (0, 1, 2, 3, N // 2 - 1):
+        out = empty(2, L, N)
+        P.ckks_hrot(h, shifted, L, rot, dev(key), out, ctx.workspace("HROT", L))
+        msg = first_mismatch(host(out), O.hrot(par, ct, L, rot, key))
+        assert not msg, f"hrot by {rot}: {msg}"
+        P.ckks_hrot_hoisted(h, shifted, L, [rot], [dev(key)], [out], ctx.workspace("HROT_HOISTED", L))
+        msg = first_mismatch(host(out), O.hrot_hoisted(par, ct, L, [rot], [key])[0])
+        assert not msg, f"hoisted rotation by {rot}: {msg}"
