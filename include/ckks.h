@@ -76,17 +76,18 @@ enum {
  * names times that kernel. */
 enum {
     CKKS_STAGE_INTT_BLOCKS = 1,     /* K1: INTT block pass of the switched polynomial */
-    CKKS_STAGE_INTT_COLS = 2,       /* K2: INTT column pass + BConv pre-multiply */
-    CKKS_STAGE_BCONV_UP = 3,        /* K3: ModUp base conversion, all digits */
-    CKKS_STAGE_NTT_COLS_UP = 4,     /* K4: NTT column pass of the ModUp rows */
-    CKKS_STAGE_NTT_IP = 5,          /* K5: NTT block pass + key inner product (+ P-row INTT pass);
-                                       the Q rows only when the inner product is split */
-    CKKS_STAGE_INTT_COLS_P = 6,     /* K6: INTT column pass of the P rows */
-    CKKS_STAGE_BCONV_DOWN = 7,      /* K7: ModDown base conversion */
-    CKKS_STAGE_NTT_COLS_DOWN = 8,   /* K8: NTT column pass of the ModDown rows */
-    CKKS_STAGE_NTT_COMBINE = 9,     /* K9: NTT block pass + (acc - w) P^-1 + epilogue */
+    CKKS_STAGE_INTT_COLS = 2,       /* KC: INTT column pass + BConv pre-multiply */
+    CKKS_STAGE_BCONV_UP = 3,        /* KC: ModUp base conversion, all digits */
+    CKKS_STAGE_NTT_COLS_UP = 4,     /* KC: NTT column pass of the ModUp rows */
+    CKKS_STAGE_NTT_IP = 5,          /* K5 on the Q rows: NTT block pass + key inner product, NTT block
+                                       pass of w, (acc - w) P^-1 + epilogue; at N = 2^12 under the
+                                       whole-limb schedule its first kernel */
+    CKKS_STAGE_INTT_COLS_P = 6,     /* KC: INTT column pass of the P rows */
+    CKKS_STAGE_BCONV_DOWN = 7,      /* KC: ModDown base conversion */
+    CKKS_STAGE_NTT_COLS_DOWN = 8,   /* KC: NTT column pass of the ModDown rows */
+    CKKS_STAGE_NTT_COMBINE = 9,     /* the same kernel as NTT_IP; under the whole-limb schedule the second */
     CKKS_STAGE_RESCALE_NTT = 10,    /* R4: rescale NTT block pass + combine */
-    CKKS_STAGE_NTT_IP_P = 11        /* K5 on the P rows when the inner product is split */
+    CKKS_STAGE_NTT_IP_P = 11        /* K5 on the P rows: NTT block pass + key inner product + INTT block pass */
 };
 
 typedef struct ckks_ctx ckks_ctx;
@@ -301,8 +302,8 @@ int ckks_rescale(const ckks_ctx *ctx, const uint32_t *ct, int L, uint32_t *out, 
  *                    kernels that hold whole limbs in LDS (ModUp + inner
  *                    product per row and digit group, ModDown + epilogue per
  *                    output row) instead of the five-kernel pipeline (hoisted
- *                    rotations and batch plans with a split inner product
- *                    keep the five kernels).  Small grids keep their own
+ *                    rotations and batch plans with split != 0 keep the
+ *                    five kernels).  Small grids keep their own
  *                    shapes.  0..15.
  * Default {12, 6, 128, 0}; {12, 6, 128, 8} for N = 2^12.  The schedule is read when work is enqueued (and when
  * a graph batch is captured); changing it must not overlap calls on the
@@ -381,15 +382,16 @@ int ckks_batch_launch(ckks_batch *batch, void *stream);
  * adjacent); consecutive groups of jobs_per_launch of them (0 = all) each
  * run the pipeline once, group g on branch g mod streams; branches are
  * streams forked from and joined back to the launch stream, so groups
- * overlap on the device; split != 0 runs the Q-row inner product of each
- * group on a side stream (Sec. IV-B complementary pipelining): split = 1
- * starts it beside the P-row inner product, split = 2 after it, so that it
- * overlaps only the P-row ModDown chain.
+ * overlap on the device.  The inner product always runs in two parts, the P
+ * rows before ModDown's column kernel and the Q rows after it, fused with
+ * ModDown's combine, so split chooses only, at N = 2^12 under the whole-limb
+ * schedule, between the two whole-limb kernels (0) and the five-kernel
+ * pipeline (1 or 2); elsewhere every value runs the same launches.
  * Rescale jobs run on the last branch.  Every plan gives bitwise the same
  * results.  Default {0, 1, 1}; {0, 1, 0} for a batch of one key-switching
  * job, and at N = 2^12 under the whole-limb schedule (ntt_shape bit 8) while
- * (L + k) * min(beta, 4) * jobs <= 800 for its largest level L (split runs
- * the five-kernel pipeline, which pays off only past that).  A batch created with use_graph runs one
+ * (L + k) * min(beta, 4) * jobs <= 800 for its largest level L (the
+ * five-kernel pipeline pays off only past that).  A batch created with use_graph runs one
  * branch (streams = 1): a multi-branch launch sequence is not captured.
  */
 typedef struct ckks_batch_plan {
@@ -417,7 +419,8 @@ int ckks_batch_set_schedule(ckks_batch *batch, const ckks_schedule *sched);
 /*
  * Autotuner: times candidate plans (jobs_per_launch in {all, 32, 16, 8, 4, 2}
  * below the job count, streams 1..4 up to the number of groups (1 for a
- * graph batch), split 0/1/2) under the batch's schedule, then, under the
+ * graph batch), at N = 2^12 under the whole-limb schedule split 0/1) under the
+ * batch's schedule, then, under the
  * best plan, up to four other BConv schedules ({12, 6, 128}, {6, 4, 128},
  * {4, 6, 128}, {12, 12, 128}, with the batch's ntt_shape), then the other
  * seven NTT shapes under the best of those: each candidate as one warm-up

@@ -201,13 +201,10 @@ struct ckks_batch {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   hipStream_t capture = nullptr;
-  // branch 0 is the launch stream; branches 1.. and every branch's side
-  // stream (complementary pipelining) belong to the batch
+  // branch 0 is the launch stream; branches 1.. belong to the batch
   hipStream_t branch[kMaxBranches] = {};
-  hipStream_t side[kMaxBranches] = {};
   hipEvent_t fork = nullptr;
   hipEvent_t join[kMaxBranches] = {};
-  std::vector<hipEvent_t> gev;  // fork / join events of the split, two per launch group
   std::vector<std::pair<ckks_batch_plan, float>> tune_log;  // last ckks_batch_tune: plan, us
   Ctx::Sched sched;  // kernel schedule of this batch's launches (the context's at creation)
 };
@@ -240,11 +237,7 @@ hipError_t batch_enqueue(ckks_batch* b, hipStream_t st) {
     } else {
       ka.table = b->d_ks + s0;
     }
-    if (b->plan.split && b->gev.size() < 2 * (size_t)group + 2) return hipErrorInvalidValue;
-    const KsSplit sp = b->plan.split
-                           ? KsSplit{b->side[br], b->gev[2 * group], b->gev[2 * group + 1], b->plan.split == 2}
-                           : KsSplit{};
-    if ((e = ks_launch(c, b->sched, ka, cnt, b->L_ks[s0], true, false, on(br), sp)) !=
+    if ((e = ks_launch(c, b->sched, ka, cnt, b->L_ks[s0], true, false, on(br), b->plan.split == 0)) !=
         hipSuccess)
       return e;
   }
@@ -263,25 +256,6 @@ hipError_t batch_enqueue(ckks_batch* b, hipStream_t st) {
       if ((e = hipEventRecord(b->join[br], b->branch[br])) != hipSuccess) return e;
       if ((e = hipStreamWaitEvent(st, b->join[br], 0)) != hipSuccess) return e;
     }
-  }
-  return hipSuccess;
-}
-
-int batch_groups(const ckks_batch* b, const ckks_batch_plan& p) {
-  if (b->n_ks == 0) return 0;
-  const int B = p.jobs_per_launch > 0 ? std::min(p.jobs_per_launch, b->n_ks) : b->n_ks;
-  return (b->n_ks + B - 1) / B;
-}
-
-// Two events per launch group, so no event is recorded twice in one launch
-// sequence (in particular not inside one graph capture).
-hipError_t batch_events(ckks_batch* b, const ckks_batch_plan& p) {
-  const size_t need = 2 * (size_t)batch_groups(b, p);
-  while (b->gev.size() < need) {
-    hipEvent_t ev;
-    const hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-    if (e != hipSuccess) return e;
-    b->gev.push_back(ev);
   }
   return hipSuccess;
 }
@@ -320,10 +294,8 @@ void batch_free(ckks_batch* b) {
   if (b->capture) (void)hipStreamDestroy(b->capture);
   for (int i = 0; i < kMaxBranches; ++i) {
     if (b->branch[i]) (void)hipStreamDestroy(b->branch[i]);
-    if (b->side[i]) (void)hipStreamDestroy(b->side[i]);
     if (b->join[i]) (void)hipEventDestroy(b->join[i]);
   }
-  for (hipEvent_t ev : b->gev) (void)hipEventDestroy(ev);
   if (b->fork) (void)hipEventDestroy(b->fork);
   if (b->d_ks) (void)hipFree(b->d_ks);
   if (b->d_rs) (void)hipFree(b->d_rs);
@@ -795,12 +767,11 @@ int ckks_batch_create(const ckks_ctx* ctx, const ckks_job* h_jobs, int n, int us
   b->Lmax_rs = Lrs;
   b->use_graph = use_graph != 0;
   b->sched = ctx->c.sched;
-  // complementary pipelining pays off only when a launch group holds several
-  // jobs; a lone key-switch runs unsplit, as a single call does.  On a small
-  // ring with the whole-limb schedule the unsplit launch (two kernels) is the
-  // faster one until its first kernel needs about 800 work-groups: HMults at
-  // N = 2^12, L = 4 (20 work-groups each) measured 1.4-2.3x faster unsplit for
-  // 2-32 jobs and even at 48.
+  // split: on a small ring with the whole-limb schedule the unsplit launch (two
+  // kernels) is the faster one until its first kernel needs about 800
+  // work-groups: HMults at N = 2^12, L = 4 (20 work-groups each) measured
+  // 1.4-2.3x faster unsplit for 2-32 jobs and even at 48.  Elsewhere the flag
+  // changes nothing.
   const int Lks = ks.empty() ? 0 : ks[order[0]].L;
   const bool whole_limb = c.logN == kSrLog && (b->sched.ntt_shape & kShapeWholeLimb);
   const long sr_wgs = (long)(Lks + c.k) * std::min(c.beta(std::max(Lks, 1)), kSrGroups) * b->n_ks;
@@ -830,9 +801,7 @@ int ckks_batch_create(const ckks_ctx* ctx, const ckks_job* h_jobs, int n, int us
   bool ok = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess;
   for (int i = 0; ok && i < kMaxBranches; ++i)
     ok = (i == 0 || hipStreamCreateWithFlags(&b->branch[i], hipStreamNonBlocking) == hipSuccess) &&
-         hipStreamCreateWithFlags(&b->side[i], hipStreamNonBlocking) == hipSuccess &&
          hipEventCreateWithFlags(&b->join[i], hipEventDisableTiming) == hipSuccess;
-  ok = ok && batch_events(b, b->plan) == hipSuccess;
   if (!ok) {
     batch_free(b);
     return fail(CKKS_EHIP, "creating the batch's streams / events failed");
@@ -875,7 +844,6 @@ int ckks_batch_set_plan(ckks_batch* b, const ckks_batch_plan* plan) {
   if (b->use_graph && plan->streams > 1)
     return fail(CKKS_EUNSUPPORTED, "a graph batch runs one branch (streams = 1)");
   DeviceGuard g(b->c->device);
-  CKKS_TRY(batch_events(b, *plan), "creating the batch's events");
   const ckks_batch_plan old = b->plan;
   b->plan = *plan;
   b->plan.reserved = 0;
@@ -948,13 +916,17 @@ int ckks_batch_tune(ckks_batch* b, int reps, void* stream, ckks_batch_plan* best
   float top_us = -1.f;
   hipError_t e = hipSuccess;
   const int max_streams = b->use_graph ? 1 : kMaxBranches;
+  // split changes the launch only where it chooses between two pipelines
+  const std::vector<int> splits = b->c->logN == kSrLog && (start_sched.ntt_shape & kShapeWholeLimb)
+                                      ? std::vector<int>{0, 1}
+                                      : std::vector<int>{start.split};
   // 1) launch plans under the batch's schedule
   for (int B : sizes) {
     const int groups = B ? (b->n_ks + B - 1) / B : 1;
-    if ((e = batch_events(b, ckks_batch_plan{B, 1, 1, 0})) != hipSuccess) break;
     for (int S = 1; S <= max_streams && e == hipSuccess; ++S) {
       if (S > 1 && S > groups + (b->n_rs ? 1 : 0)) break;
-      for (int split = 0; split <= 2 && e == hipSuccess; ++split) {
+      for (int split : splits) {
+        if (e != hipSuccess) break;
         b->plan = ckks_batch_plan{B, S, split, 0};
         float us = 0.f;
         if ((e = time_it(&us)) != hipSuccess) break;
@@ -970,7 +942,6 @@ int ckks_batch_tune(ckks_batch* b, int reps, void* stream, ckks_batch_plan* best
   // a single operation's, so the context's schedule need not suit it
   if (e == hipSuccess) {
     b->plan = top;
-    e = batch_events(b, top);
     const int sh = start_sched.ntt_shape;
     const Ctx::Sched cands[] = {{12, 6, 128, sh}, {6, 4, 128, sh}, {4, 6, 128, sh}, {12, 12, 128, sh}};
     for (const Ctx::Sched& cs : cands) {
@@ -1004,8 +975,8 @@ int ckks_batch_tune(ckks_batch* b, int reps, void* stream, ckks_batch_plan* best
   (void)hipEventDestroy(t1);
   b->plan = e == hipSuccess ? top : start;
   b->sched = e == hipSuccess ? top_sched : start_sched;
-  hipError_t ce = batch_events(b, b->plan);
-  if (ce == hipSuccess && b->use_graph) ce = batch_capture(b);
+  hipError_t ce = hipSuccess;
+  if (b->use_graph) ce = batch_capture(b);
   if (e != hipSuccess) return hip_fail(e, "timing candidate plans");
   if (ce != hipSuccess) return hip_fail(ce, "re-capturing the batch graph");
   if (best) *best = top;

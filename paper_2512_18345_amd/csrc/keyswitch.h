@@ -52,20 +52,6 @@ constexpr int kShapeWholeLimb = 8;   // N = 2^kSrLog: two kernels with whole lim
 constexpr int kShapeAll = 15;
 constexpr int kSrGroups = 4;  // whole-limb key-switch: digit groups of its first kernel, at most
 
-// Rows of the key inner product a K5 launch covers.
-enum KsPart : int { KS_PART_ALL = 0, KS_PART_P = 1, KS_PART_Q = 2 };
-
-// Complementary pipelining resources: a side stream and two events (fork,
-// join).  side == nullptr runs the pipeline on one stream.  The Q-row inner
-// product runs on the side stream either beside the P-row one (p_first =
-// false: both start after ModUp) or after it (p_first = true: the Q rows
-// overlap only the ModDown chain).
-struct KsSplit {
-  hipStream_t side = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
-  bool p_first = false;
-};
-
 // Jobs either inline in the kernel arguments (n <= kInlineJobs) or in a device
 // table written only by the host.  get() returns the job by value through
 // scalar loads, so every field is work-group uniform.
@@ -86,9 +72,10 @@ size_t rs_ws_words(const Ctx& c, int L);
 // Enqueue the key-switching pipeline for njobs jobs whose largest level is
 // Lmax under kernel schedule sc (the context's, or a batch's own).
 // with_modup: some job is not KS_HOIST (stage 1 runs); with_hoist: some job
-// is KS_HOIST.
+// is KS_HOIST.  whole_limb: at N = 2^kSrLog the schedule may choose the two
+// whole-limb kernels.
 hipError_t ks_launch(const Ctx& c, const Ctx::Sched& sc, const JobArg<KsJob>& jobs, int njobs, int Lmax,
-                     bool with_modup, bool with_hoist, hipStream_t st, const KsSplit& sp = KsSplit{});
+                     bool with_modup, bool with_hoist, hipStream_t st, bool whole_limb = true);
 // Enqueue the ModUp of njobs KS_MODUP jobs (K1, KC and the block pass of the
 // new rows: M ends fully in the evaluation domain, canonical).
 hipError_t ks_modup_launch(const Ctx& c, const Ctx::Sched& sc, const JobArg<KsJob>& jobs, int njobs, int Lmax,

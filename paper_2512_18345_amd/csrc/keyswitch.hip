@@ -7,14 +7,17 @@
 //  K1  INTT block pass of the input (loader forms d: d, c1*c1', or sigma(c1)) -> y
 //  KC  (up) INTT column pass of each digit's limbs, N^-1 (D_j/q_i)^-1, ModUp
 //      BConv, NTT column pass of the new rows                        -> z
-//  K5  NTT block pass fused with the inner product over the digits
-//      (digit rows come straight from the loader; hoisted jobs gather
-//      sigma(M) instead of transforming), then, for the P rows, the first
+//  K5  (P rows) NTT block pass fused with the inner product over the digits
+//      (hoisted jobs gather sigma(M) instead of transforming), then the first
 //      INTT pass of ModDown                                          -> acc
 //  KC  (down) INTT column pass of the P rows, N^-1 (P/p_m)^-1, ModDown BConv,
 //      NTT column pass, both components                              -> w
-//  K9  NTT block pass fused with (acc - w) P^-1 plus the epilogue
-//      term (d0 / d1 of HMult, sigma(c0) of HRot)                    -> out
+//  K5  (Q rows) the same inner product (digit rows come straight from the
+//      loader), the NTT block pass of w, (acc - w) P^-1 plus the epilogue term
+//      (d0 / d1 of HMult, sigma(c0) of HRot)                         -> out
+//
+// The Q rows' inner product waits for w so that it never leaves registers:
+// written and read back by a kernel of its own it cost 2L rows each way.
 //
 // The NTT's block pass is row-parallel; its column pass works down the columns
 // as BConv does, which is why the three column stages are one kernel.
@@ -26,6 +29,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "arith.h"
 #include "ctx.h"
@@ -367,16 +371,15 @@ __global__ __launch_bounds__(kWG) void km_ntt_blks(KsConst K, JobArg<KsJob> JA) 
 // ============================================================================
 
 // P rows of the inner product: the INTT block pass that ModDown starts with,
-// on both components (res0, res1: the lane's four quads of its line), in LDS
+// on both components (res0, res1: the lane's four quads of its line) under the
+// inverse twiddles tw, requested before the inner product, in LDS
 // tiles s and s + kBlkTile that other waves may still be reading; stored in the
 // row-group layout for the column kernel.
 __device__ __forceinline__ void p_rows_intt(uint32_t* s, const KsConst& K, int pi, const MontQ& m,
-                                            const uint4 res0[4], const uint4 res1[4], uint32_t* acc0,
-                                            uint32_t* acc1) {
+                                            const BlkTw& tw, const uint4 res0[4], const uint4 res1[4],
+                                            uint32_t* acc0, uint32_t* acc1) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int line = blk_line<16>(lane, w);
-  BlkTw tw;
-  tw.load(K.M.row_itw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_itw(pi), lane);
   __syncthreads();
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
@@ -399,6 +402,12 @@ __device__ __forceinline__ void p_rows_intt(uint32_t* s, const KsConst& K, int p
   }
 }
 
+// Has the quad's words computed here: no instruction, an order for the scheduler.
+__device__ __forceinline__ void pin4(uint4& v) {
+  asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // Reduction of four 64-bit sums.
 __device__ __forceinline__ uint4 reduce4(const uint64_t a[4], const ModC& m) {
   return make_uint4(reduce64(a[0], m.q, m.mu_hi, m.mu_lo), reduce64(a[1], m.q, m.mu_hi, m.mu_lo),
@@ -411,18 +420,127 @@ __device__ __forceinline__ void mac4(uint64_t a[4], uint4 v, uint4 e) {
   a[3] += (uint64_t)v.w * e.w;
 }
 
+// The w row of component c and Q row r (column pass done, row-group layout), loaded ahead.
+__device__ __forceinline__ void load_w(const KsView& V, int c, int r, uint32_t base, size_t N, uint4 w[8]) {
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+    w[4 * c + kk] = ld4(V.w + ((size_t)c * V.L + r) * N + base + RowGroup<16>::word(threadIdx.x, kk, 0));
+}
+
+// What a job adds to a quad of row i of the two components of
+//   out[c] = (acc[c] - w[c]) P^-1 + e[c]:
+// e = (c0 c0', c0 c1' + c1 c0') for HMULT, (sigma(c0), 0) for rotations, else
+// 0.  Loaded ahead without a branch (the kind selects addresses; a load in a
+// branch whose value merges after it makes the compiler wait for it there).
+struct TermQuad {
+  uint4 a, b, c, d;  // HMULT: c0, c0', c1, c1'; rotations: a holds the source quad of sigma(c0)
+  AutoQuad aq;
+};
+template <bool HOIST = false>
+__device__ __forceinline__ TermQuad term_load(const KsJob& J, int L, int i, uint32_t n, size_t N, int logN) {
+  const bool hm = J.kind == KS_HMULT, rot = HOIST || J.kind == KS_HROT || J.kind == KS_HOIST;
+  const size_t row = (size_t)i * N, LN = (size_t)L * N;
+  TermQuad t;
+  t.aq = rot ? auto_quad(n, J.gal, logN) : AutoQuad{n, false, false};
+  t.a = ld4(J.a + row + t.aq.src);
+  if (HOIST) return t;
+  t.b = ld4((hm ? J.b : J.a) + row + t.aq.src);
+  t.c = ld4(J.a + row + (hm ? LN : 0) + t.aq.src);
+  t.d = ld4((hm ? J.b + LN : J.a) + row + t.aq.src);
+  return t;
+}
+// w comes in [0, 4q); x = acc + 2q - w < 3q < 2^32 after a correction.  HMULT
+// reduces x P^-1 and its products in one sum, at most 5 q^2 < 2^63.
+template <bool HOIST = false>
+__device__ __forceinline__ void combine_quad(const KsConst& K, const KsJob& J, int L, int i, uint32_t n, size_t N,
+                                             const ModC& mc, const TermQuad& t, uint4 a0, uint4 a1, uint4 w0,
+                                             uint4 w1) {
+  const MontQ m = mont_q(mc);
+  auto diff = [&](uint4 a, uint4 w) {
+    w = csub4(w, m.q2);
+    return make_uint4(a.x + m.q2 - w.x, a.y + m.q2 - w.y, a.z + m.q2 - w.z, a.w + m.q2 - w.w);
+  };
+  const uint4 x0 = diff(a0, w0), x1 = diff(a1, w1);
+  uint32_t* out0 = J.out + (size_t)i * N + n;
+  uint32_t* out1 = out0 + (size_t)L * N;
+  if (!HOIST && J.kind == KS_HMULT) {
+    const uint32_t pv = ldc(K.pinv + i).x;
+    uint64_t t0[4] = {(uint64_t)x0.x * pv, (uint64_t)x0.y * pv, (uint64_t)x0.z * pv, (uint64_t)x0.w * pv};
+    uint64_t t1[4] = {(uint64_t)x1.x * pv, (uint64_t)x1.y * pv, (uint64_t)x1.z * pv, (uint64_t)x1.w * pv};
+    mac4(t0, t.a, t.b);
+    mac4(t1, t.a, t.d);
+    mac4(t1, t.c, t.b);
+    st4(out0, reduce4(t0, mc));
+    st4(out1, reduce4(t1, mc));
+    return;
+  }
+  const uint32_t pv = ldc(K.M.pinv + i);
+  auto scale = [&](uint4 x) {
+    return make_uint4(csub(mont_mul(x.x, pv, m), m.q), csub(mont_mul(x.y, pv, m), m.q),
+                      csub(mont_mul(x.z, pv, m), m.q), csub(mont_mul(x.w, pv, m), m.q));
+  };
+  uint4 o0 = scale(x0);
+  if (HOIST || J.kind != KS_PLAIN) {
+    const uint4 e = auto_turn(t.a, t.aq);
+    o0 = make_uint4(csub(o0.x + e.x, m.q), csub(o0.y + e.y, m.q), csub(o0.z + e.z, m.q), csub(o0.w + e.w, m.q));
+  }
+  st4(out0, o0);
+  st4(out1, scale(x1));
+}
+
+// Q rows: ModDown's combine on the inner product where it stands, in the
+// lane's registers (res0, res1): the block pass of both w rows in tiles s and
+// s + kBlkTile, which other waves may still be reading, under the twiddles the
+// digits used (same prime, same rows), then the job's term and the output.
+template <bool HOIST>
+__device__ __forceinline__ void q_rows_combine(uint32_t* s, const KsConst& K, const KsJob& J, const KsView& V,
+                                               int r, const ModC& mc, const BlkTw& tw, const uint4 wraw[8],
+                                               const uint4 res0[4], const uint4 res1[4]) {
+  const MontQ m = mont_q(mc);
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  const size_t N = (size_t)1 << K.T.logN;
+  __syncthreads();
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    RowGroup<16>::to_lds(s, threadIdx.x, kk, wraw[kk]);
+    RowGroup<16>::to_lds(s + kBlkTile, threadIdx.x, kk, wraw[4 + kk]);
+  }
+  const uint32_t n0 = blockIdx.x * kTile + line * 256 + 4 * (lane & 15);
+  // the job's terms: two quads now, to land during the transforms, two after
+  // them (all four would cost a resident work-group in registers)
+  TermQuad term[4];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) term[kk] = term_load<HOIST>(J, V.L, r, n0 + 64 * kk, N, K.T.logN);
+  __syncthreads();
+  blk_fwd_a(s, line, lane, tw, m);
+  blk_fwd_a(s + kBlkTile, line, lane, tw, m);
+  wave_sync();
+  blk_fwd_b(s, line, lane, tw, m);
+  blk_fwd_b(s + kBlkTile, line, lane, tw, m);
+  wave_sync();
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    if (kk < 2) term[kk + 2] = term_load<HOIST>(J, V.L, r, n0 + 64 * (kk + 2), N, K.T.logN);
+    const int pos = 4 * (lane & 15) + 64 * kk;
+    combine_quad<HOIST>(K, J, V.L, r, n0 + 64 * kk, N, mc, term[kk], res0[kk], res1[kk], blk_quad(s, line, pos),
+                 blk_quad(s + kBlkTile, line, pos));
+  }
+}
+
 // Any digit count: the digits in turn through one tile, accumulators in
 // registers.  HOIST selects the variant for hoisted-rotation jobs (gather of
 // sigma(M), no transform; each rotation brings its own key, streamed with the
 // non-temporal hint); the other variant serves every other job kind.
-template <bool HOIST>
-__global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> JA, int part) {
+template <bool HOIST, bool Q>
+__global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> JA) {
   const KsJob J = JA.get(blockIdx.z);
   const int logN = K.T.logN;
   const size_t N = (size_t)1 << logN;
   const KsView V = ks_view(J, K, N);
-  const int r = blockIdx.y + (part == KS_PART_P ? V.L : 0);
-  if (r >= V.R || (part == KS_PART_Q && r >= V.L) || (J.kind == KS_HOIST) != HOIST) return;
+  const int r = Q ? blockIdx.y : V.L + blockIdx.y;
+  if ((Q && r >= V.L) || (J.kind == KS_HOIST) != HOIST) return;
   __shared__ __align__(16) uint32_t s[2 * kBlkTile];
   const int pi = ks_pidx(r, V.L, K.T.L_max);
   const ModC mc = ldc(K.T.mod + pi);
@@ -493,39 +611,47 @@ __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> J
   }
 
   // one reduction per output (the overflow-free accumulation of Sec. III-C2)
-  uint4 r0[4], r1[4];
+  uint4 r0[4], r1[4], wraw[8];
+  BlkTw itw;
+  if constexpr (Q) {
+    load_w(V, 0, r, base, N, wraw);
+    load_w(V, 1, r, base, N, wraw);
+  } else
+    itw.load(K.M.row_itw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_itw(pi), lane);
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     r0[kk] = reduce4(a0[kk], mc);
     r1[kk] = reduce4(a1[kk], mc);
   }
-  uint32_t* acc0 = V.acc + (size_t)r * N;
-  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
-  if (r < V.L) {
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      st4(acc0 + n0 + 64 * kk, r0[kk]);
-      st4(acc1 + n0 + 64 * kk, r1[kk]);
-    }
-    return;
+  if constexpr (Q) {
+    if (HOIST) tw.load(K.M.row_tw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_tw(pi), lane);
+    q_rows_combine<HOIST>(s, K, J, V, r, mc, tw, wraw, r0, r1);
+  } else {
+    uint32_t* acc0 = V.acc + (size_t)r * N;
+    uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
+    p_rows_intt(s, K, pi, m, itw, r0, r1, acc0 + base, acc1 + base);
   }
-  p_rows_intt(s, K, pi, m, r0, r1, acc0 + base, acc1 + base);
 }
 
 // Variant of K5 for contexts with at most NB digits: every digit's tile is
 // staged and transformed in its own LDS slot first (all loads in flight at
 // once), then the inner product runs one 16-byte quad at a time, so the
 // 64-bit accumulators never hold more than four elements per component.
+// Bound: Q rows, memory (HMult at N = 2^16, L = 36: 160 MB in 33 us, 4.8 TB/s;
+// with a combine kernel of its own, all rows 29.6 + 19.1 us); P rows, the
+// chain of one round of work-groups (17 us for a quarter of the rows).  16
+// hoisted rotations: 316 + 183 us in two kernels -> 86 + 311.  At most 168
+// registers, so that three work-groups share a CU: at 191 the Q rows took 37.9.
 // NT: the key words are read with the non-temporal hint (a launch of one
 // job reads its key once; batches whose jobs share a key keep it cached).
-template <int NB, bool NT>
-__global__ __launch_bounds__(kWG) void k5s_ntt_blks_ip(KsConst K, JobArg<KsJob> JA, int part) {
+template <int NB, bool NT, bool Q>
+__global__ __launch_bounds__(kWG) void k5s_ntt_blks_ip(KsConst K, JobArg<KsJob> JA) {
   const KsJob J = JA.get(blockIdx.z);
   const int logN = K.T.logN;
   const size_t N = (size_t)1 << logN;
   const KsView V = ks_view(J, K, N);
-  const int r = blockIdx.y + (part == KS_PART_P ? V.L : 0);
-  if (r >= V.R || (part == KS_PART_Q && r >= V.L) || J.kind == KS_HOIST) return;
+  const int r = Q ? blockIdx.y : V.L + blockIdx.y;
+  if ((Q && r >= V.L) || J.kind == KS_HOIST) return;
   __shared__ __align__(16) uint32_t s[NB * kBlkTile];
   const int pi = ks_pidx(r, V.L, K.T.L_max);
   const ModC mc = ldc(K.T.mod + pi);
@@ -606,11 +732,10 @@ __global__ __launch_bounds__(kWG) void k5s_ntt_blks_ip(KsConst K, JobArg<KsJob> 
   // key word below q < 2^30, so a product is below 2^62 and the sum of at
   // most four (NB <= 4) stays below 2^64 for the single exact reduction.
   static_assert(NB >= 2 && NB <= 4, "64-bit sum of lazy products; two slots for the P rows");
-  uint4 res0[4], res1[4];
+  uint4 res0[4], res1[4], wraw[8];
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     uint64_t a0[4] = {0, 0, 0, 0}, a1[4] = {0, 0, 0, 0};
-    if (kk >= KPF) key_quad(kk);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const uint32_t msk = j < V.beta ? ~0u : 0u;
@@ -624,18 +749,26 @@ __global__ __launch_bounds__(kWG) void k5s_ntt_blks_ip(KsConst K, JobArg<KsJob> 
     }
     res0[kk] = reduce4(a0, mc);
     res1[kk] = reduce4(a1, mc);
-  }
-  uint32_t* acc0 = V.acc + (size_t)r * N;
-  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
-  if (r < V.L) {
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      st4(acc0 + n0 + 64 * kk, res0[kk]);
-      st4(acc1 + n0 + 64 * kk, res1[kk]);
+    // the next loads in the registers this quad leaves, no earlier (raising
+    // them all costs a resident work-group)
+    pin4(res0[kk]);
+    pin4(res1[kk]);
+    if (kk + KPF < 4) key_quad(kk + KPF);
+    if (Q && kk == 3) {
+      load_w(V, 0, r, base, N, wraw);
+      load_w(V, 1, r, base, N, wraw);
     }
-    return;
+    __builtin_amdgcn_sched_barrier(0);
   }
-  p_rows_intt(s, K, pi, m, res0, res1, acc0 + base, acc1 + base);
+  if constexpr (Q) {
+    q_rows_combine<false>(s, K, J, V, r, mc, tw, wraw, res0, res1);
+  } else {
+    uint32_t* acc0 = V.acc + (size_t)r * N;
+    uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
+    BlkTw itw;
+    itw.load(K.M.row_itw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_itw(pi), lane);
+    p_rows_intt(s, K, pi, m, itw, res0, res1, acc0 + base, acc1 + base);
+  }
 }
 
 // K5 for hoisted rotations of at most NB digits.  sigma_g maps each aligned
@@ -647,15 +780,15 @@ __global__ __launch_bounds__(kWG) void k5s_ntt_blks_ip(KsConst K, JobArg<KsJob> 
 // first KPF quads are requested with the tiles; the inner product and the
 // P-row INTT block pass follow as in k5s, on canonical words (M is fully
 // transformed).
-template <int NB>
-__global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA, int part) {
+template <int NB, bool Q>
+__global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA) {
   static_assert(NB >= 2 && NB <= 4, "slots for two to four digits");
   const KsJob J = JA.get(blockIdx.z);
   const int logN = K.T.logN;
   const size_t N = (size_t)1 << logN;
   const KsView V = ks_view(J, K, N);
-  const int r = blockIdx.y + (part == KS_PART_P ? V.L : 0);
-  if (r >= V.R || (part == KS_PART_Q && r >= V.L) || J.kind != KS_HOIST) return;
+  const int r = Q ? blockIdx.y : V.L + blockIdx.y;
+  if ((Q && r >= V.L) || J.kind != KS_HOIST) return;
   constexpr int WORDS = NB * kTile > 2 * kBlkTile ? NB * kTile : 2 * kBlkTile;
   __shared__ __align__(16) uint32_t s[WORDS];
   const int pi = ks_pidx(r, V.L, K.T.L_max);
@@ -696,12 +829,11 @@ __global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA
 
   // inner product of sigma(M) quad by quad (canonical words: products below
   // 2^60, at most four summed, one reduction per output)
-  uint4 res0[4], res1[4];
+  uint4 res0[4], res1[4], wraw[8];
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     const uint32_t n = n0 + 64 * kk;
     const AutoQuad aq = auto_quad(n, J.gal, logN);
-    if (kk >= KPF) key_quad(kk);
     uint64_t a0[4] = {0, 0, 0, 0}, a1[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
@@ -716,18 +848,28 @@ __global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA
     }
     res0[kk] = reduce4(a0, mc);
     res1[kk] = reduce4(a1, mc);
-  }
-  uint32_t* acc0 = V.acc + (size_t)r * N;
-  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
-  if (r < V.L) {
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      st4(acc0 + n0 + 64 * kk, res0[kk]);
-      st4(acc1 + n0 + 64 * kk, res1[kk]);
+    // the next loads in the registers this quad leaves, no earlier (raising
+    // them all costs a resident work-group)
+    pin4(res0[kk]);
+    pin4(res1[kk]);
+    if (kk + KPF < 4) key_quad(kk + KPF);
+    if (Q && kk == 3) {
+      load_w(V, 0, r, base, N, wraw);
+      load_w(V, 1, r, base, N, wraw);
     }
-    return;
+    __builtin_amdgcn_sched_barrier(0);
   }
-  p_rows_intt(s, K, pi, mont_q(mc), res0, res1, acc0 + base, acc1 + base);
+  if constexpr (Q) {
+    BlkTw tw;
+    tw.load(K.M.row_tw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_tw(pi), lane);
+    q_rows_combine<true>(s, K, J, V, r, mc, tw, wraw, res0, res1);
+  } else {
+    uint32_t* acc0 = V.acc + (size_t)r * N;
+    uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
+    BlkTw itw;
+    itw.load(K.M.row_itw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_itw(pi), lane);
+    p_rows_intt(s, K, pi, mont_q(mc), itw, res0, res1, acc0 + base, acc1 + base);
+  }
 }
 
 // K5 for small grids (few tiles x rows): one work-group per four rows of a
@@ -735,8 +877,8 @@ __global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA
 // the threads share out the inner product's 256 quads, and for P rows waves 0
 // and 1 take a component each.  Four times the work-groups of k5s and a third
 // of its chain per wave.  Every barrier below is reached by all threads.
-template <int NB>
-__global__ __launch_bounds__(64 * NB) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJob> JA, int part) {
+template <int NB, bool Q>
+__global__ __launch_bounds__(64 * NB) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJob> JA) {
   static_assert(NB >= 2 && NB <= 4, "one wave per digit");
   constexpr int T = 64 * NB;
   constexpr int QPT = (256 + T - 1) / T;  // quads per thread of the inner product, at most
@@ -745,15 +887,18 @@ __global__ __launch_bounds__(64 * NB) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJ
   const int logN = K.T.logN;
   const size_t N = (size_t)1 << logN;
   const KsView V = ks_view(J, K, N);
-  const int r = blockIdx.y + (part == KS_PART_P ? V.L : 0);
-  if (r >= V.R || (part == KS_PART_Q && r >= V.L) || J.kind == KS_HOIST) return;
+  const int r = Q ? blockIdx.y : V.L + blockIdx.y;
+  if ((Q && r >= V.L) || J.kind == KS_HOIST) return;
   __shared__ __align__(16) uint32_t s[NB * TILE4];
   const int pi = ks_pidx(r, V.L, K.T.L_max);
   const ModC mc = ldc(K.T.mod + pi);
   const MontQ m = mont_q(mc);
-  const int a4 = blockIdx.x & 3;                        // which four rows of the group of 16
-  const uint32_t group = (blockIdx.x >> 2) * kTile;     // the group's first word
-  const uint32_t base = blockIdx.x * 1024;              // the four rows' first word in row order
+  // which four rows of which group of 16: the work-groups of one group, which
+  // share its lines, a multiple of N / 4096 apart, so on one XCD from N = 2^15 on
+  const int tiles = gridDim.x >> 2;
+  const int a4 = blockIdx.x / tiles, row4 = 4 * (blockIdx.x % tiles) + a4;
+  const uint32_t group = (blockIdx.x % tiles) * kTile;  // the group's first word
+  const uint32_t base = row4 * 1024;                    // the four rows' first word in row order
   const size_t KR = (size_t)K.T.L_max + K.k;            // key rows
   const int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int line = blk_line<4>(lane, 0);
@@ -761,7 +906,7 @@ __global__ __launch_bounds__(64 * NB) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJ
   const bool own = r >= lo && r < hi;
   uint32_t* slot = s + j * TILE4;
   BlkTw tw;
-  tw.load(K.M.row_tw(K.T, pi, blockIdx.x * 4 + line), K.M.blk_tw(pi), lane);
+  tw.load(K.M.row_tw(K.T, pi, row4 * 4 + line), K.M.blk_tw(pi), lane);
   if (j < V.beta) {
     uint4 v[4];
     if (own) {
@@ -790,6 +935,14 @@ __global__ __launch_bounds__(64 * NB) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJ
       k0v[i][jj] = ld4(k0);
       k1v[i][jj] = ld4(k0 + KR * N);
     }
+  }
+  uint4 wv[4];
+  BlkTw itw;
+  if (!Q) itw.load(K.M.row_itw(K.T, pi, row4 * 4 + line), K.M.blk_itw(pi), lane);
+  if (Q && j < 2) {
+    const uint32_t* wrow = V.w + ((size_t)j * V.L + r) * N + group;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) wv[kk] = ld4(wrow + RowGroup<4>::word(lane, kk, a4));
   }
   if (j < V.beta && !own) {
     wave_sync();
@@ -820,19 +973,30 @@ __global__ __launch_bounds__(64 * NB) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJ
     res0[i] = reduce4(a0, mc);
     res1[i] = reduce4(a1, mc);
   }
-  uint32_t* acc0 = V.acc + (size_t)r * N;
-  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
-  if (r < V.L) {  // uniform over the work-group
+  if constexpr (Q) {
+    // ModDown's combine: waves 0 and 1 transform a w row each, then every
+    // thread finishes its quads
+    __syncthreads();  // the inner product has read the tiles
+    if (j < 2) {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) RowGroup<4>::to_lds(slot, lane, kk, wv[kk]);
+      wave_sync();
+      blk_fwd_a(slot, line, lane, tw, m);
+      wave_sync();
+      blk_fwd_b(slot, line, lane, tw, m);
+    }
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < QPT; ++i) {
       const int e = 4 * (threadIdx.x + i * T);
-      if (e < 1024) {
-        st4(acc0 + base + e, res0[i]);
-        st4(acc1 + base + e, res1[i]);
-      }
+      if (e < 1024)
+        combine_quad(K, J, V.L, r, base + e, N, mc, term_load(J, V.L, r, base + e, N, logN), res0[i], res1[i], blk_quad(s, e >> 8, e & 255),
+                     blk_quad(s + TILE4, e >> 8, e & 255));
     }
     return;
   }
+  uint32_t* acc0 = V.acc + (size_t)r * N;
+  uint32_t* acc1 = V.acc + ((size_t)V.R + r) * N;
   __syncthreads();  // the inner product has read the tiles
 #pragma unroll
   for (int i = 0; i < QPT; ++i) {
@@ -844,94 +1008,14 @@ __global__ __launch_bounds__(64 * NB) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJ
   }
   __syncthreads();
   if (j < 2) {
-    tw.load(K.M.row_itw(K.T, pi, blockIdx.x * 4 + line), K.M.blk_itw(pi), lane);
-    blk_inv_a(slot, line, lane, tw, m);
+    blk_inv_a(slot, line, lane, itw, m);
     wave_sync();
-    blk_inv_b(slot, line, lane, tw, m);
+    blk_inv_b(slot, line, lane, itw, m);
     wave_sync();
     uint32_t* dst = (j ? acc1 : acc0) + group;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) st4(dst + RowGroup<4>::word(lane, kk, a4), RowGroup<4>::from_lds(slot, lane, kk));
   }
-}
-
-// ============================================================================
-// Stage 3: ModDown of both components (after kc_conv<CONV_DOWN>)
-// ============================================================================
-
-// out[c][i] = (acc[c][i] - NTT(w)[c][i]) P^-1 (+ the job's epilogue term).
-// Bound: memory, near the copy rate (seven to ten rows in and out per row pair).
-__global__ __launch_bounds__(kWG) void k9_ntt_blks_combine(KsConst K, JobArg<KsJob> JA) {
-  const KsJob J = JA.get(blockIdx.z);
-  const int logN = K.T.logN;
-  const size_t N = (size_t)1 << logN;
-  const KsView V = ks_view(J, K, N);
-  const int gr = blockIdx.y;
-  if (gr >= 2 * V.L) return;
-  const int c = gr / V.L, i = gr % V.L;
-  __shared__ __align__(16) uint32_t s[kBlkTile];
-  const ModC mc = ldc(K.T.mod + i);
-  const MontQ m = mont_q(mc);
-  const uint32_t base = blockIdx.x * kTile;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int line = blk_line<16>(lane, w);
-  const uint32_t n0 = base + line * 256 + 4 * (lane & 15);  // the lane's quads: n0 + 64 kk
-  const uint32_t* wrow = V.w + (size_t)gr * N + base;
-  BlkTw tw;
-  uint4 raw[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) raw[kk] = ld4(wrow + RowGroup<16>::word(threadIdx.x, kk, 0));
-  tw.load(K.M.row_tw(K.T, i, blockIdx.x * 16 + line), K.M.blk_tw(i), lane);
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) RowGroup<16>::to_lds(s, threadIdx.x, kk, raw[kk]);
-  __syncthreads();
-  blk_fwd_a(s, line, lane, tw, m);
-  wave_sync();
-  blk_fwd_b(s, line, lane, tw, m);
-  wave_sync();
-  const uint32_t pv = ldc(K.pinv + i).x, pvm = ldc(K.M.pinv + i);
-  const uint32_t* accr = V.acc + ((size_t)c * V.R + i) * N;
-  uint32_t* out = J.out + ((size_t)c * V.L + i) * N;
-  const size_t L = V.L;
-  const bool hmult = J.kind == KS_HMULT;
-  const bool rot = (J.kind == KS_HROT || J.kind == KS_HOIST) && c == 0;
-  // w from [0, 4q) to [0, 2q): x = a + 2q - w < 3q < 2^32.  Loads first (a store
-  // to out could alias a later load): the accumulator quads and what this
-  // component adds -- d0 = c0 c0' or d1 = c0 c1' + c1 c0' (HMULT), sigma(c0)
-  // (rotations, c = 0), else nothing.  HMULT reduces x P^-1 and its products
-  // in one sum: at most 5 q^2 < 2^63.
-  uint4 res[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const uint32_t n = n0 + 64 * kk;
-    const uint4 a = ld4(accr + n);
-    const uint4 v = csub4(blk_quad(s, line, 4 * (lane & 15) + 64 * kk), m.q2);
-    const uint4 x = make_uint4(a.x + m.q2 - v.x, a.y + m.q2 - v.y, a.z + m.q2 - v.z, a.w + m.q2 - v.w);
-    if (hmult) {
-      uint64_t t[4] = {(uint64_t)x.x * pv, (uint64_t)x.y * pv, (uint64_t)x.z * pv, (uint64_t)x.w * pv};
-      const uint4 xa = ld4(J.a + i * N + n), ya = ld4(J.b + i * N + n);
-      if (c == 0) {
-        mac4(t, xa, ya);
-      } else {
-        mac4(t, xa, ld4(J.b + (L + i) * N + n));
-        mac4(t, ld4(J.a + (L + i) * N + n), ya);
-      }
-      res[kk] = reduce4(t, mc);
-    } else {
-      uint4 d = make_uint4(0, 0, 0, 0);
-      if (rot) {
-        const uint32_t* c0 = J.a + i * N;
-        const AutoQuad aq = auto_quad(n, J.gal, logN);
-        d = auto_turn(ld4(c0 + aq.src), aq);
-      }
-      res[kk] = make_uint4(csub(csub(mont_mul(x.x, pvm, m), m.q) + d.x, m.q),
-                           csub(csub(mont_mul(x.y, pvm, m), m.q) + d.y, m.q),
-                           csub(csub(mont_mul(x.z, pvm, m), m.q) + d.z, m.q),
-                           csub(csub(mont_mul(x.w, pvm, m), m.q) + d.w, m.q));
-    }
-  }
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) st4(out + n0 + 64 * kk, res[kk]);
 }
 
 // ============================================================================
@@ -1576,97 +1660,66 @@ hipError_t ks_modup_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& 
 template <int L1>
 hipError_t ks_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, const JobArg<KsJob>& jobs,
                        int njobs, int Lmax, bool with_modup, bool with_hoist, hipStream_t st,
-                       const KsSplit& sp) {
-  const int Rmax = Lmax + c.k;
+                       bool whole_limb) {
   const int tiles = c.N / kTile;
   hipError_t e;
   if constexpr (L1 + kBlockLog == kSrLog) {
     // small ring: two kernels on whole limbs (plain, HMult and HRot jobs)
-    if ((sc.ntt_shape & kShapeWholeLimb) && with_modup && !with_hoist && !sp.side) {
+    if ((sc.ntt_shape & kShapeWholeLimb) && with_modup && !with_hoist && whole_limb) {
       // every job splits its own digits into sr_groups(beta) <= min(beta, kSrGroups)
       // groups, so the grid covers min(bmax, kSrGroups) (not the largest job's count)
       const int groups = std::min(c.beta(Lmax), kSrGroups);
-      klaunch_b(c, CKKS_STAGE_NTT_IP, s1_modup_ip, dim3(Rmax, groups, njobs), kSrT, st, K, jobs);
+      klaunch_b(c, CKKS_STAGE_NTT_IP, s1_modup_ip, dim3(Lmax + c.k, groups, njobs), kSrT, st, K, jobs);
       klaunch_b(c, CKKS_STAGE_NTT_COMBINE, s2_moddown, dim3(Lmax, 2, njobs), kSrT, st, K, jobs);
       return hipGetLastError();
     }
   }
   if (with_modup && (e = modup_stage_t<L1>(c, sc, K, jobs, njobs, Lmax, st)) != hipSuccess) return e;
-  // Stage 2.  With a side stream, complementary pipelining (Sec. IV-B): the
-  // inner product of the P rows runs on st and ModDown's P-row chain (K6..K8,
-  // latency-bound) follows it there, while the Q-row inner product (key
-  // streaming, HBM-heavy) runs on the side stream; K9 joins both.
-  auto k5 = [&](int stage, int part, hipStream_t s5, int rows) {
-    const dim3 g5(tiles, rows, njobs);
+  // Stage 2 on the P rows, ModDown's column stages, stage 2 on the Q rows with
+  // the combine.
+  auto k5 = [&](auto q, int stage, int rows) {
+    constexpr bool Q = decltype(q)::value;
+    const dim3 g5(tiles, rows, njobs), g4(4 * tiles, rows, njobs);
     const int nb = std::max(c.beta(Lmax), 2);  // slots for the launch's own largest digit count
-    if (tiles * rows * njobs <= sc.small_grid && nb <= 4) {  // too few work-groups to fill the CUs
-      const dim3 g4(4 * tiles, rows, njobs);
-      switch (nb) {
-        case 2: klaunch_b(c, stage, k5p_ntt_blks_ip<2>, g4, 128, s5, K, jobs, part); break;
-        case 3: klaunch_b(c, stage, k5p_ntt_blks_ip<3>, g4, 192, s5, K, jobs, part); break;
-        default: klaunch_b(c, stage, k5p_ntt_blks_ip<4>, g4, 256, s5, K, jobs, part); break;
-      }
-      return;
-    }
     // a single job streams its key (measured: K5 39.8 -> 35.6 us at N = 2^16,
     // L = 36, alternating keys); jobs of a batch may share one
     const bool nt = njobs == 1;
+    auto of = [&](auto n) {
+      constexpr int NB = decltype(n)::value;
+      if (tiles * rows * njobs <= sc.small_grid)  // too few work-groups to fill the CUs
+        klaunch_b(c, stage, k5p_ntt_blks_ip<NB, Q>, g4, 64 * NB, st, K, jobs);
+      else if (nt)
+        klaunch(c, stage, k5s_ntt_blks_ip<NB, true, Q>, g5, st, K, jobs);
+      else
+        klaunch(c, stage, k5s_ntt_blks_ip<NB, false, Q>, g5, st, K, jobs);
+    };
     switch (nb) {
-      case 2:
-        if (nt) klaunch(c, stage, k5s_ntt_blks_ip<2, true>, g5, s5, K, jobs, part);
-        else klaunch(c, stage, k5s_ntt_blks_ip<2, false>, g5, s5, K, jobs, part);
-        break;
-      case 3:
-        if (nt) klaunch(c, stage, k5s_ntt_blks_ip<3, true>, g5, s5, K, jobs, part);
-        else klaunch(c, stage, k5s_ntt_blks_ip<3, false>, g5, s5, K, jobs, part);
-        break;
-      case 4:
-        if (nt) klaunch(c, stage, k5s_ntt_blks_ip<4, true>, g5, s5, K, jobs, part);
-        else klaunch(c, stage, k5s_ntt_blks_ip<4, false>, g5, s5, K, jobs, part);
-        break;
-      default: klaunch(c, stage, k5_ntt_blks_ip<false>, g5, s5, K, jobs, part); break;
+      case 2: of(std::integral_constant<int, 2>()); break;
+      case 3: of(std::integral_constant<int, 3>()); break;
+      case 4: of(std::integral_constant<int, 4>()); break;
+      default: klaunch(c, stage, k5_ntt_blks_ip<false, Q>, g5, st, K, jobs); break;
     }
   };
-  auto k5h = [&](int stage, int part, hipStream_t s5, int rows) {
+  auto k5h = [&](auto q, int stage, int rows) {
+    constexpr bool Q = decltype(q)::value;
     const dim3 gh(tiles, rows, njobs);
     switch (std::max(c.beta(Lmax), 2)) {  // slots for the launch's own largest digit count
-      case 2: klaunch(c, stage, k5h_gather_ip<2>, gh, s5, K, jobs, part); break;
-      case 3: klaunch(c, stage, k5h_gather_ip<3>, gh, s5, K, jobs, part); break;
-      case 4: klaunch(c, stage, k5h_gather_ip<4>, gh, s5, K, jobs, part); break;
-      default: klaunch(c, stage, k5_ntt_blks_ip<true>, gh, s5, K, jobs, part); break;
+      case 2: klaunch(c, stage, k5h_gather_ip<2, Q>, gh, st, K, jobs); break;
+      case 3: klaunch(c, stage, k5h_gather_ip<3, Q>, gh, st, K, jobs); break;
+      case 4: klaunch(c, stage, k5h_gather_ip<4, Q>, gh, st, K, jobs); break;
+      default: klaunch(c, stage, k5_ntt_blks_ip<true, Q>, gh, st, K, jobs); break;
     }
   };
-  const bool split = sp.side != nullptr;
-  auto fork = [&]() -> hipError_t {
-    hipError_t fe = hipEventRecord(sp.fork, st);
-    return fe != hipSuccess ? fe : hipStreamWaitEvent(sp.side, sp.fork, 0);
-  };
-  auto part_q = [&]() {
-    if (with_modup) k5(CKKS_STAGE_NTT_IP, KS_PART_Q, sp.side, Lmax);
-    if (with_hoist) k5h(CKKS_STAGE_NTT_IP, KS_PART_Q, sp.side, Lmax);
-  };
-  if (split) {
-    if (!sp.p_first) {
-      if ((e = fork()) != hipSuccess) return e;
-      part_q();
-    }
-    if (with_modup) k5(CKKS_STAGE_NTT_IP_P, KS_PART_P, st, c.k);
-    if (with_hoist) k5h(CKKS_STAGE_NTT_IP_P, KS_PART_P, st, c.k);
-    if (sp.p_first) {
-      if ((e = fork()) != hipSuccess) return e;
-      part_q();
-    }
-  } else {
-    if (with_modup) k5(CKKS_STAGE_NTT_IP, KS_PART_ALL, st, Rmax);
-    if (with_hoist) k5h(CKKS_STAGE_NTT_IP, KS_PART_ALL, st, Rmax);
-  }
-  if (split && (e = hipEventRecord(sp.join, sp.side)) != hipSuccess) return e;
+  if (with_modup) k5(std::false_type(), CKKS_STAGE_NTT_IP_P, c.k);
+  if (with_hoist) k5h(std::false_type(), CKKS_STAGE_NTT_IP_P, c.k);
   const int groups = conv_groups((long)(c.N / 512) * 2 * njobs, Lmax, sc.down_rows);
   e = conv_launch<L1, CONV_DOWN>(c, CKKS_STAGE_INTT_COLS_P, c.k, dim3(c.N / 512, 2 * groups, njobs), st, K, jobs,
                                  groups);
   if (e != hipSuccess) return e;
-  if (split && (e = hipStreamWaitEvent(st, sp.join, 0)) != hipSuccess) return e;
-  klaunch(c, CKKS_STAGE_NTT_COMBINE, k9_ntt_blks_combine, dim3(tiles, 2 * Lmax, njobs), st, K, jobs);
+  // one kernel under two names
+  const int stage_q = c.trace.stage == CKKS_STAGE_NTT_COMBINE ? CKKS_STAGE_NTT_COMBINE : CKKS_STAGE_NTT_IP;
+  if (with_modup) k5(std::true_type(), stage_q, Lmax);
+  if (with_hoist) k5h(std::true_type(), stage_q, Lmax);
   return hipGetLastError();
 }
 
@@ -1687,15 +1740,15 @@ hipError_t rs_launch_t(const Ctx& c, const KsConst& K, const JobArg<RsJob>& jobs
 }  // namespace
 
 hipError_t ks_launch(const Ctx& c, const Ctx::Sched& sc, const JobArg<KsJob>& jobs, int njobs, int Lmax,
-                     bool with_modup, bool with_hoist, hipStream_t st, const KsSplit& sp) {
+                     bool with_modup, bool with_hoist, hipStream_t st, bool whole_limb) {
   if (njobs <= 0) return hipSuccess;
   const KsConst K = make_const(c);
   switch (c.logN - kBlockLog) {
-    case 4: return ks_launch_t<4>(c, sc, K, jobs, njobs, Lmax, with_modup, with_hoist, st, sp);
-    case 5: return ks_launch_t<5>(c, sc, K, jobs, njobs, Lmax, with_modup, with_hoist, st, sp);
-    case 6: return ks_launch_t<6>(c, sc, K, jobs, njobs, Lmax, with_modup, with_hoist, st, sp);
-    case 7: return ks_launch_t<7>(c, sc, K, jobs, njobs, Lmax, with_modup, with_hoist, st, sp);
-    case 8: return ks_launch_t<8>(c, sc, K, jobs, njobs, Lmax, with_modup, with_hoist, st, sp);
+    case 4: return ks_launch_t<4>(c, sc, K, jobs, njobs, Lmax, with_modup, with_hoist, st, whole_limb);
+    case 5: return ks_launch_t<5>(c, sc, K, jobs, njobs, Lmax, with_modup, with_hoist, st, whole_limb);
+    case 6: return ks_launch_t<6>(c, sc, K, jobs, njobs, Lmax, with_modup, with_hoist, st, whole_limb);
+    case 7: return ks_launch_t<7>(c, sc, K, jobs, njobs, Lmax, with_modup, with_hoist, st, whole_limb);
+    case 8: return ks_launch_t<8>(c, sc, K, jobs, njobs, Lmax, with_modup, with_hoist, st, whole_limb);
     default: return hipErrorInvalidValue;
   }
 }
