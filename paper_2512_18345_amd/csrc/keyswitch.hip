@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kWG) void k1_intt_blks(KsConst K, JobArg<KsJob> JA)
   const uint32_t n0 = base + line * 256 + 4 * (lane & 15);
   // the switched polynomial in the evaluation domain, kept for K5's digit
   // rows (a ModUp-only job keeps it as the digit row of its output M)
-  uint32_t* de = J.kind == KS_MODUP ? V.z + ((size_t)(r / K.alpha) * V.R + r) * N : V.de + (size_t)r * N;
+  const OutRow de(J.kind == KS_MODUP ? V.z + ((size_t)(r / K.alpha) * V.R + r) * N : V.de + (size_t)r * N);
   // all loads first: a store to de could alias the next quad's source
   BlkTw tw;
   uint4 d[4];
@@ -187,17 +187,17 @@ __global__ __launch_bounds__(kWG) void k1_intt_blks(KsConst K, JobArg<KsJob> JA)
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     blk_quad_store(s, line, 4 * (lane & 15) + 64 * kk, d[kk]);
-    if (J.kind != KS_PLAIN) st4(de + n0 + 64 * kk, d[kk]);  // HMULT, HROT, MODUP
+    if (J.kind != KS_PLAIN) de.st4(n0 + 64 * kk, d[kk]);  // HMULT, HROT, MODUP
   }
   wave_sync();
   blk_inv_a(s, line, lane, tw, m);
   wave_sync();
   blk_inv_b(s, line, lane, tw, m);
   __syncthreads();
-  uint32_t* y = V.y + (size_t)r * N + base;
+  const OutRow y(V.y + (size_t)r * N + base);
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk)
-    st4(y + RowGroup<16>::word(threadIdx.x, kk, 0), RowGroup<16>::from_lds(s, threadIdx.x, kk));
+    y.st4(RowGroup<16>::word(threadIdx.x, kk, 0), RowGroup<16>::from_lds(s, threadIdx.x, kk));
 }
 
 // Column stages of a base conversion, one work-group per (column tile, group
@@ -283,6 +283,7 @@ __global__ __launch_bounds__(64 * kConvWaves, 4) void kc_conv(KsConst K, JobArg<
   }
   __syncthreads();
 
+  const OutRow out(MODE == CONV_UP ? V.z + (size_t)jd * V.R * N : V.w + (size_t)jd * V.L * N);
   for (int u = 2 * w; u < o1 - o0;) {
     const int o = min(o0 + u + half, o1 - 1);
     const int r = row_of(o);
@@ -321,8 +322,7 @@ __global__ __launch_bounds__(64 * kConvWaves, 4) void kc_conv(KsConst K, JobArg<
       v[k] = hi + m.q - __umulhi((uint32_t)a[k] * (0u - m.qn), m.q);
     }
     CH::forward(v, x, tw, m, n);
-    uint32_t* dst = MODE == CONV_UP ? V.z + ((size_t)jd * V.R + r) * N : V.w + ((size_t)jd * V.L + r) * N;
-    CH::store(v, x, dst, tile, n, half == 0 || u + 1 < o1 - o0);
+    CH::store(v, x, out, (uint32_t)r << K.T.logN, tile, n, half == 0 || u + 1 < o1 - o0);
     u = __builtin_amdgcn_readfirstlane(un);
   }
 }
@@ -348,6 +348,7 @@ __global__ __launch_bounds__(kWG) void km_ntt_blks(KsConst K, JobArg<KsJob> JA) 
   const int line = blk_line<16>(lane, w);
   uint32_t* row = V.z + (size_t)gr * N + blockIdx.x * kTile;
   BlkTw tw;
+  const OutRow out(row);
   uint4 raw[4];
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) raw[kk] = ld4(row + RowGroup<16>::word(threadIdx.x, kk, 0));
@@ -362,7 +363,7 @@ __global__ __launch_bounds__(kWG) void km_ntt_blks(KsConst K, JobArg<KsJob> JA) 
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     const int pos = 4 * (lane & 15) + 64 * kk;
-    st4(row + line * 256 + pos, canon4(blk_quad(s, line, pos), m.q, m.q2));
+    out.st4(line * 256 + pos, canon4(blk_quad(s, line, pos), m.q, m.q2));
   }
 }
 
@@ -393,12 +394,13 @@ __device__ __forceinline__ void p_rows_intt(uint32_t* s, const KsConst& K, int p
   wave_sync();
   blk_inv_b(s, line, lane, tw, m);
   blk_inv_b(s + kBlkTile, line, lane, tw, m);
+  const OutRow o0(acc0), o1(acc1);
   __syncthreads();
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     const int at = RowGroup<16>::word(threadIdx.x, kk, 0);
-    st4(acc0 + at, RowGroup<16>::from_lds(s, threadIdx.x, kk));
-    st4(acc1 + at, RowGroup<16>::from_lds(s + kBlkTile, threadIdx.x, kk));
+    o0.st4(at, RowGroup<16>::from_lds(s, threadIdx.x, kk));
+    o1.st4(at, RowGroup<16>::from_lds(s + kBlkTile, threadIdx.x, kk));
   }
 }
 
@@ -461,8 +463,7 @@ __device__ __forceinline__ void combine_quad(const KsConst& K, const KsJob& J, i
     return make_uint4(a.x + m.q2 - w.x, a.y + m.q2 - w.y, a.z + m.q2 - w.z, a.w + m.q2 - w.w);
   };
   const uint4 x0 = diff(a0, w0), x1 = diff(a1, w1);
-  uint32_t* out0 = J.out + (size_t)i * N + n;
-  uint32_t* out1 = out0 + (size_t)L * N;
+  const OutRow out0(J.out + (size_t)i * N), out1(J.out + ((size_t)L + i) * N);
   if (!HOIST && J.kind == KS_HMULT) {
     const uint32_t pv = ldc(K.pinv + i).x;
     uint64_t t0[4] = {(uint64_t)x0.x * pv, (uint64_t)x0.y * pv, (uint64_t)x0.z * pv, (uint64_t)x0.w * pv};
@@ -470,8 +471,8 @@ __device__ __forceinline__ void combine_quad(const KsConst& K, const KsJob& J, i
     mac4(t0, t.a, t.b);
     mac4(t1, t.a, t.d);
     mac4(t1, t.c, t.b);
-    st4(out0, reduce4(t0, mc));
-    st4(out1, reduce4(t1, mc));
+    out0.st4(n, reduce4(t0, mc));
+    out1.st4(n, reduce4(t1, mc));
     return;
   }
   const uint32_t pv = ldc(K.M.pinv + i);
@@ -484,8 +485,8 @@ __device__ __forceinline__ void combine_quad(const KsConst& K, const KsJob& J, i
     const uint4 e = auto_turn(t.a, t.aq);
     o0 = make_uint4(csub(o0.x + e.x, m.q), csub(o0.y + e.y, m.q), csub(o0.z + e.z, m.q), csub(o0.w + e.w, m.q));
   }
-  st4(out0, o0);
-  st4(out1, scale(x1));
+  out0.st4(n, o0);
+  out1.st4(n, scale(x1));
 }
 
 // Q rows: ModDown's combine on the inner product where it stands, in the
@@ -1012,9 +1013,9 @@ __global__ __launch_bounds__(64 * NB) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJ
     wave_sync();
     blk_inv_b(slot, line, lane, itw, m);
     wave_sync();
-    uint32_t* dst = (j ? acc1 : acc0) + group;
+    const OutRow dst((j ? acc1 : acc0) + group);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) st4(dst + RowGroup<4>::word(lane, kk, a4), RowGroup<4>::from_lds(slot, lane, kk));
+    for (int kk = 0; kk < 4; ++kk) dst.st4(RowGroup<4>::word(lane, kk, a4), RowGroup<4>::from_lds(slot, lane, kk));
   }
 }
 

@@ -201,8 +201,8 @@ struct ColHalf {
   // instructions would send four times the write requests to L2.  The quads
   // change lanes through the half's exchange words, rotated by n / 4 so that 16
   // lanes meet no bank twice.
-  __device__ static __forceinline__ void store(const uint32_t v[16], uint32_t* x, uint32_t* row, int t, int n,
-                                               bool on) {
+  __device__ static __forceinline__ void store(const uint32_t v[16], uint32_t* x, const OutRow& out, uint32_t row,
+                                               int t, int n, bool on) {
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       *reinterpret_cast<uint4*>(x + 16 * n + 4 * ((k + (n >> 2)) & 3)) =
@@ -216,7 +216,7 @@ struct ColHalf {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int owner = 8 * k + (n >> 2);
-      st4(row + lane_word(t, owner) + 4 * (((n & 3) - (owner >> 2)) & 3), q[k]);
+      out.st4(row + lane_word(t, owner) + 4 * (((n & 3) - (owner >> 2)) & 3), q[k]);
     }
   }
 };

@@ -45,7 +45,8 @@ def test_column_kernels_at_every_digit_size(logN, alpha):
 
 @pytest.mark.parametrize("name,L", [("n12_l4", 4), ("toy_n12", 5), ("n16_l36", 13)])
 def test_rotations_of_a_ciphertext_at_a_four_byte_offset(name, L):
-    """The automorphism reads 16-byte quads; ciphertexts need only be 4-byte aligned."""
+    """The automorphism reads and the outputs are written as 16-byte quads;
+    ciphertexts need only be 4-byte aligned."""
     spec = ci.get(name)
     par, ctx, rng = O.Params.from_spec(spec), P.Context.from_spec(spec), ci.Rng(77)
     h, N = ctx.handle, spec.N
@@ -54,8 +55,8 @@ def test_rotations_of_a_ciphertext_at_a_four_byte_offset(name, L):
     shifted = room[1:].view(2, L, N)
     shifted.copy_(dev(ct))
     assert shifted.data_ptr() % 16 == 4
+    out = torch.empty(1 + ct.size, dtype=torch.int32, device="cuda")[1:].view(2, L, N)
     for rot in (0, 1, 2, 3, N // 2 - 1):
-        out = empty(2, L, N)
         P.ckks_hrot(h, shifted, L, rot, dev(key), out, ctx.workspace("HROT", L))
         msg = first_mismatch(host(out), O.hrot(par, ct, L, rot, key))
         assert not msg, f"hrot by {rot}: {msg}"
