@@ -293,12 +293,8 @@ int ckks_rescale(const ckks_ctx *ctx, const uint32_t *ct, int L, uint32_t *out, 
  *                    work-groups use one thread group per digit tile
  *                    (0: never)
  *   ntt_shape        NTT tile / radix choices (Sec. III-C1 NTT kernels),
- *                    a bit mask: 1 = the rescale's forward column pass with
- *                    8 elements per thread in radix-8 phases (else 16,
- *                    radix-16); 2 = its inverse column pass with 16 elements
- *                    per thread in radix-16 phases (else 8, radix-8); 4 =
- *                    accepted, without effect (the ModUp INTT block pass has
- *                    one shape); 8 = at N = 2^12, the whole key-switch as two
+ *                    a bit mask: 1, 2 and 4 are accepted, without effect
+ *                    (every transform pass has one shape); 8 = at N = 2^12, the whole key-switch as two
  *                    kernels that hold whole limbs in LDS (ModUp + inner
  *                    product per row and digit group, ModDown + epilogue per
  *                    output row) instead of the five-kernel pipeline (hoisted
@@ -337,7 +333,7 @@ int ckks_ctx_tune(ckks_ctx *ctx, int L, int reps, void *stream, ckks_schedule *b
  * Batches (Sec. IV-A batching; Sec. IV-C one submission per static graph).
  * A batch is a fixed list of independent jobs, each at its own level, run
  * together: every pipeline kernel covers all jobs of a launch group at once
- * (five kernels for the key-switching jobs of a group, four for all rescale
+ * (five kernels for the key-switching jobs of a group, three for all rescale
  * jobs; groups as in ckks_batch_plan below), and with use_graph != 0 the
  * whole launch sequence is captured once into a hipGraph at creation, so
  * ckks_batch_launch is a single graph submission.

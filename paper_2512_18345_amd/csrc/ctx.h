@@ -148,7 +148,7 @@ struct Ctx {
   // (2, 4, 6 or 12), and the largest inner-product grid that uses one thread
   // group per digit (0: never).  Results do not depend on it.
   // Kernel schedule: launch shapes only, results are bitwise the same under
-  // every schedule.  ntt_shape bits (kShape*): NTT tile and radix choices.
+  // every schedule.  ntt_shape bits: kShapeWholeLimb (keyswitch.h).
   struct Sched {
     int up_rows = 12, down_rows = 6, small_grid = 128, ntt_shape = 0;
   };

@@ -44,10 +44,7 @@ struct __align__(16) RsJob {
 
 constexpr int kInlineJobs = 16;
 
-// NTT shape bits of Ctx::Sched::ntt_shape (small grids keep their own shapes):
-constexpr int kShapeFwdRadix8 = 1;   // rescale's forward column pass: 8 elements / thread, radix-8 phases (else 16, radix-16)
-constexpr int kShapeInvRadix16 = 2;  // rescale's inverse column pass: 16 elements / thread, radix-16 phases (else 8, radix-8)
-// 4: accepted, without effect
+// Bits of Ctx::Sched::ntt_shape: 1, 2 and 4 are accepted, without effect.
 constexpr int kShapeWholeLimb = 8;   // N = 2^kSrLog: two kernels with whole limbs in LDS instead of five
 constexpr int kShapeAll = 15;
 constexpr int kSrGroups = 4;  // whole-limb key-switch: digit groups of its first kernel, at most

@@ -24,7 +24,7 @@
 //
 // Every launch covers all jobs (grid.z) and all rows of a stage, which is
 // what gives small levels enough work-groups (the batching argument of
-// Sec. IV-A).  Rescale has its own four kernels (R1..R4).
+// Sec. IV-A).  Rescale has its own three kernels (R1, R2, R4).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -35,7 +35,6 @@
 #include "ctx.h"
 #include "keyswitch.h"
 #include "mont_ntt.h"
-#include "ntt_tile.h"
 
 namespace ckks {
 
@@ -1021,154 +1020,139 @@ __global__ __launch_bounds__(64 * NB) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJ
 
 // ============================================================================
 // Rescale: t = INTT_{q_{L-1}}(a_{L-1}); out_i = (a_i - NTT_{q_i}(t mod q_i)) q_{L-1}^-1
-// Scratch: t [2][N], u [2][L-1][N].
+// Scratch, in the row-group layout: t [2][N] after the block pass, u [2][L-1][N]
+// after the column pass.
 // ============================================================================
-// BPW blocks per work-group as in K1 (4: quarter tiles in radix-4 phases).
-template <int LOGN1, int BPW>
 __global__ __launch_bounds__(kWG) void r1_intt_blks(KsConst K, JobArg<RsJob> JA) {
   const RsJob J = JA.get(blockIdx.z);
-  const int c = blockIdx.y, L = J.L, pi = L - 1;
-  __shared__ uint2 stw[256];
-  const uint2 tww = tw_fetch(K.T.blk_itw(pi), 256);
-  __shared__ __align__(16) uint32_t s[kLds];
-  const size_t N = (size_t)1 << K.T.logN;
-  const uint32_t q = ldc(K.T.mod + pi).q, q2 = 2 * q;
-  constexpr int QPT = BPW / 4;  // quads per thread
-  const int blk0 = blockIdx.x * BPW;
-  const uint32_t* in = J.a + ((size_t)c * L + pi) * N + blk0 * 256;
-  uint32_t* t = J.ws + (size_t)c * N + blk0 * 256;
-  uint4 x[QPT];
-  Twist4 tfi[QPT];  // the epilogue's twist factors, requested with the tile
-#pragma unroll
-  for (int kk = 0; kk < QPT; ++kk) x[kk] = ld4(in + blk_elem(kk));
-#pragma unroll
-  for (int kk = 0; kk < QPT; ++kk) {
-    const int e = blk_elem(kk);
-    tfi[kk] = twist4_load(K.T.blk_itwist(pi, blk0 + (e >> 8)), e & 255);
-  }
-#pragma unroll
-  for (int kk = 0; kk < QPT; ++kk) lds_blk4_store(s, blk_elem(kk), x[kk]);
-  if constexpr (BPW == 16)
-    tw_put_perm(stw, tww);
-  else
-    tw_put(stw, tww, 256);
-  __syncthreads();
-  if constexpr (BPW == 16)
-    blk_stages<true>(s, PermTw{stw}, q, q2);
-  else
-    blk_stages_r4<true, const uint2*, kWG>(s, stw, q, q2);
-  __syncthreads();
-#pragma unroll
-  for (int kk = 0; kk < QPT; ++kk) st4(t + blk_elem(kk), twist4(lds_blk4(s, blk_elem(kk)), tfi[kk], q));
-}
-
-template <int LOGN1, int CW, int T>
-__global__ __launch_bounds__(T) void r2_intt_cols(KsConst K, JobArg<RsJob> JA) {
-  const RsJob J = JA.get(blockIdx.z);
   const int c = blockIdx.y, pi = J.L - 1;
-  __shared__ uint2 stw[ColGeom<LOGN1, CW, T>::N1];
-  const uint2 tww = tw_fetch(K.T.col_itw(pi), ColGeom<LOGN1, CW, T>::N1);
-  __shared__ __align__(16) uint32_t s[ColGeom<LOGN1, CW, T>::LDS];
-  constexpr int C = ColGeom<LOGN1, CW, T>::C;
+  __shared__ __align__(16) uint32_t s[kBlkTile];
   const size_t N = (size_t)1 << K.T.logN;
-  const ModC m = ldc(K.T.mod + pi);
-  const uint32_t q = m.q, q2 = 2 * q;
-  const int col0 = blockIdx.x * C;
-  uint32_t* row = J.ws + (size_t)c * N;
-  load_cols<LOGN1, CW, T>(s, row, col0);
-  tw_put(stw, tww, ColGeom<LOGN1, CW, T>::N1);
-  __syncthreads();
-  col_stages<LOGN1, true, CW, T>(s, stw, q, q2);
-  __syncthreads();
+  const MontQ m = mont_q(ldc(K.T.mod + pi));
+  const uint32_t base = blockIdx.x * kTile;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  const uint32_t* in = J.a + ((size_t)c * J.L + pi) * N + base + line * 256 + 4 * (lane & 15);
+  uint4 x[4];
+  BlkTw tw;
 #pragma unroll
-  for (int kk = 0; kk < ColGeom<LOGN1, CW, T>::QUADS; ++kk) {
-    const int lin = (threadIdx.x + kk * T) * 4;
-    const int pos = lin / C, cc = lin & (C - 1);
-    uint4 v = *reinterpret_cast<const uint4*>(s + lidx_col(pos, cc, C));
-    v.x = csub(mul_shoup(v.x, m.ninv, m.ninv_s, q), q);
-    v.y = csub(mul_shoup(v.y, m.ninv, m.ninv_s, q), q);
-    v.z = csub(mul_shoup(v.z, m.ninv, m.ninv_s, q), q);
-    v.w = csub(mul_shoup(v.w, m.ninv, m.ninv_s, q), q);
-    st4(row + pos * 256 + col0 + cc, v);
-  }
+  for (int kk = 0; kk < 4; ++kk) x[kk] = ld4(in + 64 * kk);
+  tw.load(K.M.row_itw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_itw(pi), lane);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) blk_quad_store(s, line, 4 * (lane & 15) + 64 * kk, x[kk]);
+  wave_sync();
+  blk_inv_a(s, line, lane, tw, m);
+  wave_sync();
+  blk_inv_b(s, line, lane, tw, m);
+  __syncthreads();
+  const OutRow t(J.ws + (size_t)c * N + base);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+    t.st4(RowGroup<16>::word(threadIdx.x, kk, 0), RowGroup<16>::from_lds(s, threadIdx.x, kk));
 }
 
-// NTT column pass of t mod q_i for every i < L - 1 (the broadcast is the loader).
-template <int LOGN1, int CW, int T>
-__global__ __launch_bounds__(T) void r3_ntt_cols(KsConst K, JobArg<RsJob> JA) {
-  const RsJob J = JA.get(blockIdx.z);
-  const int L1 = J.L - 1;
-  const int gr = blockIdx.y;
-  if (gr >= 2 * L1) return;
-  const int c = gr / L1, i = gr % L1;
-  __shared__ uint2 stw[ColGeom<LOGN1, CW, T>::N1];
-  const uint2 tww = tw_fetch(K.T.col_tw(i), ColGeom<LOGN1, CW, T>::N1);
-  __shared__ __align__(16) uint32_t s[ColGeom<LOGN1, CW, T>::LDS];
-  constexpr int C = ColGeom<LOGN1, CW, T>::C;
-  const size_t N = (size_t)1 << K.T.logN;
-  const ModC m = ldc(K.T.mod + i);
-  const uint32_t q = m.q, q2 = 2 * q;
-  const int col0 = blockIdx.x * C;
-  const uint32_t* t = J.ws + (size_t)c * N;
-#pragma unroll
-  for (int kk = 0; kk < ColGeom<LOGN1, CW, T>::QUADS; ++kk) {
-    const int lin = (threadIdx.x + kk * T) * 4;
-    const int pos = lin / C, cc = lin & (C - 1);
-    uint4 v = ld4(t + pos * 256 + col0 + cc);
-    v.x = reduce32(v.x, q, m.mu32);
-    v.y = reduce32(v.y, q, m.mu32);
-    v.z = reduce32(v.z, q, m.mu32);
-    v.w = reduce32(v.w, q, m.mu32);
-    *reinterpret_cast<uint4*>(s + lidx_col(pos, cc, C)) = v;
-  }
-  tw_put(stw, tww, ColGeom<LOGN1, CW, T>::N1);
-  __syncthreads();
-  col_stages<LOGN1, false, CW, T>(s, stw, q, q2);
-  __syncthreads();
-  store_cols<LOGN1, CW, T>(s, J.ws + (size_t)(2 + gr) * N, col0);
-}
-
+// The column stages of a component, as in kc_conv with one input limb: its INTT
+// column pass and N^-1 by the first wave, then t mod q_i and its NTT column pass
+// for the group's rows, a pair of rows a wave at a time.  One launch for what
+// were two (4.9 + 14.2 -> 12.8 us at N = 2^16, L = 36).
 template <int LOGN1>
+__global__ __launch_bounds__(64 * kConvWaves, 4) void r2_cols(KsConst K, JobArg<RsJob> JA, int groups) {
+  using CH = ColHalf<LOGN1>;
+  const RsJob J = JA.get(blockIdx.z);
+  const size_t N = (size_t)1 << K.T.logN;
+  const int tile = blockIdx.x, L1 = J.L - 1;
+  const int c = blockIdx.y / groups, g = blockIdx.y % groups;
+  const int per = (L1 + groups - 1) / groups;
+  const int o0 = g * per, o1 = min(o0 + per, L1);
+  if (o0 >= o1) return;
+  __shared__ __align__(16) uint32_t y[512];
+  __shared__ __align__(16) uint32_t xch[kConvWaves * 2 * CH::XCH];
+  __shared__ int next;
+  const int lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t* x = xch + (2 * w + half) * CH::XCH;
+  if (w == 0) {  // both halves, the same words
+    if (lane == 0) next = 2 * kConvWaves;
+    uint32_t v[16];
+    typename CH::Tw tw;
+    CH::load(v, J.ws + (size_t)c * N, tile, n);
+    tw.load(K.M.col_itw(K.T, L1), n);
+    const ModC mc = ldc(K.T.mod + L1);
+    const MontQ m = mont_q(mc);
+    CH::inverse(v, x, tw, m, n);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = csub(mul_shoup(v[k], mc.ninv, mc.ninv_s, m.q), m.q);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      *reinterpret_cast<uint4*>(y + k * 128 + n * 4) = make_uint4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+  }
+  __syncthreads();
+  const OutRow out(J.ws + (size_t)(2 + c * L1) * N);
+  for (int u = 2 * w; u < o1 - o0;) {
+    const int i = min(o0 + u + half, o1 - 1);
+    typename CH::Tw tw;
+    tw.load(K.M.col_tw(K.T, i), n);
+    const MontQ m = mont_q_load(K.T.mod + i);
+    const uint32_t mu32 = ld1(reinterpret_cast<const uint32_t*>(K.T.mod + i) + offsetof(ModC, mu32) / 4);
+    int un = 0;
+    if (lane == 0) un = atomicAdd(&next, 2);
+    uint32_t v[16];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint4 q = *reinterpret_cast<const uint4*>(y + k * 128 + n * 4);
+      v[4 * k] = reduce32(q.x, m.q, mu32);
+      v[4 * k + 1] = reduce32(q.y, m.q, mu32);
+      v[4 * k + 2] = reduce32(q.z, m.q, mu32);
+      v[4 * k + 3] = reduce32(q.w, m.q, mu32);
+    }
+    CH::forward(v, x, tw, m, n);
+    CH::store(v, x, out, (uint32_t)i << K.T.logN, tile, n, half == 0 || u + 1 < o1 - o0);
+    u = __builtin_amdgcn_readfirstlane(un);
+  }
+}
+
+// Bound: memory (a, u in, out: 55 MB at N = 2^16, L = 36).
 __global__ __launch_bounds__(kWG) void r4_ntt_blks_combine(KsConst K, JobArg<RsJob> JA) {
   const RsJob J = JA.get(blockIdx.z);
   const int L1 = J.L - 1;
   const int gr = blockIdx.y;
   if (gr >= 2 * L1) return;
   const int c = gr / L1, i = gr % L1;
-  __shared__ uint2 stw[256];
-  const uint2 tww = tw_fetch(K.T.blk_tw(i), 256);
-  __shared__ __align__(16) uint32_t s[kLds];
+  __shared__ __align__(16) uint32_t s[kBlkTile];
   const size_t N = (size_t)1 << K.T.logN;
-  const uint32_t q = ldc(K.T.mod + i).q, q2 = 2 * q;
-  const int blk0 = blockIdx.x * 16;
-  const uint32_t base = blk0 * 256;
+  const MontQ m = mont_q(ldc(K.T.mod + i));
+  const uint32_t base = blockIdx.x * kTile;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  const uint32_t n0 = base + line * 256 + 4 * (lane & 15);
   const uint32_t* u = J.ws + (size_t)(2 + gr) * N + base;
+  const uint32_t* a = J.a + ((size_t)c * J.L + i) * N + n0;
+  uint4 raw[4], xs[4];
+  BlkTw tw;
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
-    lds_blk4_store(s, e, twist4(ld4(u + e),
-                                K.T.blk_twist(i, blk0 + (e >> 8)), e & 255, q));
-  }
-  tw_put_perm(stw, tww);
+  for (int kk = 0; kk < 4; ++kk) raw[kk] = ld4(u + RowGroup<16>::word(threadIdx.x, kk, 0));
+  tw.load(K.M.row_tw(K.T, i, blockIdx.x * 16 + line), K.M.blk_tw(i), lane);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) xs[kk] = ld4(a + 64 * kk);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) RowGroup<16>::to_lds(s, threadIdx.x, kk, raw[kk]);
   __syncthreads();
-  blk_stages<false>(s, PermTw{stw}, q, q2);
-  __syncthreads();
+  blk_fwd_a(s, line, lane, tw, m);
+  wave_sync();
+  blk_fwd_b(s, line, lane, tw, m);
+  wave_sync();
   const uint2 qi = ldc(K.rescale_inv + (size_t)J.L * K.T.L_max + i);
-  const uint32_t* a = J.a + ((size_t)c * J.L + i) * N + base;
-  uint32_t* out = J.out + ((size_t)c * L1 + i) * N + base;
-  uint4 xs[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) xs[kk] = ld4(a + blk_elem(kk));
+  const OutRow out(J.out + ((size_t)c * L1 + i) * N);
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
-    const int e = blk_elem(kk);
-    const uint4 v = csub4(lds_blk4(s, e), q2);  // [0, 2q): x + 2q - v < 3q
+    const uint4 v = csub4(blk_quad(s, line, 4 * (lane & 15) + 64 * kk), m.q2);  // [0, 2q): x + 2q - v < 3q
     const uint4 x = xs[kk];
-    st4(out + e, make_uint4(csub(mul_shoup(x.x + q2 - v.x, qi.x, qi.y, q), q), csub(mul_shoup(x.y + q2 - v.y, qi.x, qi.y, q), q),
-                   csub(mul_shoup(x.z + q2 - v.z, qi.x, qi.y, q), q), csub(mul_shoup(x.w + q2 - v.w, qi.x, qi.y, q), q)));
+    out.st4(n0 + 64 * kk, make_uint4(csub(mul_shoup(x.x + m.q2 - v.x, qi.x, qi.y, m.q), m.q),
+                                     csub(mul_shoup(x.y + m.q2 - v.y, qi.x, qi.y, m.q), m.q),
+                                     csub(mul_shoup(x.z + m.q2 - v.z, qi.x, qi.y, m.q), m.q),
+                                     csub(mul_shoup(x.w + m.q2 - v.w, qi.x, qi.y, m.q), m.q)));
   }
 }
-
 
 // ============================================================================
 // Small rings (N = 2^kSrLog = 4096): a whole limb fits one work-group's LDS,
@@ -1554,63 +1538,6 @@ void klaunch(const Ctx& c, int stage, F kern, dim3 g, hipStream_t st, A... args)
   klaunch_b(c, stage, kern, g, kWG, st, args...);
 }
 
-// Column passes with fewer work-groups than this (half a work-group per CU)
-// use the narrowest column tiles, which double the work-groups at N = 2^16:
-// for such a grid every CU that joins shortens the pass (the rescale's INTT
-// of one limb: 8.4 -> 5.5 us), while at 192 or 288 work-groups the half-line
-// row segments cost more than the extra CUs gain (K2: 12.1 -> 14.1 us).
-constexpr int kNarrowBelow = 128;
-// Threads of the column passes over whole-line tiles: 16 elements per thread
-// (512 threads for the 8192-word tiles at N = 2^16).
-template <int L1>
-constexpr int kColThreads = ColGeom<L1>::ELEMS / 16;
-
-template <int L1, int CW, int T>
-struct R2c { static constexpr auto fn = r2_intt_cols<L1, CW, T>; };
-template <int L1, int CW, int T>
-struct R3c { static constexpr auto fn = r3_ntt_cols<L1, CW, T>; };
-
-// Launch a column pass over `rows` rows of every job in its tile shape:
-// quarter-width tiles in radix-4 phases (four elements per thread) when four
-// times the work-groups still fit one per CU and the quarter is at least 32
-// columns (N <= 2^13).  Otherwise a `sparse` pass (one whose launches have
-// about one work-group per CU or fewer: the INTT passes K2, K6 and the
-// rescale's) takes the narrowest tiles in radix-4 phases under kNarrowBelow
-// work-groups; above that, whole-line tiles with eight elements per thread in
-// radix-8 phases (radix8) or 16 per thread in radix-16 phases, as the
-// schedule's shape bits choose (col_radix8).
-template <template <int, int, int> class KF, int L1, class JA>
-void col_launch(const Ctx& c, int stage, int rows, int njobs, bool sparse, hipStream_t st,
-                const KsConst& K, const JA& jobs, bool radix8) {
-  constexpr int TL = ColGeom<L1>::TILES;
-  if constexpr (ColGeom<L1>::C / 4 >= 32) {
-    if (4 * TL * rows * njobs <= 256) {
-      constexpr int CW = ColGeom<L1>::C / 4;
-      constexpr int T = CW * (1 << L1) / 4;
-      klaunch_b(c, stage, KF<L1, CW, T>::fn, dim3(4 * TL, rows, njobs), T, st, K, jobs);
-      return;
-    }
-  }
-  if (sparse && TL * rows * njobs < kNarrowBelow) {
-    // radix-4 phases, four elements per thread: four waves per SIMD
-    constexpr int CW = kColNarrow<L1>;
-    constexpr int T = ColGeom<L1, CW>::ELEMS / 4;
-    klaunch_b(c, stage, KF<L1, CW, T>::fn, dim3(ColGeom<L1, CW>::TILES, rows, njobs), T, st, K, jobs);
-    return;
-  }
-  if (radix8) {  // 8 elements per thread: four waves per SIMD
-    constexpr int T = ColGeom<L1>::ELEMS / 8;
-    klaunch_b(c, stage, KF<L1, 0, T>::fn, dim3(TL, rows, njobs), T, st, K, jobs);
-    return;
-  }
-  klaunch_b(c, stage, KF<L1, 0, kColThreads<L1>>::fn, dim3(TL, rows, njobs), kColThreads<L1>, st, K, jobs);
-}
-// The whole-line radix of a column pass under schedule shape bits: sparse
-// (inverse) passes default to radix-8, the others to radix-16.
-inline bool col_radix8(bool sparse, int shape) {
-  return sparse ? !(shape & kShapeInvRadix16) : (shape & kShapeFwdRadix8) != 0;
-}
-
 // Groups of output rows of a column-conversion launch whose work-groups number
 // `base` at one group each (column tiles x digits or components x jobs), with
 // at most `rows` output rows: enough to have a work-group per CU (a group more
@@ -1728,14 +1655,10 @@ template <int L1>
 hipError_t rs_launch_t(const Ctx& c, const KsConst& K, const JobArg<RsJob>& jobs, int njobs,
                        int Lmax, hipStream_t st) {
   const int tiles = c.N / kTile;
-  if (4 * tiles * 2 * njobs <= 256)  // quarter tiles while they fit one work-group per CU
-    r1_intt_blks<L1, 4><<<dim3(4 * tiles, 2, njobs), kWG, 0, st>>>(K, jobs);
-  else
-    r1_intt_blks<L1, 16><<<dim3(tiles, 2, njobs), kWG, 0, st>>>(K, jobs);
-  col_launch<R2c, L1>(c, -1, 2, njobs, true, st, K, jobs, col_radix8(true, c.sched.ntt_shape));
-  col_launch<R3c, L1>(c, -1, 2 * (Lmax - 1), njobs, false, st, K, jobs, col_radix8(false, c.sched.ntt_shape));
-  klaunch(c, CKKS_STAGE_RESCALE_NTT, r4_ntt_blks_combine<L1>, dim3(tiles, 2 * (Lmax - 1), njobs), st, K,
-          jobs);
+  klaunch(c, -1, r1_intt_blks, dim3(tiles, 2, njobs), st, K, jobs);
+  const int groups = conv_groups((long)(c.N / 512) * 2 * njobs, Lmax - 1, kMaxPrimes);
+  klaunch_b(c, -1, r2_cols<L1>, dim3(c.N / 512, 2 * groups, njobs), 64 * kConvWaves, st, K, jobs, groups);
+  klaunch(c, CKKS_STAGE_RESCALE_NTT, r4_ntt_blks_combine, dim3(tiles, 2 * (Lmax - 1), njobs), st, K, jobs);
   return hipGetLastError();
 }
 }  // namespace

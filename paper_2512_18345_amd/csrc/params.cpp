@@ -18,7 +18,7 @@ namespace {
 using u64 = uint64_t;
 using u128 = unsigned __int128;
 
-u64 mulm(u64 a, u64 b, u64 m) { return (u64)((u128)a * b % m); }
+u64 mulm(u64 a, u64 b, u64 m) { return a * b % m; }  // operands below 2^32
 u64 powm(u64 b, u64 e, u64 m) {
   u64 r = 1 % m;
   b %= m;
