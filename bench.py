@@ -42,7 +42,7 @@ CYCLES_PER_WAVE_INST = 4
 
 # Sources whose change invalidates a stored PMC figure of the key-switching kernels.
 KERNEL_SOURCES = ["paper_2512_18345_amd/csrc/" + f for f in
-                  ("keyswitch.hip", "keyswitch.h", "mont_ntt.h", "ntt_tile.h", "arith.h", "ctx.h")]
+                  ("keyswitch.hip", "keyswitch.h", "mont_ntt.h", "arith.h", "ctx.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k5s_ntt_blks_ip_n16_l36_traffic.txt")
 VALU_FILE = os.path.join(ROOT, "profiles", "keyswitch_n16_l36_valu.txt")
 

@@ -152,19 +152,6 @@ uint32_t galois(const Ctx& c, int rot) {
 
 // ---- compositions ---------------------------------------------------------
 
-// ModDown of a [L + k][N] into out [L][N] (+ add if non-null); x: [k][N], z: [L][N] scratch.
-int moddown_impl(const Ctx& c, const uint32_t* a, int L, const uint32_t* add, uint32_t* out,
-                 uint32_t* x, uint32_t* z, hipStream_t st) {
-  const size_t N = c.N;
-  CKKS_TRY(launch_intt(c, a + (size_t)L * N, x, c.k, RowMap{0, c.L_max}, 0, 0, c.d_moddown_scale,
-                       c.L_max, st),
-           "ModDown INTT");
-  CKKS_TRY(launch_bconv(c, c.rows(L), x, c.k, z, L, 0, 0, c.d_moddown_T, c.k, st), "ModDown BConv");
-  CKKS_TRY(launch_ntt(c, z, z, L, c.rows(L), 0, 0, st), "ModDown NTT");
-  CKKS_TRY(launch_moddown_combine(c, L, a, z, add, out, st), "ModDown combine");
-  return CKKS_OK;
-}
-
 // One job through the fused pipeline.
 int run_one(const Ctx& c, int kind, int L, uint32_t gal, const uint32_t* a, const uint32_t* b,
             const uint32_t* key, uint32_t* out, void* ws, hipStream_t st) {
@@ -376,9 +363,9 @@ static int ntt_common(const ckks_ctx* ctx, uint32_t* a, int L, int with_P, void*
   const int rows = L + (with_P ? c.k : 0);
   const hipStream_t st = (hipStream_t)stream;
   if (inv)
-    CKKS_TRY(launch_intt(c, a, a, rows, c.rows(L), 0, 0, nullptr, 0, st), "INTT");
+    CKKS_TRY(launch_ntt(c, a, rows, c.rows(L), true, st), "INTT");
   else
-    CKKS_TRY(launch_ntt(c, a, a, rows, c.rows(L), 0, 0, st), "NTT");
+    CKKS_TRY(launch_ntt(c, a, rows, c.rows(L), false, st), "NTT");
   return CKKS_OK;
 }
 
@@ -486,10 +473,11 @@ int ckks_moddown(const ckks_ctx* ctx, const uint32_t* in, int L, uint32_t* out, 
   const Ctx& c = ctx->c;
   if ((rc = check_ws(c, CKKS_OP_MODDOWN, L, ws, ws_bytes_given))) return rc;
   DeviceGuard g(c.device);
-  WS w{(char*)ws, ws_bytes_given};
-  uint32_t* x = w.take(words(c, c.k));
-  uint32_t* z = w.take(words(c, L));
-  return moddown_impl(c, in, L, nullptr, out, x, z, (hipStream_t)stream);
+  JobArg<KsJob> ja{};
+  ja.table = nullptr;
+  ja.inl[0] = KsJob{KS_MODDOWN, L, 0, 0, in, nullptr, nullptr, out, (uint32_t*)ws};
+  CKKS_TRY(ks_moddown_launch(c, c.sched, ja, 1, L, (hipStream_t)stream), "ModDown");
+  return CKKS_OK;
 }
 
 int ckks_keyswitch(const ckks_ctx* ctx, const uint32_t* d, int L, const uint32_t* evk,

@@ -11,7 +11,7 @@
 
 namespace ckks {
 
-constexpr int kTileLog = 12;            // elements per NTT work-group tile
+constexpr int kTileLog = 12;            // words of a block-pass work-group (16 rows)
 constexpr int kTile = 1 << kTileLog;
 constexpr int kBlockLog = 8;            // pass-2 line length (N = N1 * 256)
 constexpr int kWG = 256;                // threads per work-group
@@ -29,54 +29,30 @@ struct ModC {
   uint32_t pad;
 };
 
-// What a kernel needs to find a prime's tables.  Every twiddle is stored as
-// (w, floor(w 2^32 / q)).
-//  * column pass: tw / itw [nprimes][N1], index m + i < N1 -> psi^(+-brv_logN(m + i));
-//  * block pass (after the twist below the 256-word block transform is the same
-//    for every block): ctw / ictw [nprimes][256], index 2^s + g ->
-//    psi^(+-(N / 2^s) brv_s(g));
-//  * twist of block b: twist / itwist [nprimes][N1][32], entries j < 16 are
-//    rho_b^(+-j) and 16 + h are rho_b^(+-16 h), rho_b = psi^(2 brv_logN1(b) + 1);
-//    the block pass multiplies element j of block b by rho_b^j before the
-//    forward network (by rho_b^-j after the inverse one);
-//  * whole-limb transforms of small rings (N = 2^kSrLog only, else null):
-//    ftw / fitw [nprimes][N], index m + i < N -> psi^(+-brv_logN(m + i)).
+// Per-prime constants, and the tables of the whole-limb transforms of small
+// rings (N = 2^kSrLog only, else null): ftw / fitw [nprimes][N], index m + i < N
+// -> psi^(+-brv_logN(m + i)) as (w, floor(w 2^32 / q)).
 constexpr int kSrLog = 12;
 struct DevTab {
   const ModC* mod;   // [nprimes]
-  const uint2* tw;
-  const uint2* itw;
-  const uint2* ctw;
-  const uint2* ictw;
-  const uint2* twist;
-  const uint2* itwist;
   const uint2* ftw;
   const uint2* fitw;
   int logN;
   int L_max;
   __host__ __device__ int logN1() const { return logN - 8; }
-  __device__ const uint2* col_tw(int pi) const { return tw + ((size_t)pi << logN1()); }
-  __device__ const uint2* col_itw(int pi) const { return itw + ((size_t)pi << logN1()); }
-  __device__ const uint2* blk_tw(int pi) const { return ctw + ((size_t)pi << 8); }
-  __device__ const uint2* blk_itw(int pi) const { return ictw + ((size_t)pi << 8); }
-  __device__ const uint2* blk_twist(int pi, int b) const {
-    return twist + ((((size_t)pi << logN1()) + b) << 5);
-  }
-  __device__ const uint2* blk_itwist(int pi, int b) const {
-    return itwist + ((((size_t)pi << logN1()) + b) << 5);
-  }
   __device__ const uint2* full_tw(int pi) const { return ftw + ((size_t)pi << logN); }
   __device__ const uint2* full_itw(int pi) const { return fitw + ((size_t)pi << logN); }
 };
 
-// Tables of the Montgomery transforms (mont_ntt.h), one word w 2^32 mod q per
-// entry, indexed as their Shoup forms above:
-//  * col / icol [nprimes][N1], blk / iblk [nprimes][256];
-//  * row / irow [nprimes][N1][32]: the first four block-pass stages of row b
-//    with its own twiddles, entry 2^s + g < 16 -> psi^(+-brv_logN((N1 + b) 2^s + g)),
-//    and entry 16 + j -> rho_b^(+-j), which is all of the twist that remains
-//    for the last four stages;
-//  * the base-conversion constants: pre-multipliers and T times 2^32.
+// Tables of the two-pass transforms (mont_ntt.h) and of the base conversions,
+// one word w 2^32 mod q per entry:
+//  * column pass: col / icol [nprimes][N1], index m + i < N1 -> psi^(+-brv_logN(m + i));
+//  * block pass, first four stages: row / irow [nprimes][N1][32] with row b's own
+//    twiddles, entry 2^s + g < 16 -> psi^(+-brv_logN((N1 + b) 2^s + g)), and at
+//    entry 16 + j the factor rho_b^(+-j), rho_b = psi^(2 brv_logN1(b) + 1);
+//  * block pass, last four stages: blk / iblk [nprimes][256], shared by every row
+//    once its words carry that factor: index 2^s + g -> psi^(+-(N / 2^s) brv_s(g));
+//  * the base-conversion pre-multipliers and tables.
 struct MontTab {
   const uint32_t *col, *icol, *blk, *iblk, *row, *irow;
   const uint32_t *modup_scale, *modup_T, *moddown_scale, *moddown_T, *pinv;
@@ -109,12 +85,6 @@ struct Ctx {
 
   // device tables
   ModC* d_mod = nullptr;
-  uint2* d_tw = nullptr;      // [nprimes][N1]
-  uint2* d_itw = nullptr;
-  uint2* d_ctw = nullptr;     // [nprimes][256]
-  uint2* d_ictw = nullptr;
-  uint2* d_twist = nullptr;   // [nprimes][N1][32]
-  uint2* d_itwist = nullptr;
   uint2* d_ftw = nullptr;     // [nprimes][N], N = 2^kSrLog only
   uint2* d_fitw = nullptr;
   // ModUp at level L (1-based): per Q row i < L, (N^-1 * (D_j/q_i)^-1, Shoup) where j = i / alpha.
@@ -166,7 +136,7 @@ struct Ctx {
   }
 
   DevTab tab() const {
-    return DevTab{d_mod, d_tw, d_itw, d_ctw, d_ictw, d_twist, d_itwist, d_ftw, d_fitw, logN, L_max};
+    return DevTab{d_mod, d_ftw, d_fitw, logN, L_max};
   }
   RowMap rows(int L) const { return RowMap{L, L_max}; }
   int beta(int L) const { return (L + alpha - 1) / alpha; }

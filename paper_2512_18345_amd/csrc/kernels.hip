@@ -1,172 +1,152 @@
 // gfx950 kernels for the stand-alone entry points: NTT / INTT (two passes,
-// see ntt_tile.h), base conversion, inner product, tensor, automorphism and
-// the element-wise combines.  The fused key-switching pipeline lives in
-// keyswitch.hip.
+// see mont_ntt.h), inner product, tensor, automorphism, plaintext sums.  The
+// key-switching pipeline, ModUp and ModDown live in keyswitch.hip.
 #include <hip/hip_runtime.h>
 
 #include "arith.h"
 #include "ctx.h"
 #include "kernels.h"
-#include "ntt_tile.h"
+#include "mont_ntt.h"
 
 namespace ckks {
 
 // ============================================================================
-// NTT kernels
+// NTT kernels: in place and in row order throughout (a transform has no
+// workspace), so the column pass takes tiles of at least 32 columns, whole
+// 128-byte lines of every row, through LDS.  A wave owns C of the columns and
+// transforms them in the LDS tile as mont_ntt.h does, without a barrier; the
+// block pass needs none at all.  Bound: the loads, transform and stores of one
+// round of work-groups follow one another.  N = 2^16, 48 rows: forward 12.3 +
+// 13.0 -> 8.6 + 7.4 us, inverse 10.6 + 15.5 -> 7.0 + 9.1 (radix-16 tiles of 256
+// threads with barriers and twiddles in LDS before).
 // ============================================================================
-
-// Forward column pass: rows r in [0, gridDim.y) except [skip_lo, skip_hi).
-// Output lazy in [0, 4q).
 template <int LOGN1>
-__global__ __launch_bounds__(kWG) void k_ntt_cols(DevTab T, RowMap rm, const uint32_t* src,
-                                                  uint32_t* dst, int skip_lo, int skip_hi) {
-  __shared__ __align__(16) uint32_t s[ColGeom<LOGN1>::LDS];
-  const int r = blockIdx.y;
-  if (r >= skip_lo && r < skip_hi) return;
-  const int pi = rm.pidx(r);
-  __shared__ uint2 stw[ColGeom<LOGN1>::N1];
-  const uint2 tww = tw_fetch(T.col_tw(pi), ColGeom<LOGN1>::N1);
-  const size_t N = (size_t)1 << T.logN;
-  const uint32_t q = ldc(T.mod + pi).q, q2 = 2 * q;
-  const int col0 = blockIdx.x * ColGeom<LOGN1>::C;
-  load_cols<LOGN1>(s, src + r * N, col0);
-  tw_put(stw, tww, ColGeom<LOGN1>::N1);
+struct ColTile {
+  using CH = ColPart<LOGN1, 64>;
+  static constexpr int N1 = 1 << LOGN1, C = CH::C;
+  static constexpr int W = C >= 8 ? 4 : 8;   // waves
+  static constexpr int COLS = W * C;         // 32 .. 256
+  static constexpr int T = 64 * W;
+  static constexpr int QUADS = N1 * COLS / (4 * T);  // per thread: 4
+  // word (row, col) of the tile: both layouts of a wave's columns meet 64
+  // different banks (rows of one 16 C + COLS words apart, groups of 16 rows C more)
+  __device__ static __forceinline__ int at(int row, int col) { return row * (COLS + C) + (row >> 4) * C + col; }
+  static constexpr int LDS = N1 * (COLS + C) + (N1 >> 4) * C;
+};
+
+template <int LOGN1, bool INV>
+__global__ __launch_bounds__(ColTile<LOGN1>::T) void k_ntt_cols(DevTab T, MontTab M, RowMap rm, uint32_t* a) {
+  using CT = ColTile<LOGN1>;
+  using CH = typename CT::CH;
+  __shared__ __align__(16) uint32_t s[CT::LDS];
+  const int r = blockIdx.y, pi = rm.pidx(r);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t* row = a + ((size_t)r << T.logN) + blockIdx.x * CT::COLS;
+  uint4 raw[CT::QUADS];
+#pragma unroll
+  for (int k = 0; k < CT::QUADS; ++k) {
+    const int lin = 4 * (threadIdx.x + k * CT::T);
+    raw[k] = ld4(row + (lin / CT::COLS) * 256 + lin % CT::COLS);
+  }
+  typename CH::Tw tw;
+  tw.load(INV ? M.col_itw(T, pi) : M.col_tw(T, pi), lane);
+  const ModC mc = ldc(T.mod + pi);
+  const MontQ m = mont_q(mc);
+#pragma unroll
+  for (int k = 0; k < CT::QUADS; ++k) {
+    const int lin = 4 * (threadIdx.x + k * CT::T);
+    *reinterpret_cast<uint4*>(s + CT::at(lin / CT::COLS, lin % CT::COLS)) = raw[k];
+  }
   __syncthreads();
-  col_stages<LOGN1, false>(s, stw, q, q2);
+  const int c0 = w * CT::C + lane % CT::C, node = lane / CT::C;  // node: 16-row group (low layout), r (high)
+  constexpr int E = CH::E;
+  uint32_t v[16];
+  auto high_row = [&](int k) { return 16 * (k >> (4 - E)) + ((k & ((16 >> E) - 1)) << E) + node; };
+  auto get_high = [&]() {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = s[CT::at(high_row(k), c0)];
+  };
+  auto put_high = [&]() {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) s[CT::at(high_row(k), c0)] = v[k];
+  };
+  auto get_low = [&]() {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = s[CT::at(16 * node + j, c0)];
+  };
+  auto put_low = [&]() {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s[CT::at(16 * node + j, c0)] = v[j];
+  };
+  if constexpr (!INV) {
+    if constexpr (E > 0) {
+      get_high();
+      ct_stages<0, E>(v, tw.hi, m);
+      put_high();
+      wave_sync();
+    }
+    get_low();
+    ct_stages<0, 4>(v, tw.lo, m);
+    put_low();
+  } else {
+    get_low();
+    gs_stages<0, 4>(v, tw.lo, m);
+    if constexpr (E > 0) {
+      put_low();
+      wave_sync();
+      get_high();
+      gs_stages<0, E>(v, tw.hi, m);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = csub(mul_shoup(v[k], mc.ninv, mc.ninv_s, m.q), m.q);
+    if constexpr (E > 0)
+      put_high();
+    else
+      put_low();
+  }
   __syncthreads();
-  store_cols<LOGN1>(s, dst + r * N, col0);
+  const OutRow out(row);
+#pragma unroll
+  for (int k = 0; k < CT::QUADS; ++k) {
+    const int lin = 4 * (threadIdx.x + k * CT::T);
+    out.st4((lin / CT::COLS) * 256 + lin % CT::COLS,
+            *reinterpret_cast<const uint4*>(s + CT::at(lin / CT::COLS, lin % CT::COLS)));
+  }
 }
 
-// Forward block pass; canonical output.
-template <int LOGN1>
-__global__ __launch_bounds__(kWG) void k_ntt_blks(DevTab T, RowMap rm, const uint32_t* src,
-                                                  uint32_t* dst, int skip_lo, int skip_hi) {
-  __shared__ __align__(16) uint32_t s[kLds];
-  const int r = blockIdx.y;
-  if (r >= skip_lo && r < skip_hi) return;
-  const int pi = rm.pidx(r);
-  __shared__ uint2 stw[256];
-  const uint2 tww = tw_fetch(T.blk_tw(pi), 256);
-  const size_t N = (size_t)1 << T.logN;
-  const uint32_t q = ldc(T.mod + pi).q, q2 = 2 * q;
-  const int blk0 = blockIdx.x * 16;
-  const uint32_t* in = src + r * N + blk0 * 256;
-  uint32_t* out = dst + r * N + blk0 * 256;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int e = blk_elem(k);
-    lds_blk4_store(s, e, twist4(ld4(in + e),
-                                T.blk_twist(pi, blk0 + (e >> 8)), e & 255, q));
-  }
-  tw_put_perm(stw, tww);
-  __syncthreads();
-  blk_stages<false>(s, PermTw{stw}, q, q2);
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int e = blk_elem(k);
-    st4(out + e, canon4(lds_blk4(s, e), q, q2));
-  }
-}
-
-// Inverse block pass (first Gentleman-Sande stages); output in [0, 2q).
-template <int LOGN1>
-__global__ __launch_bounds__(kWG) void k_intt_blks(DevTab T, RowMap rm, const uint32_t* src,
-                                                   uint32_t* dst, int skip_lo, int skip_hi) {
-  __shared__ __align__(16) uint32_t s[kLds];
-  const int r = blockIdx.y;
-  if (r >= skip_lo && r < skip_hi) return;
-  const int pi = rm.pidx(r);
-  __shared__ uint2 stw[256];
-  const uint2 tww = tw_fetch(T.blk_itw(pi), 256);
-  const size_t N = (size_t)1 << T.logN;
-  const uint32_t q = ldc(T.mod + pi).q, q2 = 2 * q;
-  const int blk0 = blockIdx.x * 16;
-  const uint32_t* in = src + r * N + blk0 * 256;
-  uint32_t* out = dst + r * N + blk0 * 256;
+template <bool INV>
+__global__ __launch_bounds__(kWG) void k_ntt_blks(DevTab T, MontTab M, RowMap rm, uint32_t* a) {
+  __shared__ __align__(16) uint32_t s[kBlkTile];
+  const int r = blockIdx.y, pi = rm.pidx(r);
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  uint32_t* row = a + ((size_t)r << T.logN) + blockIdx.x * kTile;
+  const int n0 = line * 256 + 4 * (lane & 15);
   uint4 x[4];
-  Twist4 tfi[4];  // the epilogue's twist factors, requested with the tile
+  BlkTw tw;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) x[k] = ld4(in + blk_elem(k));
+  for (int kk = 0; kk < 4; ++kk) x[kk] = ld4(row + n0 + 64 * kk);
+  tw.load(INV ? M.row_itw(T, pi, blockIdx.x * 16 + line) : M.row_tw(T, pi, blockIdx.x * 16 + line),
+          INV ? M.blk_itw(pi) : M.blk_tw(pi), lane);
+  const MontQ m = mont_q(ldc(T.mod + pi));
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int e = blk_elem(k);
-    tfi[k] = twist4_load(T.blk_itwist(pi, blk0 + (e >> 8)), e & 255);
-  }
+  for (int kk = 0; kk < 4; ++kk) blk_quad_store(s, line, 4 * (lane & 15) + 64 * kk, x[kk]);
+  wave_sync();
+  if constexpr (INV)
+    blk_inv_a(s, line, lane, tw, m);
+  else
+    blk_fwd_a(s, line, lane, tw, m);
+  wave_sync();
+  if constexpr (INV)
+    blk_inv_b(s, line, lane, tw, m);
+  else
+    blk_fwd_b(s, line, lane, tw, m);
+  wave_sync();
+  const OutRow out(row);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) lds_blk4_store(s, blk_elem(k), x[k]);
-  tw_put_perm(stw, tww);
-  __syncthreads();
-  blk_stages<true>(s, PermTw{stw}, q, q2);
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 4; ++k) st4(out + blk_elem(k), twist4(lds_blk4(s, blk_elem(k)), tfi[k], q));
-}
-
-// Inverse column pass + per-row scale (N^-1 times an optional base-conversion
-// pre-multiplier) -> canonical output.  scale[pidx - scale_off] = (c, Shoup(c));
-// scale == nullptr means N^-1 alone.
-template <int LOGN1>
-__global__ __launch_bounds__(kWG) void k_intt_cols(DevTab T, RowMap rm, const uint32_t* src,
-                                                   uint32_t* dst, int skip_lo, int skip_hi,
-                                                   const uint2* scale, int scale_off) {
-  __shared__ __align__(16) uint32_t s[ColGeom<LOGN1>::LDS];
-  constexpr int C = ColGeom<LOGN1>::C;
-  const int r = blockIdx.y;
-  if (r >= skip_lo && r < skip_hi) return;
-  const int pi = rm.pidx(r);
-  __shared__ uint2 stw[ColGeom<LOGN1>::N1];
-  const uint2 tww = tw_fetch(T.col_itw(pi), ColGeom<LOGN1>::N1);
-  const size_t N = (size_t)1 << T.logN;
-  const ModC mc = T.mod[pi];
-  const uint32_t q = mc.q, q2 = 2 * q;
-  const uint2 sc = scale ? scale[pi - scale_off] : make_uint2(mc.ninv, mc.ninv_s);
-  const int col0 = blockIdx.x * C;
-  load_cols<LOGN1>(s, src + r * N, col0);
-  tw_put(stw, tww, ColGeom<LOGN1>::N1);
-  __syncthreads();
-  col_stages<LOGN1, true>(s, stw, q, q2);
-  __syncthreads();
-  uint32_t* row = dst + r * N;
-#pragma unroll
-  for (int k = 0; k < ColGeom<LOGN1>::QUADS; ++k) {
-    const int lin = (threadIdx.x + k * kWG) * 4;
-    const int pos = lin / C, c = lin & (C - 1);
-    uint4 v = *reinterpret_cast<const uint4*>(s + lidx_col(pos, c, C));
-    v.x = csub(mul_shoup(v.x, sc.x, sc.y, q), q);
-    v.y = csub(mul_shoup(v.y, sc.x, sc.y, q), q);
-    v.z = csub(mul_shoup(v.z, sc.x, sc.y, q), q);
-    v.w = csub(mul_shoup(v.w, sc.x, sc.y, q), q);
-    st4(row + pos * 256 + col0 + c, v);
-  }
-}
-
-// ============================================================================
-// Base conversion (Sec. II-B2, III-C2): z_r = sum_i y_i * T[r][i] mod prime(r),
-// y canonical coefficient-domain rows (pre-multiplied already), one 64-bit
-// accumulation and a single reduction per output (overflow-free by the
-// bound checked at context creation).
-// ============================================================================
-template <int NIN>
-__global__ __launch_bounds__(kWG) void k_bconv(DevTab T, RowMap rm, const uint32_t* y, int nin,
-                                               uint32_t* out, int nrows, int skip_lo, int skip_hi,
-                                               const uint32_t* Tt, int tstride, int rows_per_block) {
-  const size_t N = (size_t)1 << T.logN;
-  const size_t n = (size_t)blockIdx.x * kWG + threadIdx.x;
-  uint32_t x[NIN];
-#pragma unroll
-  for (int i = 0; i < NIN; ++i) x[i] = i < nin ? y[i * N + n] : 0u;
-  const int r0 = blockIdx.y * rows_per_block;
-  const int r1 = min(r0 + rows_per_block, nrows);
-  for (int r = r0; r < r1; ++r) {
-    if (r >= skip_lo && r < skip_hi) continue;
-    const ModC mc = T.mod[rm.pidx(r)];
-    const uint32_t* t = Tt + (size_t)r * tstride;
-    uint64_t acc = 0;
-#pragma unroll
-    for (int i = 0; i < NIN; ++i)
-      if (i < nin) acc += (uint64_t)x[i] * t[i];
-    out[r * N + n] = reduce64(acc, mc.q, mc.mu_hi, mc.mu_lo);
+  for (int kk = 0; kk < 4; ++kk) {
+    const uint4 v = blk_quad(s, line, 4 * (lane & 15) + 64 * kk);
+    out.st4(n0 + 64 * kk, INV ? v : canon4(v, m.q, m.q2));
   }
 }
 
@@ -225,48 +205,6 @@ __global__ __launch_bounds__(kWG) void k_automorph(int logN, const uint32_t* in,
   const int r0 = blockIdx.y * rows_per_block;
   const int r1 = min(r0 + rows_per_block, rows);
   for (int r = r0; r < r1; ++r) out[(size_t)r * N + j] = in[(size_t)r * N + src];
-}
-
-// out_i = (acc_i - z_i) * P^-1 (+ add_i) mod q_i: the ModDown combine (floor form).
-__global__ __launch_bounds__(kWG) void k_moddown_combine(DevTab T, const uint32_t* acc,
-                                                         const uint32_t* z, const uint2* pinv,
-                                                         const uint32_t* add, uint32_t* out) {
-  const size_t N = (size_t)1 << T.logN;
-  const size_t n = (size_t)blockIdx.x * kWG + threadIdx.x;
-  const int i = blockIdx.y;
-  const uint32_t q = T.mod[i].q;
-  const size_t e = (size_t)i * N + n;
-  const uint2 pv = pinv[i];
-  uint32_t v = csub(mul_shoup(acc[e] + q - z[e], pv.x, pv.y, q), q);
-  if (add) v = csub(v + add[e], q);
-  out[e] = v;
-}
-
-// out = a + b mod q_r over [rows][N] (rows are Q rows 0..rows-1).
-__global__ __launch_bounds__(kWG) void k_add(DevTab T, const uint32_t* a, const uint32_t* b,
-                                             uint32_t* out) {
-  const size_t N = (size_t)1 << T.logN;
-  const size_t e = (size_t)blockIdx.y * N + (size_t)blockIdx.x * kWG + threadIdx.x;
-  out[e] = csub(a[e] + b[e], T.mod[blockIdx.y].q);
-}
-
-// Rescale helpers: bc[i][n] = t[n] mod q_i (i < rows), t canonical mod q_top.
-__global__ __launch_bounds__(kWG) void k_broadcast_mod(DevTab T, const uint32_t* t, uint32_t* bc) {
-  const size_t N = (size_t)1 << T.logN;
-  const size_t n = (size_t)blockIdx.x * kWG + threadIdx.x;
-  const ModC mc = T.mod[blockIdx.y];
-  bc[(size_t)blockIdx.y * N + n] = reduce32(t[n], mc.q, mc.mu32);
-}
-
-// out_i = (a_i - v_i) * qinv_i mod q_i.
-__global__ __launch_bounds__(kWG) void k_sub_scale(DevTab T, const uint32_t* a, const uint32_t* v,
-                                                   const uint2* qinv, uint32_t* out) {
-  const size_t N = (size_t)1 << T.logN;
-  const int i = blockIdx.y;
-  const size_t e = (size_t)i * N + (size_t)blockIdx.x * kWG + threadIdx.x;
-  const uint32_t q = T.mod[i].q;
-  const uint2 c = qinv[i];
-  out[e] = csub(mul_shoup(a[e] + q - v[e], c.x, c.y, q), q);
 }
 
 // Plaintext products summed (the baby-step inner products of a BSGS linear
@@ -374,49 +312,22 @@ __global__ __launch_bounds__(kWG) void k_ct_add(DevTab T, const uint32_t* a, con
     default: return hipErrorInvalidValue; \
   }
 
-hipError_t launch_ntt(const Ctx& c, const uint32_t* src, uint32_t* dst, int rows, RowMap rm,
-                      int skip_lo, int skip_hi, hipStream_t st) {
+hipError_t launch_ntt(const Ctx& c, uint32_t* a, int rows, RowMap rm, bool inverse, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
-  const int logN1 = c.logN - kBlockLog;
-  const dim3 grid(c.N / kTile, rows);
-#define CALL(L1)                                                                              \
-  k_ntt_cols<L1><<<dim3(ColGeom<L1>::TILES, rows), kWG, 0, st>>>(c.tab(), rm, src, dst, skip_lo, skip_hi); \
-  k_ntt_blks<L1><<<grid, kWG, 0, st>>>(c.tab(), rm, dst, dst, skip_lo, skip_hi);
-  CKKS_DISPATCH_LOGN1(logN1, CALL)
+  const dim3 blks(c.N / kTile, rows);
+#define CALL(L1)                                                                       \
+  {                                                                                    \
+    const dim3 cols(256 / ColTile<L1>::COLS, rows);                                    \
+    if (inverse) {                                                                     \
+      k_ntt_blks<true><<<blks, kWG, 0, st>>>(c.tab(), c.mont, rm, a);                  \
+      k_ntt_cols<L1, true><<<cols, ColTile<L1>::T, 0, st>>>(c.tab(), c.mont, rm, a);   \
+    } else {                                                                           \
+      k_ntt_cols<L1, false><<<cols, ColTile<L1>::T, 0, st>>>(c.tab(), c.mont, rm, a);  \
+      k_ntt_blks<false><<<blks, kWG, 0, st>>>(c.tab(), c.mont, rm, a);                 \
+    }                                                                                  \
+  }
+  CKKS_DISPATCH_LOGN1(c.logN - kBlockLog, CALL)
 #undef CALL
-  return hipGetLastError();
-}
-
-hipError_t launch_intt(const Ctx& c, const uint32_t* src, uint32_t* dst, int rows, RowMap rm,
-                       int skip_lo, int skip_hi, const uint2* scale, int scale_off,
-                       hipStream_t st) {
-  if (rows <= 0) return hipSuccess;
-  const int logN1 = c.logN - kBlockLog;
-  const dim3 grid(c.N / kTile, rows);
-#define CALL(L1)                                                                              \
-  k_intt_blks<L1><<<grid, kWG, 0, st>>>(c.tab(), rm, src, dst, skip_lo, skip_hi);            \
-  k_intt_cols<L1><<<dim3(ColGeom<L1>::TILES, rows), kWG, 0, st>>>(c.tab(), rm, dst, dst, skip_lo, skip_hi, scale, scale_off);
-  CKKS_DISPATCH_LOGN1(logN1, CALL)
-#undef CALL
-  return hipGetLastError();
-}
-
-hipError_t launch_bconv(const Ctx& c, RowMap rm, const uint32_t* y, int nin, uint32_t* out,
-                        int nrows, int skip_lo, int skip_hi, const uint32_t* Tt, int tstride,
-                        hipStream_t st) {
-  if (nrows <= 0) return hipSuccess;
-  const int rpb = 4;
-  const dim3 grid(c.N / kWG, (nrows + rpb - 1) / rpb);
-  if (nin <= 4)
-    k_bconv<4><<<grid, kWG, 0, st>>>(c.tab(), rm, y, nin, out, nrows, skip_lo, skip_hi, Tt, tstride, rpb);
-  else if (nin <= 8)
-    k_bconv<8><<<grid, kWG, 0, st>>>(c.tab(), rm, y, nin, out, nrows, skip_lo, skip_hi, Tt, tstride, rpb);
-  else if (nin <= 12)
-    k_bconv<12><<<grid, kWG, 0, st>>>(c.tab(), rm, y, nin, out, nrows, skip_lo, skip_hi, Tt, tstride, rpb);
-  else if (nin <= 16)
-    k_bconv<16><<<grid, kWG, 0, st>>>(c.tab(), rm, y, nin, out, nrows, skip_lo, skip_hi, Tt, tstride, rpb);
-  else
-    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -436,32 +347,6 @@ hipError_t launch_automorph(const Ctx& c, const uint32_t* in, uint32_t* out, int
                             hipStream_t st) {
   const int rpb = 4;
   k_automorph<<<dim3(c.N / kWG, (rows + rpb - 1) / rpb), kWG, 0, st>>>(c.logN, in, out, rows, g, rpb);
-  return hipGetLastError();
-}
-
-hipError_t launch_moddown_combine(const Ctx& c, int L, const uint32_t* acc, const uint32_t* z,
-                                  const uint32_t* add, uint32_t* out, hipStream_t st) {
-  k_moddown_combine<<<dim3(c.N / kWG, L), kWG, 0, st>>>(c.tab(), acc, z, c.d_pinv, add, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_add(const Ctx& c, int rows, const uint32_t* a, const uint32_t* b, uint32_t* out,
-                      hipStream_t st) {
-  k_add<<<dim3(c.N / kWG, rows), kWG, 0, st>>>(c.tab(), a, b, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_broadcast_mod(const Ctx& c, int rows, const uint32_t* t, uint32_t* bc,
-                                hipStream_t st) {
-  if (rows <= 0) return hipSuccess;
-  k_broadcast_mod<<<dim3(c.N / kWG, rows), kWG, 0, st>>>(c.tab(), t, bc);
-  return hipGetLastError();
-}
-
-hipError_t launch_sub_scale(const Ctx& c, int rows, const uint32_t* a, const uint32_t* v,
-                            const uint2* qinv, uint32_t* out, hipStream_t st) {
-  if (rows <= 0) return hipSuccess;
-  k_sub_scale<<<dim3(c.N / kWG, rows), kWG, 0, st>>>(c.tab(), a, v, qinv, out);
   return hipGetLastError();
 }
 

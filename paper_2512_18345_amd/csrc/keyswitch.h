@@ -19,6 +19,7 @@ enum KsKind : int {
   KS_HOIST = 3,  // a = ct, b = ModUp(c1) [beta][L + k][N]; out as HROT but from sigma(ModUp(c1))
   KS_MODUP = 4,  // ModUp alone (the shared ModUp of hoisted rotations): a = d [L][N] (evaluation
                  // domain), out = M [beta][L + k][N] (every row, the digit rows copied), ws = [L][N]
+  KS_MODDOWN = 5,  // ModDown alone: a [L + k][N], out [L][N], ws = [k + L][N]
 };
 
 struct __align__(16) KsJob {
@@ -77,6 +78,9 @@ hipError_t ks_launch(const Ctx& c, const Ctx::Sched& sc, const JobArg<KsJob>& jo
 // new rows: M ends fully in the evaluation domain, canonical).
 hipError_t ks_modup_launch(const Ctx& c, const Ctx::Sched& sc, const JobArg<KsJob>& jobs, int njobs, int Lmax,
                            hipStream_t st);
+// Enqueue the ModDown of njobs KS_MODDOWN jobs.
+hipError_t ks_moddown_launch(const Ctx& c, const Ctx::Sched& sc, const JobArg<KsJob>& jobs, int njobs, int Lmax,
+                             hipStream_t st);
 // Enqueue rescale (drop the top prime) for njobs jobs.
 hipError_t rs_launch(const Ctx& c, const JobArg<RsJob>& jobs, int njobs, int Lmax, hipStream_t st);
 

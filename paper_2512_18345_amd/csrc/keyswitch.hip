@@ -58,11 +58,13 @@ KsConst make_const(const Ctx& c) {
                  c.d_modup_T_off, c.d_moddown_scale, c.d_moddown_T, c.d_pinv, c.d_rescale_inv, c.mont};
 }
 
-// Scratch layout of one job (rows of N words): acc [2][R], x [2][k], w [2][L],
+// Scratch layout of one job (rows of N words): acc [2][R], [2][k] unused, w [2][L],
 // then, for jobs that run ModUp, y [L], z [beta][R] and de [L] (the eval-domain
 // polynomial being switched, kept by K1 for the digit rows of K5); R = L + k.
 struct KsView {
-  uint32_t *y, *z, *de, *acc, *x, *w;
+  uint32_t *y, *z, *de, *acc, *w;
+  const uint32_t* p;  // the P rows after their INTT block pass (row-group layout), component c at p + c ps N
+  int ps;
   int L, R, beta;
 };
 
@@ -74,12 +76,23 @@ __device__ __forceinline__ KsView ks_view(const KsJob& J, const KsConst& K, size
   if (J.kind == KS_MODUP) {  // ModUp alone: y in the scratch, z is the output M
     v.y = J.ws;
     v.z = J.out;
-    v.acc = v.x = v.w = v.de = nullptr;
+    v.acc = v.w = v.de = nullptr;
+    v.p = nullptr;
+    v.ps = 0;
+    return v;
+  }
+  if (J.kind == KS_MODDOWN) {  // ModDown alone: P rows, then w, in the scratch
+    v.y = J.ws;
+    v.w = J.ws + (size_t)K.k * N;
+    v.p = J.ws;
+    v.ps = K.k;
+    v.z = v.acc = v.de = nullptr;
     return v;
   }
   v.acc = J.ws;
-  v.x = v.acc + (size_t)2 * v.R * N;
-  v.w = v.x + (size_t)2 * K.k * N;
+  v.p = v.acc + (size_t)v.L * N;
+  v.ps = v.R;
+  v.w = v.acc + ((size_t)2 * v.R + 2 * K.k) * N;
   v.y = v.w + (size_t)2 * v.L * N;
   v.z = v.y + (size_t)v.L * N;
   v.de = v.z + (size_t)v.beta * v.R * N;
@@ -122,7 +135,7 @@ __device__ __forceinline__ uint32_t mulmod(uint32_t a, uint32_t b, const ModC& m
 // issued before any of them is used.
 __device__ __forceinline__ void load_d16(const KsJob& J, int r, uint32_t n0, size_t N, int logN,
                                          const ModC& m, uint4 d[4]) {
-  if (J.kind == KS_PLAIN || J.kind == KS_MODUP) {
+  if (J.kind == KS_PLAIN || J.kind == KS_MODUP || J.kind == KS_MODDOWN) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) d[kk] = ld4(J.a + (size_t)r * N + n0 + 64 * kk);
     return;
@@ -164,11 +177,13 @@ __device__ __forceinline__ void load_d16(const KsJob& J, int r, uint32_t n0, siz
 __global__ __launch_bounds__(kWG) void k1_intt_blks(KsConst K, JobArg<KsJob> JA) {
   const KsJob J = JA.get(blockIdx.z);
   const int r = blockIdx.y;
-  if (J.kind == KS_HOIST || r >= J.L) return;
+  const bool down = J.kind == KS_MODDOWN;  // the P rows of its input, else every row
+  if (J.kind == KS_HOIST || r >= (down ? K.k : J.L)) return;
   __shared__ __align__(16) uint32_t s[kBlkTile];
   const int logN = K.T.logN;
   const size_t N = (size_t)1 << logN;
-  const ModC mc = ldc(K.T.mod + r);
+  const int pi = down ? K.T.L_max + r : r;
+  const ModC mc = ldc(K.T.mod + pi);
   const MontQ m = mont_q(mc);
   const uint32_t base = blockIdx.x * kTile;
   const KsView V = ks_view(J, K, N);
@@ -181,12 +196,12 @@ __global__ __launch_bounds__(kWG) void k1_intt_blks(KsConst K, JobArg<KsJob> JA)
   // all loads first: a store to de could alias the next quad's source
   BlkTw tw;
   uint4 d[4];
-  load_d16(J, r, n0, N, logN, mc, d);
-  tw.load(K.M.row_itw(K.T, r, blockIdx.x * 16 + line), K.M.blk_itw(r), lane);
+  load_d16(J, down ? J.L + r : r, n0, N, logN, mc, d);
+  tw.load(K.M.row_itw(K.T, pi, blockIdx.x * 16 + line), K.M.blk_itw(pi), lane);
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     blk_quad_store(s, line, 4 * (lane & 15) + 64 * kk, d[kk]);
-    if (J.kind != KS_PLAIN) de.st4(n0 + 64 * kk, d[kk]);  // HMULT, HROT, MODUP
+    if (J.kind != KS_PLAIN && !down) de.st4(n0 + 64 * kk, d[kk]);  // HMULT, HROT, MODUP
   }
   wave_sync();
   blk_inv_a(s, line, lane, tw, m);
@@ -264,7 +279,7 @@ __global__ __launch_bounds__(64 * kConvWaves, 4) void kc_conv(KsConst K, JobArg<
     const int i = min(i0 + half, nin - 1);  // an odd last limb: both halves, the same words
     const int pi = MODE == CONV_UP ? lo + i : K.T.L_max + i;
     const uint32_t* src = MODE == CONV_UP ? V.y + (size_t)(lo + i) * N
-                                          : V.acc + ((size_t)jd * V.R + V.L + i) * N;
+                                          : V.p + ((size_t)jd * V.ps + i) * N;
     uint32_t v[16];
     typename CH::Tw tw;
     CH::load(v, src, tile, n);
@@ -1111,29 +1126,24 @@ __global__ __launch_bounds__(64 * kConvWaves, 4) void r2_cols(KsConst K, JobArg<
   }
 }
 
-// Bound: memory (a, u in, out: 55 MB at N = 2^16, L = 36).
-__global__ __launch_bounds__(kWG) void r4_ntt_blks_combine(KsConst K, JobArg<RsJob> JA) {
-  const RsJob J = JA.get(blockIdx.z);
-  const int L1 = J.L - 1;
-  const int gr = blockIdx.y;
-  if (gr >= 2 * L1) return;
-  const int c = gr / L1, i = gr % L1;
+// One row group of out = (a - NTT(u)) f mod q of prime i: the block pass of u
+// (column pass done, row-group layout), a and out in row order; f with its
+// Shoup companion.
+__device__ __forceinline__ void sub_scale_rows(const KsConst& K, int i, const uint32_t* u, const uint32_t* a,
+                                               uint32_t* dst, uint2 f) {
   __shared__ __align__(16) uint32_t s[kBlkTile];
-  const size_t N = (size_t)1 << K.T.logN;
   const MontQ m = mont_q(ldc(K.T.mod + i));
   const uint32_t base = blockIdx.x * kTile;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int line = blk_line<16>(lane, w);
   const uint32_t n0 = base + line * 256 + 4 * (lane & 15);
-  const uint32_t* u = J.ws + (size_t)(2 + gr) * N + base;
-  const uint32_t* a = J.a + ((size_t)c * J.L + i) * N + n0;
   uint4 raw[4], xs[4];
   BlkTw tw;
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) raw[kk] = ld4(u + RowGroup<16>::word(threadIdx.x, kk, 0));
+  for (int kk = 0; kk < 4; ++kk) raw[kk] = ld4(u + base + RowGroup<16>::word(threadIdx.x, kk, 0));
   tw.load(K.M.row_tw(K.T, i, blockIdx.x * 16 + line), K.M.blk_tw(i), lane);
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) xs[kk] = ld4(a + 64 * kk);
+  for (int kk = 0; kk < 4; ++kk) xs[kk] = ld4(a + n0 + 64 * kk);
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) RowGroup<16>::to_lds(s, threadIdx.x, kk, raw[kk]);
   __syncthreads();
@@ -1141,17 +1151,38 @@ __global__ __launch_bounds__(kWG) void r4_ntt_blks_combine(KsConst K, JobArg<RsJ
   wave_sync();
   blk_fwd_b(s, line, lane, tw, m);
   wave_sync();
-  const uint2 qi = ldc(K.rescale_inv + (size_t)J.L * K.T.L_max + i);
-  const OutRow out(J.out + ((size_t)c * L1 + i) * N);
+  const OutRow out(dst);
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     const uint4 v = csub4(blk_quad(s, line, 4 * (lane & 15) + 64 * kk), m.q2);  // [0, 2q): x + 2q - v < 3q
     const uint4 x = xs[kk];
-    out.st4(n0 + 64 * kk, make_uint4(csub(mul_shoup(x.x + m.q2 - v.x, qi.x, qi.y, m.q), m.q),
-                                     csub(mul_shoup(x.y + m.q2 - v.y, qi.x, qi.y, m.q), m.q),
-                                     csub(mul_shoup(x.z + m.q2 - v.z, qi.x, qi.y, m.q), m.q),
-                                     csub(mul_shoup(x.w + m.q2 - v.w, qi.x, qi.y, m.q), m.q)));
+    out.st4(n0 + 64 * kk, make_uint4(csub(mul_shoup(x.x + m.q2 - v.x, f.x, f.y, m.q), m.q),
+                                     csub(mul_shoup(x.y + m.q2 - v.y, f.x, f.y, m.q), m.q),
+                                     csub(mul_shoup(x.z + m.q2 - v.z, f.x, f.y, m.q), m.q),
+                                     csub(mul_shoup(x.w + m.q2 - v.w, f.x, f.y, m.q), m.q)));
   }
+}
+
+// Bound: memory (a, u in, out: 55 MB at N = 2^16, L = 36, both components).
+__global__ __launch_bounds__(kWG) void r4_ntt_blks_combine(KsConst K, JobArg<RsJob> JA) {
+  const RsJob J = JA.get(blockIdx.z);
+  const int L1 = J.L - 1;
+  const int gr = blockIdx.y;
+  if (gr >= 2 * L1) return;
+  const int c = gr / L1, i = gr % L1;
+  const size_t N = (size_t)1 << K.T.logN;
+  sub_scale_rows(K, i, J.ws + (size_t)(2 + gr) * N, J.a + ((size_t)c * J.L + i) * N,
+                 J.out + ((size_t)c * L1 + i) * N, ldc(K.rescale_inv + (size_t)J.L * K.T.L_max + i));
+}
+
+// ModDown alone (one component): the combine.
+__global__ __launch_bounds__(kWG) void kd_ntt_blks_combine(KsConst K, JobArg<KsJob> JA) {
+  const KsJob J = JA.get(blockIdx.z);
+  const int i = blockIdx.y;
+  if (i >= J.L) return;
+  const size_t N = (size_t)1 << K.T.logN;
+  const KsView V = ks_view(J, K, N);
+  sub_scale_rows(K, i, V.w + (size_t)i * N, J.a + (size_t)i * N, J.out + (size_t)i * N, ldc(K.pinv + i));
 }
 
 // ============================================================================
@@ -1585,6 +1616,20 @@ hipError_t ks_modup_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& 
   return hipGetLastError();
 }
 
+// ModDown alone: block pass of the P rows, the column kernel, the combine
+// (N = 2^16, L = 36: 57 us in six stand-alone kernels -> 28).
+template <int L1>
+hipError_t ks_moddown_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, const JobArg<KsJob>& jobs,
+                               int njobs, int Lmax, hipStream_t st) {
+  klaunch(c, -1, k1_intt_blks, dim3(c.N / kTile, c.k, njobs), st, K, jobs);
+  const int groups = conv_groups((long)(c.N / 512) * njobs, Lmax, sc.down_rows);
+  const hipError_t e =
+      conv_launch<L1, CONV_DOWN>(c, -1, c.k, dim3(c.N / 512, groups, njobs), st, K, jobs, groups);
+  if (e != hipSuccess) return e;
+  klaunch(c, -1, kd_ntt_blks_combine, dim3(c.N / kTile, Lmax, njobs), st, K, jobs);
+  return hipGetLastError();
+}
+
 template <int L1>
 hipError_t ks_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, const JobArg<KsJob>& jobs,
                        int njobs, int Lmax, bool with_modup, bool with_hoist, hipStream_t st,
@@ -1687,6 +1732,20 @@ hipError_t ks_modup_launch(const Ctx& c, const Ctx::Sched& sc, const JobArg<KsJo
     case 6: return ks_modup_launch_t<6>(c, sc, K, jobs, njobs, Lmax, st);
     case 7: return ks_modup_launch_t<7>(c, sc, K, jobs, njobs, Lmax, st);
     case 8: return ks_modup_launch_t<8>(c, sc, K, jobs, njobs, Lmax, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t ks_moddown_launch(const Ctx& c, const Ctx::Sched& sc, const JobArg<KsJob>& jobs, int njobs, int Lmax,
+                             hipStream_t st) {
+  if (njobs <= 0) return hipSuccess;
+  const KsConst K = make_const(c);
+  switch (c.logN - kBlockLog) {
+    case 4: return ks_moddown_launch_t<4>(c, sc, K, jobs, njobs, Lmax, st);
+    case 5: return ks_moddown_launch_t<5>(c, sc, K, jobs, njobs, Lmax, st);
+    case 6: return ks_moddown_launch_t<6>(c, sc, K, jobs, njobs, Lmax, st);
+    case 7: return ks_moddown_launch_t<7>(c, sc, K, jobs, njobs, Lmax, st);
+    case 8: return ks_moddown_launch_t<8>(c, sc, K, jobs, njobs, Lmax, st);
     default: return hipErrorInvalidValue;
   }
 }

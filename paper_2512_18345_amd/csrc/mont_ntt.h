@@ -126,17 +126,18 @@ __device__ __forceinline__ void load_top_tw(uint32_t tw[16], const uint32_t* tab
   }
 }
 
-// ----- column pass: 512 words (all N1 rows of C columns) per half wave ---------
-// The two halves of a wave hold the same columns of two limbs, so twiddles
-// and moduli are per lane; n is the lane's number in its half.
+// ----- column pass: 16 LANES words (all N1 rows of C columns) per LANES lanes --
+// LANES = 64: a wave holds C columns of one limb.  LANES = 32 (ColHalf): the
+// halves of a wave hold the same columns of two limbs, so twiddles and moduli
+// are per lane; n is the lane's number in its half.
 // Low layout: lane n = h C + c holds rows 16 h + j, j < 16, of column c.
 // High layout: lane n = r C + c holds rows 16 kh + (kl << E) + r as word
 // k = kh 2^(4-E) + kl, so the row bits above the low four are register bits.
-template <int LOGN1>
-struct ColHalf {
-  static constexpr int E = LOGN1 - 4;  // row bits above the low nibble
-  static constexpr int C = 32 >> E;    // columns of a tile
-  static constexpr int XCH = 17 * 32;  // exchange words of a half (one word of pad per 16 rows)
+template <int LOGN1, int LANES>
+struct ColPart {
+  static constexpr int E = LOGN1 - 4;     // row bits above the low nibble
+  static constexpr int C = LANES >> E;    // columns of a tile
+  static constexpr int XCH = 17 * LANES;  // exchange words (one word of pad per 16 rows)
 
   __device__ static __forceinline__ int high_at(int k) {
     return 17 * C * (k >> (4 - E)) + C * ((k & ((16 >> E) - 1)) << E);
@@ -210,16 +211,19 @@ struct ColHalf {
     wave_sync();
     uint4 q[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) q[k] = *reinterpret_cast<const uint4*>(x + 4 * (32 * k + n));
+    for (int k = 0; k < 4; ++k) q[k] = *reinterpret_cast<const uint4*>(x + 4 * (LANES * k + n));
     wave_sync();
     if (!on) return;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int owner = 8 * k + (n >> 2);
+      const int owner = LANES / 4 * k + (n >> 2);
       out.st4(row + lane_word(t, owner) + 4 * (((n & 3) - (owner >> 2)) & 3), q[k]);
     }
   }
 };
+
+template <int LOGN1>
+using ColHalf = ColPart<LOGN1, 32>;
 
 // ----- block pass: four rows of 256 words per wave ----------------------------
 // LDS tile of 16 rows (or four): word pos of line at line kBlkS + pos + pos / 16.

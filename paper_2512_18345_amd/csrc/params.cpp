@@ -108,9 +108,8 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
   const u64 N1 = N >> 8;
   const int logN1 = c.logN - 8;
   std::vector<ModC> mod(nP);
-  std::vector<uint2> tw((size_t)nP * N1), itw((size_t)nP * N1);
-  std::vector<uint2> ctw((size_t)nP * 256), ictw((size_t)nP * 256);
-  std::vector<uint2> twist((size_t)nP * N1 * 32), itwist((size_t)nP * N1 * 32);
+  std::vector<uint32_t> tw((size_t)nP * N1), itw((size_t)nP * N1);
+  std::vector<uint32_t> ctw((size_t)nP * 256), ictw((size_t)nP * 256);
   std::vector<uint32_t> mrow((size_t)nP * N1 * 32, 0), mirow((size_t)nP * N1 * 32, 0);
   // whole-limb tables of small rings: all N entries of the bit-reversed table
   const bool small_ring = c.logN == kSrLog;
@@ -133,8 +132,8 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
     // column pass: the first N1 entries of the bit-reversed table
     for (u64 e = 0; e < N1; ++e) {
       const uint32_t b = brv((uint32_t)e, c.logN);
-      tw[(size_t)i * N1 + e] = shoup(P(b), qi);
-      itw[(size_t)i * N1 + e] = shoup(PI(b), qi);
+      tw[(size_t)i * N1 + e] = mont(P(b), qi);
+      itw[(size_t)i * N1 + e] = mont(PI(b), qi);
     }
     if (small_ring)
       for (u64 e = 0; e < N; ++e) {
@@ -142,19 +141,17 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
         ftw[(size_t)i * N + e] = shoup(P(b), qi);
         fitw[(size_t)i * N + e] = shoup(PI(b), qi);
       }
-    // block pass (twisted): index 2^s + g -> psi^((N / 2^s) brv_s(g))
-    ctw[(size_t)i * 256] = ictw[(size_t)i * 256] = shoup(1, qi);
+    // block pass: index 2^s + g -> psi^((N / 2^s) brv_s(g))
+    ctw[(size_t)i * 256] = ictw[(size_t)i * 256] = mont(1, qi);
     for (int s = 0; s < 8; ++s)
       for (u64 g = 0; g < (1ull << s); ++g) {
         const u64 ex = (N >> s) * (s ? brv((uint32_t)g, s) : 0);
-        ctw[(size_t)i * 256 + (1u << s) + g] = shoup(P(ex), qi);
-        ictw[(size_t)i * 256 + (1u << s) + g] = shoup(PI(ex), qi);
+        ctw[(size_t)i * 256 + (1u << s) + g] = mont(P(ex), qi);
+        ictw[(size_t)i * 256 + (1u << s) + g] = mont(PI(ex), qi);
       }
-    // twist of block b: rho_b = psi^(2 brv(b) + 1)
+    // row b: its own twiddles for four stages, rho_b = psi^(2 brv(b) + 1) for the rest
     for (u64 b = 0; b < N1; ++b) {
       const u64 rho = 2 * (u64)brv((uint32_t)b, logN1) + 1;  // rho_b = psi^rho
-      uint2* t = &twist[((size_t)i * N1 + b) * 32];
-      uint2* ti = &itwist[((size_t)i * N1 + b) * 32];
       uint32_t* mr = &mrow[((size_t)i * N1 + b) * 32];
       uint32_t* mri = &mirow[((size_t)i * N1 + b) * 32];
       for (int s = 0; s < 4; ++s)
@@ -166,10 +163,6 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
       for (u64 j = 0; j < 16; ++j) {
         mr[16 + j] = mont(P(rho * j), qi);
         mri[16 + j] = mont(PI(rho * j), qi);
-        t[j] = shoup(P(rho * j), qi);
-        ti[j] = shoup(PI(rho * j), qi);
-        t[16 + j] = shoup(P(rho * 16 * j), qi);
-        ti[16 + j] = shoup(PI(rho * 16 * j), qi);
       }
     }
   }
@@ -253,23 +246,15 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
       rinv[(size_t)L * c.L_max + i] = shoup(invm(c.primes[L - 1] % qi, qi), qi);
     }
 
-  // Montgomery tables: the words of the Shoup tables times 2^32, the rows'
-  // own tables and the base-conversion constants, in one allocation
+  // the two-pass transforms' tables and the base-conversion constants times
+  // 2^32, in one allocation
   std::vector<uint32_t> all;
   std::vector<size_t> at;  // offset of each table, 64-word aligned
   auto begin = [&]() {
     all.resize((all.size() + 63) / 64 * 64, 0);
     at.push_back(all.size());
   };
-  auto per_prime = [&](const std::vector<uint2>& t, size_t n) {  // [nP][n]
-    begin();
-    for (size_t e = 0; e < t.size(); ++e) all.push_back(mont(t[e].x, c.primes[e / n]));
-  };
-  per_prime(tw, N1);
-  per_prime(itw, N1);
-  per_prime(ctw, 256);
-  per_prime(ictw, 256);
-  for (const std::vector<uint32_t>* t : {&mrow, &mirow}) {
+  for (const std::vector<uint32_t>* t : {&tw, &itw, &ctw, &ictw, &mrow, &mirow}) {
     begin();
     all.insert(all.end(), t->begin(), t->end());
   }
@@ -296,12 +281,6 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
   c.mont = MontTab{d + at[0], d + at[1], d + at[2], d + at[3], d + at[4],  d + at[5],
                    d + at[6], d + at[7], d + at[8], d + at[9], d + at[10]};
   if (!(err = upload(&c.d_mod, mod, code)).empty()) return err;
-  if (!(err = upload(&c.d_tw, tw, code)).empty()) return err;
-  if (!(err = upload(&c.d_itw, itw, code)).empty()) return err;
-  if (!(err = upload(&c.d_ctw, ctw, code)).empty()) return err;
-  if (!(err = upload(&c.d_ictw, ictw, code)).empty()) return err;
-  if (!(err = upload(&c.d_twist, twist, code)).empty()) return err;
-  if (!(err = upload(&c.d_itwist, itwist, code)).empty()) return err;
   if (small_ring) {
     if (!(err = upload(&c.d_ftw, ftw, code)).empty()) return err;
     if (!(err = upload(&c.d_fitw, fitw, code)).empty()) return err;
@@ -319,7 +298,7 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
 }
 
 void free_tables(Ctx& c) {
-  void* ptrs[] = {c.d_mod, c.d_tw, c.d_itw, c.d_ctw, c.d_ictw, c.d_twist, c.d_itwist, c.d_ftw, c.d_fitw,
+  void* ptrs[] = {c.d_mod, c.d_ftw, c.d_fitw,
                   c.d_mont, c.d_modup_scale, c.d_modup_T, c.d_modup_T_off,
                   c.d_moddown_scale, c.d_moddown_T, c.d_pinv, c.d_rescale_inv};
   for (void* p : ptrs)
