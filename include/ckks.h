@@ -294,15 +294,16 @@ int ckks_rescale(const ckks_ctx *ctx, const uint32_t *ct, int L, uint32_t *out, 
  *                    (0: never)
  *   ntt_shape        NTT tile / radix choices (Sec. III-C1 NTT kernels),
  *                    a bit mask: 1, 2 and 4 are accepted, without effect
- *                    (every transform pass has one shape); 8 = at N = 2^12, the whole key-switch as two
+ *                    (every transform pass has one shape); 8 = at N = 2^12
+ *                    and digit sizes 1 and 2, the whole key-switch as two
  *                    kernels that hold whole limbs in LDS (ModUp + inner
  *                    product per row and digit group, ModDown + epilogue per
- *                    output row) instead of the five-kernel pipeline (hoisted
- *                    rotations and batch plans with split != 0 keep the
- *                    five kernels).  Small grids keep their own
+ *                    output row) instead of the five-kernel pipeline (larger
+ *                    digits, hoisted rotations and batch plans with
+ *                    split != 0 keep the five kernels).  Small grids keep their own
  *                    shapes.  0..15.
- * Default {12, 6, 128, 0}; {12, 6, 128, 8} for N = 2^12.  The schedule is read when work is enqueued (and when
- * a graph batch is captured); changing it must not overlap calls on the
+ * Default {12, 6, 128, 0}; {12, 6, 128, 8} for N = 2^12.  The schedule is
+ * read when work is enqueued (and when a graph batch is captured); changing it must not overlap calls on the
  * context.  Every schedule gives bitwise the same results.
  */
 typedef struct ckks_schedule {

@@ -29,19 +29,13 @@ struct ModC {
   uint32_t pad;
 };
 
-// Per-prime constants, and the tables of the whole-limb transforms of small
-// rings (N = 2^kSrLog only, else null): ftw / fitw [nprimes][N], index m + i < N
-// -> psi^(+-brv_logN(m + i)) as (w, floor(w 2^32 / q)).
-constexpr int kSrLog = 12;
+// Per-prime constants and the ring.
+constexpr int kSrLog = 12;  // rings of this degree: whole-limb key-switch kernels
 struct DevTab {
   const ModC* mod;   // [nprimes]
-  const uint2* ftw;
-  const uint2* fitw;
   int logN;
   int L_max;
   __host__ __device__ int logN1() const { return logN - 8; }
-  __device__ const uint2* full_tw(int pi) const { return ftw + ((size_t)pi << logN); }
-  __device__ const uint2* full_itw(int pi) const { return fitw + ((size_t)pi << logN); }
 };
 
 // Tables of the two-pass transforms (mont_ntt.h) and of the base conversions,
@@ -85,19 +79,13 @@ struct Ctx {
 
   // device tables
   ModC* d_mod = nullptr;
-  uint2* d_ftw = nullptr;     // [nprimes][N], N = 2^kSrLog only
-  uint2* d_fitw = nullptr;
-  // ModUp at level L (1-based): per Q row i < L, (N^-1 * (D_j/q_i)^-1, Shoup) where j = i / alpha.
-  uint2* d_modup_scale = nullptr;     // [L_max + 1][L_max]
-  // ModUp BConv tables at level L, digit j: T[r][i] = (D_j / q_{j alpha + i}) mod prime(r),
-  // r over the L + k ModUp rows.  Offsets into one buffer.
-  uint32_t* d_modup_T = nullptr;
+  // Base conversions: the constants times 2^32 are in `mont`.  ModUp at level L
+  // (1-based): pre-multipliers N^-1 (D_j/q_i)^-1 at [L][i], tables T[r][i] =
+  // (D_j / q_{j alpha + i}) mod prime(r) over the L + k ModUp rows at offset
+  // modup_T_off of (L, j).  ModDown: N^-1 (P/p_m)^-1, T[i][m] = (P/p_m) mod q_i.
   std::vector<size_t> modup_T_off;    // index (L * beta_max + j)
   uint32_t* d_modup_T_off = nullptr;  // device copy of modup_T_off
-  // ModDown: P rows scale (N^-1 * (P/p_m)^-1, Shoup) indexed m; T_down[i][m] = (P/p_m) mod q_i;
   // P^-1 mod q_i with Shoup.
-  uint2* d_moddown_scale = nullptr;   // [k]
-  uint32_t* d_moddown_T = nullptr;    // [L_max][k]
   uint2* d_pinv = nullptr;            // [L_max]
   // Rescale at level L: q_{L-1}^-1 mod q_i (Shoup), i < L - 1.
   uint2* d_rescale_inv = nullptr;     // [L_max + 1][L_max]
@@ -136,7 +124,7 @@ struct Ctx {
   }
 
   DevTab tab() const {
-    return DevTab{d_mod, d_ftw, d_fitw, logN, L_max};
+    return DevTab{d_mod, logN, L_max};
   }
   RowMap rows(int L) const { return RowMap{L, L_max}; }
   int beta(int L) const { return (L + alpha - 1) / alpha; }

@@ -43,19 +43,14 @@ namespace {
 struct KsConst {
   DevTab T;
   int k, alpha, beta_max;
-  const uint2* modup_scale;
-  const uint32_t* modup_T;
   const uint32_t* modup_T_off;
-  const uint2* moddown_scale;
-  const uint32_t* moddown_T;
   const uint2* pinv;
   const uint2* rescale_inv;
   MontTab M;
 };
 
 KsConst make_const(const Ctx& c) {
-  return KsConst{c.tab(), c.k, c.alpha, c.beta_max(), c.d_modup_scale, c.d_modup_T,
-                 c.d_modup_T_off, c.d_moddown_scale, c.d_moddown_T, c.d_pinv, c.d_rescale_inv, c.mont};
+  return KsConst{c.tab(), c.k, c.alpha, c.beta_max(), c.d_modup_T_off, c.d_pinv, c.d_rescale_inv, c.mont};
 }
 
 // Scratch layout of one job (rows of N words): acc [2][R], [2][k] unused, w [2][L],
@@ -465,42 +460,42 @@ __device__ __forceinline__ TermQuad term_load(const KsJob& J, int L, int i, uint
   t.d = ld4((hm ? J.b + LN : J.a) + row + t.aq.src);
   return t;
 }
-// w comes in [0, 4q); x = acc + 2q - w < 3q < 2^32 after a correction.  HMULT
-// reduces x P^-1 and its products in one sum, at most 5 q^2 < 2^63.
+// Component c of the result for a quad.  w comes in [0, 4q); x = acc + 2q - w < 3q
+// < 2^32 after a correction.  HMULT reduces x P^-1 and its products in one sum,
+// at most 5 q^2 < 2^63.
+template <bool HOIST = false>
+__device__ __forceinline__ uint4 combine_comp(const KsConst& K, const KsJob& J, int c, int i, const ModC& mc,
+                                              const TermQuad& t, uint4 a, uint4 w) {
+  const MontQ m = mont_q(mc);
+  w = csub4(w, m.q2);
+  const uint4 x = make_uint4(a.x + m.q2 - w.x, a.y + m.q2 - w.y, a.z + m.q2 - w.z, a.w + m.q2 - w.w);
+  if (!HOIST && J.kind == KS_HMULT) {
+    const uint32_t pv = ldc(K.pinv + i).x;
+    uint64_t s[4] = {(uint64_t)x.x * pv, (uint64_t)x.y * pv, (uint64_t)x.z * pv, (uint64_t)x.w * pv};
+    if (c == 0) {
+      mac4(s, t.a, t.b);
+    } else {
+      mac4(s, t.a, t.d);
+      mac4(s, t.c, t.b);
+    }
+    return reduce4(s, mc);
+  }
+  const uint32_t pv = ldc(K.M.pinv + i);
+  const uint4 o = make_uint4(csub(mont_mul(x.x, pv, m), m.q), csub(mont_mul(x.y, pv, m), m.q),
+                             csub(mont_mul(x.z, pv, m), m.q), csub(mont_mul(x.w, pv, m), m.q));
+  if (c || (!HOIST && J.kind == KS_PLAIN)) return o;
+  const uint4 e = auto_turn(t.a, t.aq);
+  return make_uint4(csub(o.x + e.x, m.q), csub(o.y + e.y, m.q), csub(o.z + e.z, m.q), csub(o.w + e.w, m.q));
+}
 template <bool HOIST = false>
 __device__ __forceinline__ void combine_quad(const KsConst& K, const KsJob& J, int L, int i, uint32_t n, size_t N,
                                              const ModC& mc, const TermQuad& t, uint4 a0, uint4 a1, uint4 w0,
                                              uint4 w1) {
-  const MontQ m = mont_q(mc);
-  auto diff = [&](uint4 a, uint4 w) {
-    w = csub4(w, m.q2);
-    return make_uint4(a.x + m.q2 - w.x, a.y + m.q2 - w.y, a.z + m.q2 - w.z, a.w + m.q2 - w.w);
-  };
-  const uint4 x0 = diff(a0, w0), x1 = diff(a1, w1);
   const OutRow out0(J.out + (size_t)i * N), out1(J.out + ((size_t)L + i) * N);
-  if (!HOIST && J.kind == KS_HMULT) {
-    const uint32_t pv = ldc(K.pinv + i).x;
-    uint64_t t0[4] = {(uint64_t)x0.x * pv, (uint64_t)x0.y * pv, (uint64_t)x0.z * pv, (uint64_t)x0.w * pv};
-    uint64_t t1[4] = {(uint64_t)x1.x * pv, (uint64_t)x1.y * pv, (uint64_t)x1.z * pv, (uint64_t)x1.w * pv};
-    mac4(t0, t.a, t.b);
-    mac4(t1, t.a, t.d);
-    mac4(t1, t.c, t.b);
-    out0.st4(n, reduce4(t0, mc));
-    out1.st4(n, reduce4(t1, mc));
-    return;
-  }
-  const uint32_t pv = ldc(K.M.pinv + i);
-  auto scale = [&](uint4 x) {
-    return make_uint4(csub(mont_mul(x.x, pv, m), m.q), csub(mont_mul(x.y, pv, m), m.q),
-                      csub(mont_mul(x.z, pv, m), m.q), csub(mont_mul(x.w, pv, m), m.q));
-  };
-  uint4 o0 = scale(x0);
-  if (HOIST || J.kind != KS_PLAIN) {
-    const uint4 e = auto_turn(t.a, t.aq);
-    o0 = make_uint4(csub(o0.x + e.x, m.q), csub(o0.y + e.y, m.q), csub(o0.z + e.z, m.q), csub(o0.w + e.w, m.q));
-  }
+  const uint4 o0 = combine_comp<HOIST>(K, J, 0, i, mc, t, a0, w0);
+  const uint4 o1 = combine_comp<HOIST>(K, J, 1, i, mc, t, a1, w1);
   out0.st4(n, o0);
-  out1.st4(n, scale(x1));
+  out1.st4(n, o1);
 }
 
 // Q rows: ModDown's combine on the inner product where it stands, in the
@@ -1186,361 +1181,310 @@ __global__ __launch_bounds__(kWG) void kd_ntt_blks_combine(KsConst K, JobArg<KsJ
 }
 
 // ============================================================================
-// Small rings (N = 2^kSrLog = 4096): a whole limb fits one work-group's LDS,
-// so the two-pass NTT split -- and with it the five-kernel pipeline -- is not
-// needed.  A key-switch runs as two kernels of 1024-thread work-groups:
+// Small rings (N = 2^kSrLog = 4096): a whole limb fits one work-group, so the
+// column pass needs no kernel of its own -- and neither does the five-kernel
+// pipeline.  A key-switch runs as two kernels of 256 threads, 16 words each:
 //   S1  per (ModUp row t, group of digits): each non-digit limb of a digit
-//       transformed back whole in LDS, scaled, converted to row t (BConv),
-//       the sum transformed forward, times the key rows; the products summed
-//       over the group's digits -> one partial accumulator per group;
+//       transformed back whole, scaled, converted to row t (BConv), the sum
+//       transformed forward, times the key rows; the products summed over the
+//       group's digits -> one partial accumulator per group;
 //   S2  per (Q row i, component): the partials summed; ModDown -- the P rows'
-//       INTT whole in LDS, their conversion to q_i, its NTT -- combined with
-//       the accumulator, plus the job's epilogue term.
+//       INTT, their conversion to q_i, its NTT -- combined with the
+//       accumulator, plus the job's epilogue term.
 // The arithmetic is that of the five kernels (exact: the same residues).
 // Scratch of a job: the partials [groups][2][L + k][N] (at most kSrGroups = 4).
+// Bound: the chain of one work-group, four transforms of about 800 instructions
+// a wave with one barrier each.  With 1024 threads in radix-4 phases, six
+// barriers a transform and both 32 KiB twiddle tables staged in LDS, HMult at
+// L = 4 took 12.0 + 14.6 us, and 16 of them 23.4 + 14.8; now 10.2 + 10.3 and
+// 15.5 + 11.2.
 // ============================================================================
 constexpr int kSrN = 1 << kSrLog;
-constexpr int kSrT = kSrN / 4;  // threads: one radix-4 unit / one quad each
+static_assert(kSrN == kTile, "one 16-row group per limb");
+// A work-group transforms a digit's limbs, and ModDown's P rows (as many), one
+// after another, 6 us a limb in all, where the five kernels' time hardly
+// depends on their number: HMult at digit size 1 19 us against 29, 2: 25
+// against 31, 3: 32 against 31, 4: 38 against 31, 12: 89 against 36.
+constexpr int kSrDigit = 2;
 
 __device__ __forceinline__ int sr_per(int beta) { return (beta + kSrGroups - 1) / kSrGroups; }  // digits per group
 __device__ __forceinline__ int sr_groups(int beta) { return (beta + sr_per(beta) - 1) / sr_per(beta); }
 
-// Forward negacyclic NTT of the limb in s (natural coefficients in,
-// bit-reversed evaluations out) as six radix-4 phases; twiddle of group
-// (m, g) at tw[m + g].  Unit u of the phase on stages (ls, ls + 1) covers
-// a = 4 g t2 + i, a + t2, a + 2 t2, a + 3 t2 (t2 = N / (4 m), g = u / t2,
-// i = u % t2).  Words in [0, 4q) throughout (Harvey butterflies).
-__device__ __forceinline__ void sr_ntt(uint32_t* s, const uint2* tw, uint32_t q) {
-  const uint32_t q2 = 2 * q;
-  const int u = threadIdx.x;
-#pragma unroll
-  for (int ls = 0; ls < kSrLog; ls += 2) {
-    const int lt2 = kSrLog - ls - 2;  // log2 t2
-    const int m = 1 << ls;
-    const int g = u >> lt2, i = u & ((1 << lt2) - 1);
-    const int a = (g << (lt2 + 2)) + i, t2 = 1 << lt2;
-    uint32_t x0 = s[a], x1 = s[a + t2], x2 = s[a + 2 * t2], x3 = s[a + 3 * t2];
-    const uint2 w = tw[m + g], w0 = tw[2 * m + 2 * g], w1 = tw[2 * m + 2 * g + 1];
-    bfly_ct(x0, x2, w.x, w.y, q, q2);
-    bfly_ct(x1, x3, w.x, w.y, q, q2);
-    bfly_ct(x0, x1, w0.x, w0.y, q, q2);
-    bfly_ct(x2, x3, w1.x, w1.y, q, q2);
-    s[a] = x0;
-    s[a + t2] = x1;
-    s[a + 2 * t2] = x2;
-    s[a + 3 * t2] = x3;
-    __syncthreads();
+// The column pass of a whole limb is one 16-point network: thread c (of 256)
+// holds rows 0..15 of column c.
+struct SrTw {
+  BlkTw blk;
+  Words16 col;  // uniform
+  __device__ __forceinline__ void load(const KsConst& K, int pi, int line, int lane) {
+    blk.load(K.M.row_tw(K.T, pi, line), K.M.blk_tw(pi), lane);
+    col = ldc(reinterpret_cast<const Words16*>(K.M.col_tw(K.T, pi)));
   }
-}
-
-// Inverse (Gentleman-Sande, bit-reversed in, natural out, no N^-1), six
-// radix-4 phases: unit u of the phase on half-sizes (t, 2t) covers
-// a = 4 g t + i, a + t, a + 2t, a + 3t (g = u / t, i = u % t); the stage of
-// m = N / (2t) groups pairs (a, a + t) and (a + 2t, a + 3t), the next
-// (a, a + 2t) and (a + t, a + 3t).  Words in [0, 2q) throughout.
-__device__ __forceinline__ void sr_intt(uint32_t* s, const uint2* itw, uint32_t q) {
-  const uint32_t q2 = 2 * q;
-  const int u = threadIdx.x;
-#pragma unroll
-  for (int lt = 0; lt < kSrLog; lt += 2) {
-    const int m = kSrN >> (lt + 1);
-    const int g = u >> lt, i = u & ((1 << lt) - 1);
-    const int a = (g << (lt + 2)) + i, t = 1 << lt;
-    uint32_t x0 = s[a], x1 = s[a + t], x2 = s[a + 2 * t], x3 = s[a + 3 * t];
-    const uint2 w0 = itw[m + 2 * g], w1 = itw[m + 2 * g + 1], w = itw[(m >> 1) + g];
-    bfly_gs(x0, x1, w0.x, w0.y, q, q2);
-    bfly_gs(x2, x3, w1.x, w1.y, q, q2);
-    bfly_gs(x0, x2, w.x, w.y, q, q2);
-    bfly_gs(x1, x3, w.x, w.y, q, q2);
-    s[a] = x0;
-    s[a + t] = x1;
-    s[a + 2 * t] = x2;
-    s[a + 3 * t] = x3;
-    __syncthreads();
+  __device__ __forceinline__ void load_inv(const KsConst& K, int pi, int line, int lane) {
+    blk.load(K.M.row_itw(K.T, pi, line), K.M.blk_itw(pi), lane);
+    col = ldc(reinterpret_cast<const Words16*>(K.M.col_itw(K.T, pi)));
   }
-}
-
-// The quad at 4 threadIdx.x of row r of the polynomial a job key-switches
-// (evaluation domain): d, c1 c1' or sigma(c1).  Loaded raw (both factors of
-// the product) so that a prefetch does not wait for its data; the product is
-// taken by sr_switched_finish where the quad is used.
-struct SrRaw {
-  uint4 x, y;
-  AutoQuad aq;
 };
-// Branch-free (the kind selects addresses, every load is issued): a load in
-// a branch whose value merges after it makes the compiler wait for it there.
-// x: row r of d, the evaluations of c1 (HMult) or sigma(c1) gathered (HRot);
-// y: row r of c1' (HMult; otherwise x's row again, unused).
-__device__ __forceinline__ SrRaw sr_switched_load(const KsJob& J, int r) {
-  const size_t N = kSrN;
-  const uint32_t n = 4 * threadIdx.x;
-  const bool rot = J.kind == KS_HROT;
-  const uint32_t* src = J.a + (size_t)(J.kind == KS_PLAIN ? r : J.L + r) * N;
-  const uint32_t* src2 = J.kind == KS_HMULT ? J.b + (size_t)(J.L + r) * N : src;
-  SrRaw o;
-  o.aq = rot ? auto_quad(n, J.gal, kSrLog) : AutoQuad{n, false, false};
-  o.x = ld4(src + o.aq.src);
-  o.y = ld4(src2 + n);
-  return o;
+
+// The lane's four quads of its line (evaluations) -> the thread's column of
+// coefficients, times sc 2^-32, canonical.  s: a tile no wave still reads.
+__device__ __forceinline__ void sr_inverse(uint32_t v[16], uint32_t* s, const uint4 x[4], const SrTw& tw,
+                                           uint32_t sc, const MontQ& m, int line, int lane) {
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) blk_quad_store(s, line, 4 * (lane & 15) + 64 * kk, x[kk]);
+  wave_sync();
+  blk_inv_a(s, line, lane, tw.blk, m);
+  wave_sync();
+  blk_inv_b(s, line, lane, tw.blk, m);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 16; ++j) v[j] = s[blk_at(j, threadIdx.x)];
+  gs_stages<0, 4>(v, tw.col.w, m);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) v[j] = csub(mont_mul(v[j], sc, m), m.q);
 }
-__device__ __forceinline__ uint4 sr_switched_finish(const KsJob& J, const SrRaw& v, const ModC& m) {
-  if (J.kind != KS_HMULT) return auto_turn(v.x, v.aq);
-  return make_uint4(mulmod(v.x.x, v.y.x, m), mulmod(v.x.y, v.y.y, m), mulmod(v.x.z, v.y.z, m),
-                    mulmod(v.x.w, v.y.w, m));
+// The thread's column of coefficients (below 4q) -> the lane's quads of
+// evaluations, in [0, 4q).
+__device__ __forceinline__ void sr_forward(uint4 x[4], uint32_t* s, uint32_t v[16], const SrTw& tw, const MontQ& m,
+                                           int line, int lane) {
+  ct_stages<0, 4>(v, tw.col.w, m);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) s[blk_at(j, threadIdx.x)] = v[j];
+  __syncthreads();
+  blk_fwd_a(s, line, lane, tw.blk, m);
+  wave_sync();
+  blk_fwd_b(s, line, lane, tw.blk, m);
+  wave_sync();
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) x[kk] = blk_quad(s, line, 4 * (lane & 15) + 64 * kk);
 }
 
-// A thread's four twiddle pairs of a whole-limb table (words t, t + T, t + 2T, t + 3T).
-__device__ __forceinline__ void sr_load_tw(uint2 w[4], const uint2* __restrict__ src) {
+// The lane's quads (words n0 + 64 kk) of row r of the polynomial a job
+// key-switches (evaluation domain): d, c1 c1' or sigma(c1).  Loaded raw (both
+// factors of the product) so that a prefetch does not wait for its data; the
+// product is taken by finish where the quads are used.  Branch-free (the kind
+// selects addresses, every load is issued): a load in a branch whose value
+// merges after it makes the compiler wait for it there.
+struct SrRaw {
+  uint4 x[4], y[4];
+  AutoQuad aq[4];
+  __device__ __forceinline__ void load(const KsJob& J, int r, uint32_t n0) {
+    const size_t N = kSrN;
+    const bool rot = J.kind == KS_HROT;
+    const uint32_t* src = J.a + (size_t)(J.kind == KS_PLAIN ? r : J.L + r) * N;
+    const uint32_t* src2 = J.kind == KS_HMULT ? J.b + (size_t)(J.L + r) * N : src;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) w[k] = src[threadIdx.x + k * kSrT];
-}
-__device__ __forceinline__ void sr_put_tw(uint2* dst, const uint2 w[4]) {
+    for (int kk = 0; kk < 4; ++kk) {
+      const uint32_t n = n0 + 64 * kk;
+      aq[kk] = rot ? auto_quad(n, J.gal, kSrLog) : AutoQuad{n, false, false};
+      x[kk] = ld4(src + aq[kk].src);
+      y[kk] = ld4(src2 + n);
+    }
+  }
+  __device__ __forceinline__ void finish(const KsJob& J, const ModC& m, uint4 d[4]) const {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) dst[threadIdx.x + k * kSrT] = w[k];
-}
+    for (int kk = 0; kk < 4; ++kk)
+      d[kk] = J.kind != KS_HMULT
+                  ? auto_turn(x[kk], aq[kk])
+                  : make_uint4(mulmod(x[kk].x, y[kk].x, m), mulmod(x[kk].y, y[kk].y, m),
+                               mulmod(x[kk].z, y[kk].z, m), mulmod(x[kk].w, y[kk].w, m));
+  }
+};
 
 // S1.  The work-group's items are its digits' limbs in order (a digit row of
-// the switched polynomial is one item without transforms).  The loads of an
-// item -- its quad of the switched polynomial, its prime's inverse twiddles
-// and BConv constants, the digit's key words -- are issued one item ahead,
-// before the current item's transforms, so only the first item waits on
-// memory.
-__global__ __launch_bounds__(kSrT) void s1_modup_ip(KsConst K, JobArg<KsJob> JA) {
+// the switched polynomial is one item without transforms).  Two tiles in turn,
+// so that one barrier a transform is enough.
+// ONE: a single digit per group, so no accumulators.
+template <bool ONE>
+__global__ __launch_bounds__(kWG, ONE ? 2 : 1) void s1_modup_ip(KsConst K, JobArg<KsJob> JA) {
   const KsJob J = JA.get(blockIdx.z);
   const int L = J.L, R = L + K.k, beta = (L + K.alpha - 1) / K.alpha;
-  const int t = blockIdx.x, per = sr_per(beta), gi = blockIdx.y;
+  const int t = blockIdx.x, per = ONE ? 1 : sr_per(beta), gi = blockIdx.y;
   const int j0 = gi * per, j1 = min(beta, j0 + per);
   if (t >= R || j0 >= beta || J.kind > KS_HROT) return;
-  __shared__ __align__(16) uint32_t sd[kSrN];
-  __shared__ uint2 stw[kSrN], sitw[kSrN];
+  __shared__ __align__(16) uint32_t s[2 * kBlkTile];
   const size_t N = kSrN;
   const size_t KR = (size_t)K.T.L_max + K.k;
   const int pt = ks_pidx(t, L, K.T.L_max);
-  const ModC mt = ldc(K.T.mod + pt);
-  const uint32_t n = 4 * threadIdx.x;
-  // the first item of digit j: its first limb, or row t itself when t is one of the digit's rows
-  auto first_limb = [&](int j) { return (t >= j * K.alpha && t < min(j * K.alpha + K.alpha, L)) ? t : j * K.alpha; };
-  auto key_of = [&](int j, uint4& e0, uint4& e1) {
-    const uint32_t* k0 = J.key + ((size_t)j * 2 * KR + pt) * N + n;
-    e0 = ld4(k0);
-    e1 = ld4(k0 + KR * N);
-  };
-  // BConv constants of limb i of digit j: N^-1 (D_j / q_i)^-1 and [D_j / q_i]_{q_t}
-  auto consts_of = [&](int j, int i, uint2& sc, uint64_t& T) {
-    sc = ldc(K.modup_scale + (size_t)L * K.T.L_max + i);
-    T = ldc(K.modup_T + ldc(K.modup_T_off + (size_t)L * K.beta_max + j) + (size_t)t * K.alpha + (i - j * K.alpha));
-  };
-  int j = j0, i = first_limb(j0);
-  SrRaw x = sr_switched_load(J, i);
-  uint4 e0, e1;
-  uint2 iw[4], sc, fw[4];
-  uint64_t T;
-  key_of(j, e0, e1);
-  sr_load_tw(iw, K.T.full_itw(i));  // i < L: a Q prime's table
-  consts_of(j, i, sc, T);
-  sr_load_tw(fw, K.T.full_tw(pt));  // forward twiddles of q_t, issued last: their wait covers the rest
-  sr_put_tw(stw, fw);               // published by the first barrier
-  uint64_t a0[4] = {0, 0, 0, 0}, a1[4] = {0, 0, 0, 0};
-  uint64_t z0 = 0, z1 = 0, z2 = 0, z3 = 0;
-  for (;;) {
-    const int hi = min(j * K.alpha + K.alpha, L);
-    const bool own = i == t;
-    const bool last_of_digit = own || i == hi - 1;
-    int jn = j, in = i + 1;  // the next item
-    if (last_of_digit) {
-      jn = j + 1;
-      in = jn < j1 ? first_limb(jn) : -1;
-    }
-    // the next item's loads; the registers are written only when there is
-    // one (a load left in flight at the end would hold the wave until it lands)
-    SrRaw xn;
-    uint4 e0n, e1n;
-    uint2 iwn[4], scn;
-    uint64_t Tn;
-    if (in >= 0) {
-      xn = sr_switched_load(J, in);
-      key_of(jn, e0n, e1n);
-      sr_load_tw(iwn, K.T.full_itw(in));  // a Q prime's table (in < L)
-      consts_of(jn, in, scn, Tn);
-    }
-    uint4 v;
-    bool have_v = false;
+  const ModC mct = ldc(K.T.mod + pt);
+  const MontQ mt = mont_q(mct);
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  const uint32_t n0 = line * 256 + 4 * (lane & 15);
+  uint32_t* cur = s;
+  uint32_t* other = s + kBlkTile;
+  uint64_t a0[4][4], a1[4][4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a0[kk][e] = a1[kk][e] = 0;
+  for (int j = j0; j < j1; ++j) {
+    const int lo = j * K.alpha, hi = min(lo + K.alpha, L);
+    const bool own = t >= lo && t < hi;
+    const uint32_t* k0 = J.key + ((size_t)j * 2 * KR + pt) * N + n0;
+    const uint32_t* k1 = k0 + KR * N;
+    SrRaw x;
+    SrTw it, ft;
+    uint4 d[4], e0[4], e1[4];
+    const int first = own ? t : lo;
+    x.load(J, first, n0);
+    it.load_inv(K, first, line, lane);
+    ft.load(K, pt, line, lane);
+    auto keys = [&]() {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        e0[kk] = ld4(k0 + 64 * kk);
+        e1[kk] = ld4(k1 + 64 * kk);
+      }
+    };
     if (own) {
-      v = sr_switched_finish(J, x, mt);
-      have_v = true;
+      keys();
+      x.finish(J, mct, d);
     } else {
-      const ModC mi = ldc(K.T.mod + i);
-      const uint4 xi = sr_switched_finish(J, x, mi);
-      __syncthreads();  // the previous transform has been read out of LDS
-      sr_put_tw(sitw, iw);
-      *reinterpret_cast<uint4*>(sd + n) = xi;
-      __syncthreads();
-      sr_intt(sd, sitw, mi.q);
-      const uint4 y = *reinterpret_cast<const uint4*>(sd + n);
-      z0 += (uint64_t)csub(mul_shoup(y.x, sc.x, sc.y, mi.q), mi.q) * T;
-      z1 += (uint64_t)csub(mul_shoup(y.y, sc.x, sc.y, mi.q), mi.q) * T;
-      z2 += (uint64_t)csub(mul_shoup(y.z, sc.x, sc.y, mi.q), mi.q) * T;
-      z3 += (uint64_t)csub(mul_shoup(y.w, sc.x, sc.y, mi.q), mi.q) * T;
-      if (last_of_digit) {  // the digit's sum, mod q_t, transformed forward
-        __syncthreads();
-        *reinterpret_cast<uint4*>(sd + n) =
-            make_uint4(reduce64(z0, mt.q, mt.mu_hi, mt.mu_lo), reduce64(z1, mt.q, mt.mu_hi, mt.mu_lo),
-                       reduce64(z2, mt.q, mt.mu_hi, mt.mu_lo), reduce64(z3, mt.q, mt.mu_hi, mt.mu_lo));
-        z0 = z1 = z2 = z3 = 0;
-        __syncthreads();
-        sr_ntt(sd, stw, mt.q);
-        v = canon4(*reinterpret_cast<const uint4*>(sd + n), mt.q, 2 * mt.q);
-        have_v = true;
+      uint64_t z[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) z[c] = 0;
+      const uint32_t* T = K.M.modup_T + ldc(K.modup_T_off + (size_t)L * K.beta_max + j) + (size_t)t * K.alpha;
+      for (int i = lo; i < hi; ++i) {
+        const ModC mci = ldc(K.T.mod + i);
+        const uint32_t sc = ldc(K.M.modup_scale + (size_t)L * K.T.L_max + i), Ti = ldc(T + (i - lo));
+        if (i > lo) {
+          x.load(J, i, n0);
+          it.load_inv(K, i, line, lane);
+        }
+        x.finish(J, mci, d);
+        uint32_t v[16];
+        sr_inverse(v, cur, d, it, sc, mont_q(mci), line, lane);
+        uint32_t* sw = cur;
+        cur = other;
+        other = sw;
+#pragma unroll
+        for (int c = 0; c < 16; ++c) z[c] += (uint64_t)v[c] * Ti;
+      }
+      // the key words land during the forward transform (no earlier: the
+      // registers would not hold them beside the inverse one's)
+      __builtin_amdgcn_sched_barrier(0);
+      keys();
+      uint32_t v[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c)  // REDC (the table carries 2^32): below 4q, see kc_conv
+        v[c] = csub((uint32_t)(z[c] >> 32), mt.q2) + mt.q - __umulhi((uint32_t)z[c] * (0u - mt.qn), mt.q);
+      sr_forward(d, cur, v, ft, mt, line, lane);
+      uint32_t* sw = cur;
+      cur = other;
+      other = sw;
+      if (!ONE) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) d[kk] = canon4(d[kk], mt.q, mt.q2);
       }
     }
-    if (have_v) {
-      a0[0] += (uint64_t)v.x * e0.x;
-      a0[1] += (uint64_t)v.y * e0.y;
-      a0[2] += (uint64_t)v.z * e0.z;
-      a0[3] += (uint64_t)v.w * e0.w;
-      a1[0] += (uint64_t)v.x * e1.x;
-      a1[1] += (uint64_t)v.y * e1.y;
-      a1[2] += (uint64_t)v.z * e1.z;
-      a1[3] += (uint64_t)v.w * e1.w;
-      if (((j - j0) & 7) == 7) {  // canonical products < 2^60: fold every eighth digit
+    // (ONE: a word below 4q times a key word, reduced at once)
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      mac4(a0[kk], d[kk], e0[kk]);
+      mac4(a1[kk], d[kk], e1[kk]);
+    }
+    if (ONE) break;
+    if (((j - j0) & 7) == 7) {  // canonical products < 2^60: fold every eighth digit
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          a0[e] = reduce64(a0[e], mt.q, mt.mu_hi, mt.mu_lo);
-          a1[e] = reduce64(a1[e], mt.q, mt.mu_hi, mt.mu_lo);
+          a0[kk][e] = reduce64(a0[kk][e], mct.q, mct.mu_hi, mct.mu_lo);
+          a1[kk][e] = reduce64(a1[kk][e], mct.q, mct.mu_hi, mct.mu_lo);
         }
-      }
     }
-    if (in < 0) break;
-    j = jn;
-    i = in;
-    x = xn;
-    e0 = e0n;
-    e1 = e1n;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) iw[k] = iwn[k];
-    sc = scn;
-    T = Tn;
   }
-  uint32_t* p0 = J.ws + ((size_t)(2 * gi) * R + t) * N + n;
-  uint32_t* p1 = p0 + (size_t)R * N;
-  st4(p0, make_uint4(reduce64(a0[0], mt.q, mt.mu_hi, mt.mu_lo), reduce64(a0[1], mt.q, mt.mu_hi, mt.mu_lo),
-                     reduce64(a0[2], mt.q, mt.mu_hi, mt.mu_lo), reduce64(a0[3], mt.q, mt.mu_hi, mt.mu_lo)));
-  st4(p1, make_uint4(reduce64(a1[0], mt.q, mt.mu_hi, mt.mu_lo), reduce64(a1[1], mt.q, mt.mu_hi, mt.mu_lo),
-                     reduce64(a1[2], mt.q, mt.mu_hi, mt.mu_lo), reduce64(a1[3], mt.q, mt.mu_hi, mt.mu_lo)));
+  const OutRow p0(J.ws + ((size_t)(2 * gi) * R + t) * N), p1(J.ws + ((size_t)(2 * gi + 1) * R + t) * N);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    p0.st4(n0 + 64 * kk, reduce4(a0[kk], mct));
+    p1.st4(n0 + 64 * kk, reduce4(a1[kk], mct));
+  }
 }
 
-// The groups' partials (at most four) at the thread's quad of row r, loaded
-// raw: group indices past `groups` repeat the last group and are dropped by
-// sr_partials_sum.
-__device__ __forceinline__ void sr_partials_load(uint4 v[4], const uint32_t* ws, int groups, int c, int R, int r) {
-  const size_t N = kSrN;
-  const uint32_t n = 4 * threadIdx.x;
+// The groups' partials (at most four) at the lane's quads of row r, summed: a
+// sum of four canonical words stays below 4q < 2^32.  Group indices past
+// `groups` repeat the last group and are dropped.
+struct SrPartials {
+  uint4 v[4][4];
+  __device__ __forceinline__ void load(const uint32_t* ws, int groups, int c, int R, int r, uint32_t n0) {
+    const size_t N = kSrN;
 #pragma unroll
-  for (int g = 0; g < 4; ++g) v[g] = ld4(ws + ((size_t)(2 * min(g, groups - 1) + c) * R + r) * N + n);
-}
-__device__ __forceinline__ uint4 sr_partials_sum(const uint4 v[4], int groups, uint32_t q) {
-  uint4 s = v[0];  // canonical partials: the sum of four stays below 4q < 2^32
+    for (int g = 0; g < 4; ++g)
 #pragma unroll
-  for (int g = 1; g < 4; ++g) {
-    const uint32_t k = g < groups ? 0xffffffffu : 0u;
-    s.x += v[g].x & k;
-    s.y += v[g].y & k;
-    s.z += v[g].z & k;
-    s.w += v[g].w & k;
+      for (int kk = 0; kk < 4; ++kk)
+        v[g][kk] = ld4(ws + ((size_t)(2 * min(g, groups - 1) + c) * R + r) * N + n0 + 64 * kk);
   }
-  return canon4(s, q, 2 * q);
-}
+  __device__ __forceinline__ uint4 sum(int kk, int groups, uint32_t q) const {
+    uint4 a = v[0][kk];
+#pragma unroll
+    for (int g = 1; g < 4; ++g) {
+      const uint32_t on = g < groups ? 0xffffffffu : 0u;
+      a.x += v[g][kk].x & on;
+      a.y += v[g][kk].y & on;
+      a.z += v[g][kk].z & on;
+      a.w += v[g][kk].w & on;
+    }
+    return canon4(a, q, 2 * q);
+  }
+};
 
-// S2.  Every load is issued at the start (the next P row's during the
-// current P row's transform): q_i's forward twiddles, the accumulator's
-// partials at row i, the epilogue operands, the first P row's partials and
-// inverse twiddles.
-__global__ __launch_bounds__(kSrT) void s2_moddown(KsConst K, JobArg<KsJob> JA) {
+__global__ __launch_bounds__(kWG, 2) void s2_moddown(KsConst K, JobArg<KsJob> JA) {
   const KsJob J = JA.get(blockIdx.z);
   const int L = J.L, R = L + K.k, beta = (L + K.alpha - 1) / K.alpha;
   const int i = blockIdx.x, c = blockIdx.y, groups = sr_groups(beta);
   if (i >= L || J.kind > KS_HROT) return;
-  __shared__ __align__(16) uint32_t sd[kSrN];
-  __shared__ uint2 stw[kSrN], sitw[kSrN];
-  const size_t N = kSrN, Lz = L;
-  const uint32_t n = 4 * threadIdx.x;
-  const ModC mi = ldc(K.T.mod + i);
-  const uint32_t q = mi.q, q2 = 2 * q;
-  uint2 fw[4], iw[4];
-  sr_load_tw(fw, K.T.full_tw(i));
-  uint4 pa[4], px[4];
-  sr_partials_load(px, J.ws, groups, c, R, L);
-  sr_load_tw(iw, K.T.full_itw(K.T.L_max));
-  sr_partials_load(pa, J.ws, groups, c, R, i);
-  // the epilogue operands, branch-free (as in sr_switched_load): c0, c0', c1,
-  // c1' at row i (HMult: c0 c0' / c0 c1' + c1 c0'); sigma(c0) gathered (HRot, c = 0)
-  const bool hm = J.kind == KS_HMULT, rot = J.kind == KS_HROT && c == 0;
-  const uint32_t* ra = J.a + i * N;
-  const uint32_t* rb = hm ? J.b + i * N : ra;
-  const uint32_t* rc = hm ? J.a + (Lz + i) * N : ra;
-  const uint32_t* rd = hm ? J.b + (Lz + i) * N : ra;
-  const AutoQuad aq = rot ? auto_quad(n, J.gal, kSrLog) : AutoQuad{n, false, false};
-  const uint4 ea = ld4(ra + aq.src);
-  const uint4 eb = ld4(rb + n), ec = ld4(rc + n), ed = ld4(rd + n);
-  sr_put_tw(stw, fw);  // published by the first barrier below
+  __shared__ __align__(16) uint32_t s[2 * kBlkTile];
+  const size_t N = kSrN;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int line = blk_line<16>(lane, w);
+  const uint32_t n0 = line * 256 + 4 * (lane & 15);
+  const ModC mc = ldc(K.T.mod + i);
+  const MontQ m = mont_q(mc);
+  uint32_t* cur = s;
+  uint32_t* other = s + kBlkTile;
   // ModDown: w = sum_m x_m [P / p_m]_{q_i}, x_m = INTT(acc P row m) N^-1 (P / p_m)^-1
-  uint64_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
+  uint64_t z[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) z[e] = 0;
+  uint4 x[4];
   for (int mm = 0; mm < K.k; ++mm) {
     const int pm = K.T.L_max + mm;
-    const ModC mp = ldc(K.T.mod + pm);
-    const uint2 sc = ldc(K.moddown_scale + mm);
-    const uint64_t T = ldc(K.moddown_T + (size_t)i * K.k + mm);
-    const bool more = mm + 1 < K.k;
-    uint4 pxn[4];
-    uint2 iwn[4];
-    if (more) {  // the next P row's loads
-      sr_partials_load(pxn, J.ws, groups, c, R, L + mm + 1);
-      sr_load_tw(iwn, K.T.full_itw(pm + 1));
-    }
-    const uint4 x = sr_partials_sum(px, groups, mp.q);
-    __syncthreads();  // the previous P row has been read out of LDS
-    sr_put_tw(sitw, iw);
-    *reinterpret_cast<uint4*>(sd + n) = x;
-    __syncthreads();
-    sr_intt(sd, sitw, mp.q);
-    const uint4 y = *reinterpret_cast<const uint4*>(sd + n);
-    w0 += (uint64_t)csub(mul_shoup(y.x, sc.x, sc.y, mp.q), mp.q) * T;
-    w1 += (uint64_t)csub(mul_shoup(y.y, sc.x, sc.y, mp.q), mp.q) * T;
-    w2 += (uint64_t)csub(mul_shoup(y.z, sc.x, sc.y, mp.q), mp.q) * T;
-    w3 += (uint64_t)csub(mul_shoup(y.w, sc.x, sc.y, mp.q), mp.q) * T;
-    if (more) {
+    const ModC mcp = ldc(K.T.mod + pm);
+    const uint32_t sc = ldc(K.M.moddown_scale + mm), T = ldc(K.M.moddown_T + (size_t)i * K.k + mm);
+    SrPartials px;
+    px.load(J.ws, groups, c, R, L + mm, n0);
+    SrTw it;
+    it.load_inv(K, pm, line, lane);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        px[k] = pxn[k];
-        iw[k] = iwn[k];
-      }
-    }
+    for (int kk = 0; kk < 4; ++kk) x[kk] = px.sum(kk, groups, mcp.q);
+    uint32_t v[16];
+    sr_inverse(v, cur, x, it, sc, mont_q(mcp), line, lane);
+    uint32_t* sw = cur;
+    cur = other;
+    other = sw;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) z[e] += (uint64_t)v[e] * T;
   }
-  const uint2 pv = ldc(K.pinv + i);
-  __syncthreads();
-  *reinterpret_cast<uint4*>(sd + n) = make_uint4(reduce64(w0, q, mi.mu_hi, mi.mu_lo), reduce64(w1, q, mi.mu_hi, mi.mu_lo),
-                                                 reduce64(w2, q, mi.mu_hi, mi.mu_lo), reduce64(w3, q, mi.mu_hi, mi.mu_lo));
-  __syncthreads();
-  sr_ntt(sd, stw, q);
-  const uint4 w = csub4(*reinterpret_cast<const uint4*>(sd + n), q2);  // [0, 2q)
-  const uint4 a = sr_partials_sum(pa, groups, q);
-  uint4 d = rot ? auto_turn(ea, aq) : make_uint4(0, 0, 0, 0);
-  if (hm) {
-    if (c == 0) {
-      d = make_uint4(mulmod(ea.x, eb.x, mi), mulmod(ea.y, eb.y, mi), mulmod(ea.z, eb.z, mi), mulmod(ea.w, eb.w, mi));
-    } else {
-      d = make_uint4(reduce64((uint64_t)ea.x * ed.x + (uint64_t)ec.x * eb.x, q, mi.mu_hi, mi.mu_lo),
-                     reduce64((uint64_t)ea.y * ed.y + (uint64_t)ec.y * eb.y, q, mi.mu_hi, mi.mu_lo),
-                     reduce64((uint64_t)ea.z * ed.z + (uint64_t)ec.z * eb.z, q, mi.mu_hi, mi.mu_lo),
-                     reduce64((uint64_t)ea.w * ed.w + (uint64_t)ec.w * eb.w, q, mi.mu_hi, mi.mu_lo));
-    }
-  }
-  const uint32_t o0 = csub(mul_shoup(a.x + q2 - w.x, pv.x, pv.y, q), q);
-  const uint32_t o1 = csub(mul_shoup(a.y + q2 - w.y, pv.x, pv.y, q), q);
-  const uint32_t o2 = csub(mul_shoup(a.z + q2 - w.z, pv.x, pv.y, q), q);
-  const uint32_t o3 = csub(mul_shoup(a.w + q2 - w.w, pv.x, pv.y, q), q);
-  st4(J.out + ((size_t)c * Lz + i) * N + n, make_uint4(csub(o0 + d.x, q), csub(o1 + d.y, q), csub(o2 + d.z, q), csub(o3 + d.w, q)));
+  // what the end needs, to land during the forward transform (no earlier: the
+  // registers would not hold it beside the inverse ones)
+  __builtin_amdgcn_sched_barrier(0);
+  SrTw ft;
+  SrPartials pa;
+  TermQuad term[4];
+  ft.load(K, i, line, lane);
+  pa.load(J.ws, groups, c, R, i, n0);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) term[kk] = term_load(J, L, i, n0 + 64 * kk, N, kSrLog);
+  uint32_t v[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+    v[e] = csub((uint32_t)(z[e] >> 32), m.q2) + m.q - __umulhi((uint32_t)z[e] * (0u - m.qn), m.q);
+  sr_forward(x, cur, v, ft, m, line, lane);
+  const OutRow out(J.out + ((size_t)c * L + i) * N);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+    out.st4(n0 + 64 * kk, combine_comp(K, J, c, i, mc, term[kk], pa.sum(kk, groups, m.q), x[kk]));
 }
 }  // namespace
 
@@ -1637,13 +1581,18 @@ hipError_t ks_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, con
   const int tiles = c.N / kTile;
   hipError_t e;
   if constexpr (L1 + kBlockLog == kSrLog) {
-    // small ring: two kernels on whole limbs (plain, HMult and HRot jobs)
-    if ((sc.ntt_shape & kShapeWholeLimb) && with_modup && !with_hoist && whole_limb) {
+    // small ring: two kernels on whole limbs (plain, HMult and HRot jobs), for
+    // digits of at most kSrDigit limbs
+    if ((sc.ntt_shape & kShapeWholeLimb) && c.alpha <= kSrDigit && with_modup && !with_hoist && whole_limb) {
       // every job splits its own digits into sr_groups(beta) <= min(beta, kSrGroups)
       // groups, so the grid covers min(bmax, kSrGroups) (not the largest job's count)
       const int groups = std::min(c.beta(Lmax), kSrGroups);
-      klaunch_b(c, CKKS_STAGE_NTT_IP, s1_modup_ip, dim3(Lmax + c.k, groups, njobs), kSrT, st, K, jobs);
-      klaunch_b(c, CKKS_STAGE_NTT_COMBINE, s2_moddown, dim3(Lmax, 2, njobs), kSrT, st, K, jobs);
+      const dim3 g1(Lmax + c.k, groups, njobs);
+      if (c.beta(Lmax) <= kSrGroups)
+        klaunch(c, CKKS_STAGE_NTT_IP, s1_modup_ip<true>, g1, st, K, jobs);
+      else
+        klaunch(c, CKKS_STAGE_NTT_IP, s1_modup_ip<false>, g1, st, K, jobs);
+      klaunch_b(c, CKKS_STAGE_NTT_COMBINE, s2_moddown, dim3(Lmax, 2, njobs), kWG, st, K, jobs);
       return hipGetLastError();
     }
   }

@@ -114,6 +114,10 @@ __device__ __forceinline__ void load_node_tw(uint32_t tw[16], const uint32_t* ta
   tw[14] = e.z;
   tw[15] = e.w;
 }
+// 16 words read at once, the same for every lane.
+struct Words16 {
+  uint32_t w[16];
+};
 // The first 16 words of a table.
 __device__ __forceinline__ void load_top_tw(uint32_t tw[16], const uint32_t* tab) {
 #pragma unroll

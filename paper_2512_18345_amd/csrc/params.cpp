@@ -111,9 +111,6 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
   std::vector<uint32_t> tw((size_t)nP * N1), itw((size_t)nP * N1);
   std::vector<uint32_t> ctw((size_t)nP * 256), ictw((size_t)nP * 256);
   std::vector<uint32_t> mrow((size_t)nP * N1 * 32, 0), mirow((size_t)nP * N1 * 32, 0);
-  // whole-limb tables of small rings: all N entries of the bit-reversed table
-  const bool small_ring = c.logN == kSrLog;
-  std::vector<uint2> ftw(small_ring ? (size_t)nP * N : 0), fitw(small_ring ? (size_t)nP * N : 0);
   for (int i = 0; i < nP; ++i) {
     const u64 qi = c.primes[i];
     const u64 psi = min_root(qi, N);
@@ -135,12 +132,6 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
       tw[(size_t)i * N1 + e] = mont(P(b), qi);
       itw[(size_t)i * N1 + e] = mont(PI(b), qi);
     }
-    if (small_ring)
-      for (u64 e = 0; e < N; ++e) {
-        const uint32_t b = brv((uint32_t)e, c.logN);
-        ftw[(size_t)i * N + e] = shoup(P(b), qi);
-        fitw[(size_t)i * N + e] = shoup(PI(b), qi);
-      }
     // block pass: index 2^s + g -> psi^((N / 2^s) brv_s(g))
     ctw[(size_t)i * 256] = ictw[(size_t)i * 256] = mont(1, qi);
     for (int s = 0; s < 8; ++s)
@@ -281,16 +272,8 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
   c.mont = MontTab{d + at[0], d + at[1], d + at[2], d + at[3], d + at[4],  d + at[5],
                    d + at[6], d + at[7], d + at[8], d + at[9], d + at[10]};
   if (!(err = upload(&c.d_mod, mod, code)).empty()) return err;
-  if (small_ring) {
-    if (!(err = upload(&c.d_ftw, ftw, code)).empty()) return err;
-    if (!(err = upload(&c.d_fitw, fitw, code)).empty()) return err;
-  }
-  if (!(err = upload(&c.d_modup_scale, mscale, code)).empty()) return err;
-  if (!(err = upload(&c.d_modup_T, mT, code)).empty()) return err;
   std::vector<uint32_t> toff(c.modup_T_off.begin(), c.modup_T_off.end());
   if (!(err = upload(&c.d_modup_T_off, toff, code)).empty()) return err;
-  if (!(err = upload(&c.d_moddown_scale, dscale, code)).empty()) return err;
-  if (!(err = upload(&c.d_moddown_T, dT, code)).empty()) return err;
   if (!(err = upload(&c.d_pinv, pinv, code)).empty()) return err;
   if (!(err = upload(&c.d_rescale_inv, rinv, code)).empty()) return err;
   *code = CKKS_OK;
@@ -298,9 +281,7 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
 }
 
 void free_tables(Ctx& c) {
-  void* ptrs[] = {c.d_mod, c.d_ftw, c.d_fitw,
-                  c.d_mont, c.d_modup_scale, c.d_modup_T, c.d_modup_T_off,
-                  c.d_moddown_scale, c.d_moddown_T, c.d_pinv, c.d_rescale_inv};
+  void* ptrs[] = {c.d_mod, c.d_mont, c.d_modup_T_off, c.d_pinv, c.d_rescale_inv};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
 }
