@@ -568,18 +568,40 @@ __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> J
 #pragma unroll
     for (int i = 0; i < 4; ++i) a0[kk][i] = a1[kk][i] = 0;
 
+  // hoisted rotation: sigma_g applied to the shared ModUp rows (a gather).  A
+  // digit's words are requested a digit ahead, its key words with them: nothing
+  // else would cover their latency (20 digits at N = 2^12, eight rotations: P
+  // rows 57 -> 25 us, Q rows 52 -> 34).
+  AutoQuad aq[4];
+  uint4 nv[4], ne0[4], ne1[4];
+  auto hoist_load = [&](int j) {
+    const uint32_t* Mrow = J.b + ((size_t)j * V.R + r) * N;
+    const uint32_t* k0 = J.key + ((size_t)j * 2 * KR + pi) * N + n0;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      nv[kk] = ld4(Mrow + aq[kk].src);
+      ne0[kk] = ld4nt(k0 + 64 * kk);
+      ne1[kk] = ld4nt(k0 + KR * N + 64 * kk);
+    }
+  };
+  if (HOIST) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) aq[kk] = auto_quad(n0 + 64 * kk, J.gal, logN);
+    hoist_load(0);
+  }
   for (int j = 0; j < V.beta; ++j) {
     const int lo = j * K.alpha, hi = min(lo + K.alpha, V.L);
-    uint4 v[4];
+    uint4 v[4], e0[4], e1[4];
     if (HOIST) {
-      // hoisted rotation: sigma_g applied to the shared ModUp rows (a gather)
-      const uint32_t* Mrow = J.b + ((size_t)j * V.R + r) * N;
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        const uint32_t n = n0 + 64 * kk;
-        const AutoQuad aq = auto_quad(n, J.gal, logN);
-        v[kk] = auto_turn(ld4(Mrow + aq.src), aq);
+        v[kk] = nv[kk];
+        e0[kk] = ne0[kk];
+        e1[kk] = ne1[kk];
       }
+      hoist_load(min(j + 1, V.beta - 1));
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) v[kk] = auto_turn(v[kk], aq[kk]);
     } else if (r >= lo && r < hi) {
       // digit rows are the switched polynomial itself (kept by K1 unless it is the input)
       const uint32_t* drow = (J.kind == KS_PLAIN ? J.a : V.de) + (size_t)r * N + n0;
@@ -599,12 +621,18 @@ __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> J
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) v[kk] = canon4(blk_quad(s, line, 4 * (lane & 15) + 64 * kk), m.q, m.q2);
     }
-    const uint32_t* k0 = J.key + ((size_t)j * 2 * KR + pi) * N + n0;
-    const uint32_t* k1 = k0 + KR * N;
+    if (!HOIST) {
+      const uint32_t* k0 = J.key + ((size_t)j * 2 * KR + pi) * N + n0;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        e0[kk] = ld4(k0 + 64 * kk);
+        e1[kk] = ld4(k0 + KR * N + 64 * kk);
+      }
+    }
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      mac4(a0[kk], v[kk], HOIST ? ld4nt(k0 + 64 * kk) : ld4(k0 + 64 * kk));
-      mac4(a1[kk], v[kk], HOIST ? ld4nt(k1 + 64 * kk) : ld4(k1 + 64 * kk));
+      mac4(a0[kk], v[kk], e0[kk]);
+      mac4(a1[kk], v[kk], e1[kk]);
     }
     // Each product of canonical words is below q^2 < 2^60, so 16 of them fit
     // a 64-bit sum; chains of more digits (digit size 1 allows up to 63) fold
