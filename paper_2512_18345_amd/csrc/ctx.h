@@ -62,6 +62,9 @@ struct MontTab {
   }
 };
 
+// A word below 2^31 - 2^23 as four signed bytes, sum b_d 2^(8 d).
+__host__ __device__ inline uint32_t signed_bytes(uint32_t v) { return (v + 0x808080u) ^ 0x808080u; }
+
 // Rows of a launch: row r of the data is prime index pidx(r).
 struct RowMap {
   int L;       // rows [0, L) are q_0..q_{L-1}
@@ -84,7 +87,7 @@ struct Ctx {
   // (D_j / q_{j alpha + i}) mod prime(r) over the L + k ModUp rows at offset
   // modup_T_off of (L, j).  ModDown: N^-1 (P/p_m)^-1, T[i][m] = (P/p_m) mod q_i.
   std::vector<size_t> modup_T_off;    // index (L * beta_max + j)
-  uint32_t* d_modup_T_off = nullptr;  // device copy of modup_T_off
+  uint32_t* d_modup_T_off = nullptr;  // modup_T_off in words, then again in table rows
   // P^-1 mod q_i with Shoup.
   uint2* d_pinv = nullptr;            // [L_max]
   // Rescale at level L: q_{L-1}^-1 mod q_i (Shoup), i < L - 1.
@@ -92,6 +95,10 @@ struct Ctx {
 
   MontTab mont{};
   uint32_t* d_mont = nullptr;         // every table of `mont`, one allocation
+  // In it too, for conversions of more than four limbs: the tables in signed
+  // bytes, four words an entry.  Word [row][e][i], a row's limbs padded to a
+  // multiple of four, holds byte e of T[row][i] 2^(32 + 8 d) mod q in its byte d.
+  const uint32_t *modup_bytes = nullptr, *moddown_bytes = nullptr;
 
   // kernel tracing (ckks_trace_begin / ckks_trace_end)
   struct Trace {

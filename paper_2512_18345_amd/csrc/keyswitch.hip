@@ -222,20 +222,31 @@ __global__ __launch_bounds__(kWG) void k1_intt_blks(KsConst K, JobArg<KsJob> JA)
 // from a counter, so that an odd number of rows or waves per SIMD does not
 // leave one idle.  Each group of output rows repeats the input transforms, so
 // a launch uses one group unless its work-groups would not fill the chip
-// (conv_groups).  Bound: vector arithmetic, about 900 instructions a wave for
-// a pair of rows (a multiply-add per input limb and half a transform a word)
-// and 650 for a pair of inputs: 78% of the issue slots at 16 rotations.
-// N = 2^16, L = 36, 12 + 12 limbs: ModUp 43.5 us in three kernels -> 28.4,
-// ModDown 32.1 -> 19.9; ModDown of 16 rotations 274 -> 202.  Two limbs a wave
-// instead of one (tiles of 1024 words, half the work-groups, so twice the
-// groups): 34.8 -> 28.4 and 24.1 -> 19.9.
+// (conv_groups).
+// The conversion of more than four limbs runs on the matrix cores, in whole
+// numbers: inputs and table as four signed bytes each, the table's already
+// times 2^(8 d) mod q for the input's byte d (modup_bytes), so that one product
+// of 16 x 64 by 64 x 16 bytes gives the four byte sums of up to 16 limbs for 64
+// words, and the word's sum mod q is these times 1, 2^8, 2^16 and 2^24: eight
+// vector instructions a word instead of a multiply-add per limb and four.  At
+// four limbs or fewer the multiply-adds are no more than that.
+// Bound: vector arithmetic, 570 instructions a wave for a pair of rows (half a
+// transform a word is 450 of them) and 650 for a pair of inputs.
+// N = 2^16, L = 36, 12 + 12 limbs: ModUp 43.5 us in three kernels -> 28.4 with
+// multiply-adds -> 26.3, ModDown 32.1 -> 18.0 -> 16.9; HMult and rescale
+// together 234.8 -> 226.9 us by the matrix cores, 16 rotations 633 -> 620.  Two
+// limbs a wave instead of one (tiles of 1024 words, half the work-groups, so
+// twice the groups): 34.8 -> 28.4 and 24.1 -> 19.9.
+using i32x4 = int __attribute__((ext_vector_type(4)));
 enum ConvMode : int { CONV_UP = 0, CONV_DOWN = 1 };
 constexpr int kConvWaves = 8;
 
 template <int LOGN1, int MODE, int NY>
-__global__ __launch_bounds__(64 * kConvWaves, 4) void kc_conv(KsConst K, JobArg<KsJob> JA, int groups) {
+__global__ __launch_bounds__(64 * kConvWaves, 4) void kc_conv(KsConst K, JobArg<KsJob> JA, int groups,
+                                                              const uint32_t* bytes) {
   using CH = ColHalf<LOGN1>;
-  static_assert(NY % 4 == 0, "base conversion in steps of four limbs");
+  static_assert(NY % 4 == 0 && NY <= 16, "base conversion in steps of four limbs");
+  constexpr bool BYTES = NY > 4;  // the conversion on the matrix cores
   const KsJob J = JA.get(blockIdx.z);
   const size_t N = (size_t)1 << K.T.logN;
   const KsView V = ks_view(J, K, N);
@@ -256,18 +267,34 @@ __global__ __launch_bounds__(64 * kConvWaves, 4) void kc_conv(KsConst K, JobArg<
   if (o0 >= o1) return;
   __shared__ __align__(16) uint32_t y[NY * 512];
   __shared__ __align__(16) uint32_t xch[kConvWaves * 2 * CH::XCH];
-  __shared__ __align__(16) uint32_t Ts[kMaxPrimes * NY];  // the group's rows of the table, zero past nin
+  __shared__ __align__(16) uint32_t Ts[BYTES ? 4 : kMaxPrimes * NY];  // the group's rows of the table, zero past nin
   __shared__ int next;
   const int lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* x = xch + (2 * w + half) * CH::XCH;
   auto row_of = [&](int o) { return MODE == CONV_UP && o >= lo ? o + nin : o; };
 
-  const uint32_t* T = MODE == CONV_UP ? K.M.modup_T + ldc(K.modup_T_off + (size_t)V.L * K.beta_max + jd) : K.M.moddown_T;
-  const int stride = MODE == CONV_UP ? K.alpha : K.k;
-  for (int e = threadIdx.x; e < (o1 - o0) * NY; e += 64 * kConvWaves) {
-    const int o = e / NY, i = e % NY;
-    Ts[e] = i < nin ? ld1(T + (size_t)row_of(o0 + o) * stride + i) : 0;
+  const int stride = MODE == CONV_UP ? K.alpha : K.k, pad = (stride + 3) & ~3;
+  // the digit's place in its table, in words or (BYTES) rows
+  const size_t T0 =
+      MODE == CONV_UP ? ldc(K.modup_T_off + (size_t)(V.L + (BYTES ? K.T.L_max + 1 : 0)) * K.beta_max + jd) : 0;
+  // The A operands of a pair of output rows: lane l holds row l & 15 (bit 3: which
+  // output, bit 2: for which of two blocks, bits 1..0: byte e of the table), limbs
+  // 4 (l >> 4) and up.
+  auto load_a = [&](int u) {
+    const size_t row = T0 + row_of(min(o0 + u + (lane >> 3 & 1), o1 - 1));
+    return 4 * (lane >> 4) < pad ? ld4(bytes + (row * 4 + (lane & 3)) * pad + 4 * (lane >> 4))
+                                 : make_uint4(0, 0, 0, 0);
+  };
+  uint4 ta;
+  if constexpr (BYTES) {
+    ta = load_a(min(2 * w, o1 - o0 - 1));
+  } else {
+    const uint32_t* T = (MODE == CONV_UP ? K.M.modup_T : K.M.moddown_T) + T0;
+    for (int e = threadIdx.x; e < (o1 - o0) * NY; e += 64 * kConvWaves) {
+      const int o = e / NY, i = e % NY;
+      Ts[e] = i < nin ? ld1(T + (size_t)row_of(o0 + o) * stride + i) : 0;
+    }
   }
   if (threadIdx.x == 0) next = 2 * kConvWaves;
   for (int i0 = 2 * w; i0 < nin; i0 += 2 * kConvWaves) {
@@ -285,10 +312,18 @@ __global__ __launch_bounds__(64 * kConvWaves, 4) void kc_conv(KsConst K, JobArg<
     CH::inverse(v, x, tw, m, n);
 #pragma unroll
     for (int k = 0; k < 16; ++k) v[k] = csub(mont_mul(v[k], sc, m), m.q);
+    if constexpr (BYTES) {
+      // word k of lane n: column n & 15 of block 2 k + (n >> 4); a block's columns
+      // of four limbs lie together, the limb innermost
+      uint32_t* yi = y + ((n >> 4) * (NY / 4) + (i >> 2)) * 64 + (n & 15) * 4 + (i & 3);
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      *reinterpret_cast<uint4*>(y + i * 512 + k * 128 + n * 4) =
-          make_uint4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+      for (int k = 0; k < 16; ++k) yi[k * 2 * (NY / 4) * 64] = signed_bytes(v[k]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        *reinterpret_cast<uint4*>(y + i * 512 + k * 128 + n * 4) =
+            make_uint4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+    }
   }
   __syncthreads();
 
@@ -302,37 +337,65 @@ __global__ __launch_bounds__(64 * kConvWaves, 4) void kc_conv(KsConst K, JobArg<
     const MontQ m = mont_q_load(K.T.mod + pi);
     int un = 0;
     if (lane == 0) un = atomicAdd(&next, 2);
-    const uint32_t* t = Ts + (o - o0) * NY;
-    uint64_t a[16];
+    uint32_t v[16];
+    if constexpr (BYTES) {
+      // Two products of 16 x 64 by 64 x 16 bytes a word: the first fills the
+      // rows of lanes with bit 4 clear (block 2 k), the second the others
+      // (block 2 k + 1), so that a lane ends up with the four byte sums of its own
+      // word of its own half's output.
+      const bool odd = lane & 4;
+      const i32x4 a0 = {odd ? 0 : (int)ta.x, odd ? 0 : (int)ta.y, odd ? 0 : (int)ta.z, odd ? 0 : (int)ta.w};
+      const i32x4 a1 = {odd ? (int)ta.x : 0, odd ? (int)ta.y : 0, odd ? (int)ta.z : 0, odd ? (int)ta.w : 0};
+      // (opaque to the compiler: a shift of 64 bits and a negation a word otherwise)
+      int k16 = 1 << 16;
+      uint32_t qi = 0u - m.qn;
+      asm("" : "+s"(k16));
+      asm("" : "+v"(qi));
+      const uint32_t* yb = y + min(lane >> 4, NY / 4 - 1) * 64 + (lane & 15) * 4;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) a[k] = 0;
-    for (int i0 = 0; i0 < nin; i0 += 4) {
-      const uint4 t4 = *reinterpret_cast<const uint4*>(t + i0);
+      for (int k = 0; k < 16; ++k) {
+        const i32x4 b0 = *reinterpret_cast<const i32x4*>(yb + 2 * k * (NY / 4) * 64);
+        const i32x4 b1 = *reinterpret_cast<const i32x4*>(yb + (2 * k + 1) * (NY / 4) * 64);
+        i32x4 s = {0, 0, 0, 0};
+        s = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, b0, s, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, b1, s, 0, 0, 0);
+        // |s_e| <= 64 2^14, so the sum's high word is within 2^12 + 2^4 of zero,
+        // less than any prime (q > 2 N): the reduced word lies in (0, 4q)
+        const int64_t sum = (int64_t)(s[2] + (s[3] << 8)) * k16 + (s[0] + (s[1] << 8));
+        v[k] = (uint32_t)(sum >> 32) + m.q2 - __umulhi((uint32_t)sum * qi, m.q);
+        if (k % 4 == 3) {  // four words in flight (left alone, the compiler keeps 16 and spills)
+          asm volatile("" : "+v"(v[k - 3]), "+v"(v[k - 2]), "+v"(v[k - 1]), "+v"(v[k]));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    } else {
+      const uint32_t* t = Ts + (o - o0) * NY;
+      uint64_t a[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) a[k] = 0;
+      const uint4 t4 = *reinterpret_cast<const uint4*>(t);
       const uint32_t ts[4] = {t4.x, t4.y, t4.z, t4.w};
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const uint4 c = *reinterpret_cast<const uint4*>(y + (i0 + i) * 512 + k * 128 + n * 4);
+          const uint4 c = *reinterpret_cast<const uint4*>(y + i * 512 + k * 128 + n * 4);
           a[4 * k] += (uint64_t)c.x * ts[i];
           a[4 * k + 1] += (uint64_t)c.y * ts[i];
           a[4 * k + 2] += (uint64_t)c.z * ts[i];
           a[4 * k + 3] += (uint64_t)c.w * ts[i];
         }
-    }
-    // Montgomery reduction of the sum (the table carries 2^32): with T < q and
-    // inputs below 2^30 its high word is below nin q / 4, so for up to 12
-    // inputs the result lies in (0, 4q) at once; past 12, one correction first.
-    uint32_t v[16];
+      // Montgomery reduction of the sum (the table carries 2^32): with T < q and
+      // inputs below 2^30 its high word is below q, so the result is in (0, 4q).
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      uint32_t hi = (uint32_t)(a[k] >> 32);
-      if (NY > 12) hi = csub(hi, m.q2);
-      v[k] = hi + m.q - __umulhi((uint32_t)a[k] * (0u - m.qn), m.q);
+      for (int k = 0; k < 16; ++k)
+        v[k] = (uint32_t)(a[k] >> 32) + m.q - __umulhi((uint32_t)a[k] * (0u - m.qn), m.q);
     }
-    CH::forward(v, x, tw, m, n);
-    CH::store(v, x, out, (uint32_t)r << K.T.logN, tile, n, half == 0 || u + 1 < o1 - o0);
+    const bool pair = half == 0 || u + 1 < o1 - o0;
     u = __builtin_amdgcn_readfirstlane(un);
+    if constexpr (BYTES) ta = load_a(min(u, o1 - o0 - 1));
+    CH::forward(v, x, tw, m, n);
+    CH::store(v, x, out, (uint32_t)r << K.T.logN, tile, n, pair);
   }
 }
 
@@ -1558,7 +1621,8 @@ int conv_groups(long base, int rows, int cap) {
 template <int L1, int MODE>
 hipError_t conv_launch(const Ctx& c, int stage, int nin, dim3 g, hipStream_t st, const KsConst& K,
                        const JobArg<KsJob>& jobs, int groups) {
-  auto go = [&](auto kern) { klaunch_b(c, stage, kern, g, 64 * kConvWaves, st, K, jobs, groups); };
+  const uint32_t* bytes = MODE == CONV_UP ? c.modup_bytes : c.moddown_bytes;
+  auto go = [&](auto kern) { klaunch_b(c, stage, kern, g, 64 * kConvWaves, st, K, jobs, groups, bytes); };
   if (nin <= 4)
     go(kc_conv<L1, MODE, 4>);
   else if (nin <= 12)

@@ -265,14 +265,38 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
   for (size_t e = 0; e < dT.size(); ++e) all.push_back(mont(dT[e], c.primes[e / c.k]));
   begin();
   for (int i = 0; i < c.L_max; ++i) all.push_back(mont(pinv[i].x, c.primes[i]));
+  // the conversion tables in signed bytes, for the matrix cores
+  auto bytes = [&](const uint32_t* T, int nin, u64 q) {
+    const int pad = (nin + 3) / 4 * 4;
+    const size_t at0 = all.size();
+    all.resize(at0 + 4 * (size_t)pad, 0);
+    for (int i = 0; i < nin; ++i)
+      for (int d = 0; d < 4; ++d) {
+        const uint32_t t = signed_bytes(mont(mulm(T[i], (1ull << (8 * d)) % q, q), q));
+        for (int e = 0; e < 4; ++e) all[at0 + (size_t)e * pad + i] |= (t >> (8 * e) & 255u) << (8 * d);
+      }
+  };
+  begin();
+  if (c.alpha > 4) {
+    size_t e = 0;
+    for (int L = 1; L <= c.L_max; ++L)
+      for (int j = 0; j < c.beta(L); ++j)
+        for (int r = 0; r < L + c.k; ++r, e += c.alpha) bytes(&mT[e], c.alpha, c.primes[c.rows(L).pidx(r)]);
+  }
+  begin();
+  if (c.k > 4)
+    for (int i = 0; i < c.L_max; ++i) bytes(&dT[(size_t)i * c.k], c.k, c.primes[i]);
 
   std::string err;
   if (!(err = upload(&c.d_mont, all, code)).empty()) return err;
   const uint32_t* d = c.d_mont;
   c.mont = MontTab{d + at[0], d + at[1], d + at[2], d + at[3], d + at[4],  d + at[5],
                    d + at[6], d + at[7], d + at[8], d + at[9], d + at[10]};
+  c.modup_bytes = d + at[11];
+  c.moddown_bytes = d + at[12];
   if (!(err = upload(&c.d_mod, mod, code)).empty()) return err;
   std::vector<uint32_t> toff(c.modup_T_off.begin(), c.modup_T_off.end());
+  for (size_t w : c.modup_T_off) toff.push_back((uint32_t)(w / c.alpha));
   if (!(err = upload(&c.d_modup_T_off, toff, code)).empty()) return err;
   if (!(err = upload(&c.d_pinv, pinv, code)).empty()) return err;
   if (!(err = upload(&c.d_rescale_inv, rinv, code)).empty()) return err;

@@ -5,6 +5,7 @@ digit sizes on both sides of a step of four limbs, of an even count and of the
 limb past it and every limb; every ring degree's tile width.
 
 Bit-exact against the oracle on every residue (tolerance 0)."""
+import numpy as np
 import pytest
 import torch
 
@@ -63,3 +64,35 @@ def test_rotations_of_a_ciphertext_at_a_four_byte_offset(name, L):
         P.ckks_hrot_hoisted(h, shifted, L, [rot], [dev(key)], [out], ctx.workspace("HROT_HOISTED", L))
         msg = first_mismatch(host(out), O.hrot_hoisted(par, ct, L, [rot], [key])[0])
         assert not msg, f"hoisted rotation by {rot}: {msg}"
+
+
+@pytest.mark.parametrize("alpha", [4, 5, 11, 16])
+def test_conversions_of_extreme_words(alpha):
+    """Scaled inputs whose words, or every byte of them, are the largest and the
+    smallest there are, over all limbs at once: the largest sums."""
+    spec = ci.chain_spec(f"x{alpha}", 13, 2 * alpha, alpha, 2, 7)
+    par, ctx = O.Params.from_spec(spec), P.Context.from_spec(spec)
+    h, N, L = ctx.handle, spec.N, alpha + 2
+    low = 128 * (1 + (1 << 8) + (1 << 16))
+
+    def words(primes):  # coefficients that the pre-multiplier turns into these words
+        rows = []
+        for q in primes:
+            rest = 1
+            for t in primes:
+                rest = rest * (t if t != q else 1) % q
+            y = [q - 1, 0, (63 << 24) - low, (63 << 24) + 127 * (low >> 7), 1, (q - 1) // 2, low, 128]
+            rows.append([w % q * rest % q for w in y])
+        return np.tile(np.array(rows, dtype=np.uint32), (1, N // 8))
+
+    d = np.concatenate([words(spec.q[r.start:r.stop]) for r in par.digits(L)])
+    d = O.ntt(par, d, spec.q[:L])
+    out = empty(par.beta(L), L + alpha, N)
+    P.ckks_modup(h, dev(d), L, out, ctx.workspace("MODUP", L))
+    msg = first_mismatch(host(out), O.modup(par, d, L))
+    assert not msg, f"ModUp, digits of {alpha}: {msg}"
+    a = np.concatenate([d, O.ntt(par, words(spec.p), spec.p)])
+    out = empty(L, N)
+    P.ckks_moddown(h, dev(a), L, out, ctx.workspace("MODDOWN", L))
+    msg = first_mismatch(host(out), O.moddown(par, a, L))
+    assert not msg, f"ModDown, {alpha} special primes: {msg}"
