@@ -219,9 +219,9 @@ def main():
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
-    # Dominant kernel: NTT block pass fused with the key inner product (stage 2
-    # of key-switching), timed by events the runtime records at the start and
-    # end of each of its dispatches inside the timed region.
+    # Dominant kernel: the Q rows' NTT block pass fused with the key inner product
+    # (stage 2 of key-switching) and ModDown's combine, timed by events the runtime
+    # records at the start and end of each of its dispatches inside the timed region.
     ip_launches = 2 * args.steps
     P.ckks_trace_begin(h, P.STAGE["NTT_IP"], ip_launches)
     t0 = time.perf_counter()
@@ -252,12 +252,14 @@ def main():
     limb = N * LIMB_BYTES
     # Algorithmic bytes of one key-switch at level L: the switched polynomial
     # in, the key rows of level L in, both output components out (the
-    # intermediates are assumed on chip).  One K5 launch of the step processes
-    # one key-switch.
-    ks_bytes = _op_limbs("KEYSWITCH", L, k, beta) * limb
-    # K5's own input and output: the beta*R ModUp rows and 2*beta*R key rows
-    # in, the 2*R accumulator rows out
-    ip_io_bytes = (3 * beta + 2) * R * limb
+    # intermediates are assumed on chip).  One launch of the dominant kernel
+    # processes one key-switch's Q rows: L of the L + k key rows of each digit and
+    # component (the P rows' own launch reads the others).
+    ks_bytes = (_op_limbs("KEYSWITCH", L, k, beta) - 2 * beta * (R - L)) * limb
+    # The kernel's own input and output: beta*L ModUp rows, 2*beta*L key rows, the
+    # 2*L converted rows and the operation's own terms (HMult's four inputs,
+    # HRot's sigma(c0); a mean of 5/2 L) in, the 2*L output rows out
+    ip_io_bytes = (2 * (3 * beta + 4) + 5) * L * limb // 2
     ip_s = 1e-3 * float(np.mean(ip_ms))
     achieved = ks_bytes / ip_s / 1e9
     roofline = {

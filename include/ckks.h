@@ -321,9 +321,10 @@ int ckks_ctx_set_schedule(ckks_ctx *ctx, const ckks_schedule *sched);
  * Schedule autotuner: times an HMult at level L on synthetic inputs (zeros;
  * the arithmetic is data-independent) under every candidate schedule
  * (rows in {2, 4, 6, 12} for both BConvs, small_grid in {0, 128, 1024},
- * ntt_shape 0..7, and 8..15 at N = 2^12: 384 or 768 candidates), one
- * warm-up and `reps` calls each between two events on `stream`, and keeps
- * the fastest.  Allocates its own device buffers (inputs, key, workspace)
+ * ntt_shape 0, and 8 at N = 2^12: 48 or 96 candidates), one
+ * warm-up and `reps` calls each between two events on `stream`, four keys in
+ * turn (one where there is no room for four), and keeps
+ * the fastest.  Allocates its own device buffers (inputs, keys, workspace)
  * for the duration of the call and synchronises `stream`; not for use while
  * other calls run on the context.  best / best_us (either may be NULL)
  * receive the schedule and its time per HMult in microseconds.
@@ -419,11 +420,12 @@ int ckks_batch_set_schedule(ckks_batch *batch, const ckks_schedule *sched);
  * graph batch), at N = 2^12 under the whole-limb schedule split 0/1) under the
  * batch's schedule, then, under the
  * best plan, up to four other BConv schedules ({12, 6, 128}, {6, 4, 128},
- * {4, 6, 128}, {12, 12, 128}, with the batch's ntt_shape), then the other
- * seven NTT shapes under the best of those: each candidate as one warm-up
+ * {4, 6, 128}, {12, 12, 128}, with the batch's ntt_shape), then at N = 2^12
+ * the other value of ntt_shape's bit 8 under the best of those: each candidate
+ * as one warm-up
  * launch then `reps` launches between two events on `stream`; keeps the
  * fastest plan and schedule (graph batches are re-captured and timed as graph
- * launches).  Runs the batch up to 83 x (reps + 1) times and synchronises
+ * launches).  Runs the batch up to 53 x (reps + 1) times and synchronises
  * `stream`:
  * outputs are written, inputs only read.  best / best_us (either may be
  * NULL) receive the chosen plan and its time per launch in microseconds;

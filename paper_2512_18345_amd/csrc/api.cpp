@@ -651,21 +651,35 @@ int ckks_ctx_tune(ckks_ctx* ctx, int L, int reps, void* stream, ckks_schedule* b
     if (t0) (void)hipEventDestroy(t0);
     if (t1) (void)hipEventDestroy(t1);
   };
-  if (hipMalloc(&d_ct, 2 * ct_b) != hipSuccess || hipMalloc(&d_key, key_b) != hipSuccess ||
-      hipMalloc(&d_out, ct_b) != hipSuccess || hipMalloc(&d_ws, ws_b) != hipSuccess) {
+  // Calls take keys in turn, as a program's calls do: four keys of a large ring
+  // (75 MB each at N = 2^16, 36 + 12 primes) pass the 256 MB Infinity Cache, so
+  // each comes from HBM.  With one key, cached from call to call, the small grids'
+  // kernels won (small_grid 1024: HMult p50 95.4 us against 97.7), which are slower
+  // where keys alternate (two key-switches and a rescale 244 us against 236).
+  bool room = hipMalloc(&d_ct, 2 * ct_b) == hipSuccess && hipMalloc(&d_out, ct_b) == hipSuccess &&
+              hipMalloc(&d_ws, ws_b) == hipSuccess;
+  int keys = 4;
+  if (room && hipMalloc(&d_key, keys * key_b) != hipSuccess) {
+    (void)hipGetLastError();
+    d_key = nullptr;
+    keys = 1;
+    room = hipMalloc(&d_key, key_b) == hipSuccess;
+  }
+  if (!room) {
     cleanup();
     return fail(CKKS_ENOMEM, "tuning buffers");
   }
   hipError_t e = hipMemsetAsync(d_ct, 0, 2 * ct_b, st);
-  if (e == hipSuccess) e = hipMemsetAsync(d_key, 0, key_b, st);
+  if (e == hipSuccess) e = hipMemsetAsync(d_key, 0, keys * key_b, st);
   if (e == hipSuccess) e = hipEventCreate(&t0);
   if (e == hipSuccess) e = hipEventCreate(&t1);
   const Ctx::Sched start = c.sched;
   Ctx::Sched top = start;
   float top_us = -1.f;
+  unsigned turn = 0;
   const uint32_t* ct1 = (const uint32_t*)d_ct;
   const uint32_t* ct2 = (const uint32_t*)((char*)d_ct + ct_b);
-  for (int shape = 0; shape <= kShapeAll; ++shape)
+  for (int shape : {0, kShapeWholeLimb})  // (the other bits have no effect)
   for (int up : {12, 6, 4, 2}) {
     if ((shape & kShapeWholeLimb) && c.logN != kSrLog) break;  // the bit means nothing there
     for (int down : {6, 12, 4, 2}) {
@@ -673,7 +687,8 @@ int ckks_ctx_tune(ckks_ctx* ctx, int L, int reps, void* stream, ckks_schedule* b
         if (e != hipSuccess) break;
         c.sched = Ctx::Sched{up, down, small, shape};
         auto once = [&]() {
-          return run_one(c, KS_HMULT, L, 0, ct1, ct2, (const uint32_t*)d_key, (uint32_t*)d_out, d_ws, st);
+          const uint32_t* key = (const uint32_t*)((char*)d_key + (turn++ % keys) * key_b);
+          return run_one(c, KS_HMULT, L, 0, ct1, ct2, key, (uint32_t*)d_out, d_ws, st);
         };
         if (once() != CKKS_OK) {
           e = hipErrorUnknown;
@@ -945,15 +960,13 @@ int ckks_batch_tune(ckks_batch* b, int reps, void* stream, ckks_batch_plan* best
         top_sched = cs;
       }
     }
-    // 3) NTT tile / radix shapes under the best plan and BConv schedule
-    const Ctx::Sched base = top_sched;
-    for (int shape = 0; shape <= kShapeAll && e == hipSuccess; ++shape) {
-      if (shape == base.ntt_shape || ((shape & kShapeWholeLimb) && b->c->logN != kSrLog)) continue;
-      b->sched = base;
-      b->sched.ntt_shape = shape;
+    // 3) the other of whole limbs and pipeline under the best plan and schedule
+    if (e == hipSuccess && b->c->logN == kSrLog) {
+      b->sched = top_sched;
+      b->sched.ntt_shape = top_sched.ntt_shape ^ kShapeWholeLimb;
       float us = 0.f;
-      if ((e = time_it(&us)) != hipSuccess) break;
-      if (us < top_us) {
+      e = time_it(&us);
+      if (e == hipSuccess && us < top_us) {
         top_us = us;
         top_sched = b->sched;
       }

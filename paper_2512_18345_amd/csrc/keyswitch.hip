@@ -1607,7 +1607,7 @@ void klaunch(const Ctx& c, int stage, F kern, dim3 g, hipStream_t st, A... args)
 // Groups of output rows of a column-conversion launch whose work-groups number
 // `base` at one group each (column tiles x digits or components x jobs), with
 // at most `rows` output rows: enough to have a work-group per CU (a group more
-// repeats the input transforms, a third of the work at 12 inputs and 36 rows,
+// repeats the input transforms, a quarter of the work at 12 inputs and 36 rows,
 // and a second work-group on a CU only shares its vector units), none with
 // less than a pair of rows, and at most 8 `cap` rows in a group, `cap` being
 // the schedule's BConv rows.
