@@ -978,6 +978,12 @@ __global__ __launch_bounds__(kWG) void k5h_gather_ip(KsConst K, JobArg<KsJob> JA
 // the threads share out the inner product's 256 quads, and for P rows waves 0
 // and 1 take a component each.  Four times the work-groups of k5s and a third
 // of its chain per wave.  Every barrier below is reached by all threads.
+// The line of 128 work-groups (the schedule's small_grid): below it, with half of
+// the CUs idle under k5s, HMult at N = 2^14, L = 13 (48 and 52 work-groups) takes
+// 35.3 us against 43.9 by k5s and HRot at N = 2^15, L = 25 (96) 55.9 against 59.7;
+// above it the side-by-side waves load a CU more than they shorten its chain: at
+// 192 HRot at N = 2^16, L = 7 takes 41.7 us against 40.3, a step at L = 36 229.5
+// against 227.4 (at 200, three digits, 55.4 against 56.0).
 template <int NB, bool Q>
 __global__ __launch_bounds__(64 * NB) void k5p_ntt_blks_ip(KsConst K, JobArg<KsJob> JA) {
   static_assert(NB >= 2 && NB <= 4, "one wave per digit");
