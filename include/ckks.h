@@ -417,15 +417,15 @@ int ckks_batch_set_schedule(ckks_batch *batch, const ckks_schedule *sched);
 /*
  * Autotuner: times candidate plans (jobs_per_launch in {all, 32, 16, 8, 4, 2}
  * below the job count, streams 1..4 up to the number of groups (1 for a
- * graph batch), at N = 2^12 under the whole-limb schedule split 0/1) under the
- * batch's schedule, then, under the
+ * graph batch); at N = 2^12 and digit sizes 1 and 2 each of them with the
+ * whole-limb kernels, split 0 and ntt_shape bit 8, and with the pipeline) under
+ * the batch's schedule, then, where the pipeline was faster, under the
  * best plan, up to four other BConv schedules ({12, 6, 128}, {6, 4, 128},
- * {4, 6, 128}, {12, 12, 128}, with the batch's ntt_shape), then at N = 2^12
- * the other value of ntt_shape's bit 8 under the best of those: each candidate
+ * {4, 6, 128}, {12, 12, 128}, with the batch's ntt_shape): each candidate
  * as one warm-up
  * launch then `reps` launches between two events on `stream`; keeps the
  * fastest plan and schedule (graph batches are re-captured and timed as graph
- * launches).  Runs the batch up to 53 x (reps + 1) times and synchronises
+ * launches).  Runs the batch up to 52 x (reps + 1) times and synchronises
  * `stream`:
  * outputs are written, inputs only read.  best / best_us (either may be
  * NULL) receive the chosen plan and its time per launch in microseconds;

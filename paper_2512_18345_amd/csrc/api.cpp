@@ -919,33 +919,45 @@ int ckks_batch_tune(ckks_batch* b, int reps, void* stream, ckks_batch_plan* best
   float top_us = -1.f;
   hipError_t e = hipSuccess;
   const int max_streams = b->use_graph ? 1 : kMaxBranches;
-  // split changes the launch only where it chooses between two pipelines
-  const std::vector<int> splits = b->c->logN == kSrLog && (start_sched.ntt_shape & kShapeWholeLimb)
-                                      ? std::vector<int>{0, 1}
-                                      : std::vector<int>{start.split};
+  // The whole-limb kernels take both the plan's split 0 and the schedule's bit
+  // 8, so where the ring has them a plan is timed once with both and once with
+  // the pipeline; elsewhere split changes nothing.
+  const int bit = kShapeWholeLimb, sh0 = start_sched.ntt_shape;
+  struct {
+    int split, shape;
+  } ways[2] = {{start.split, sh0}, {0, sh0 | bit}};
+  const int n_ways = ks_whole_limb_ring(*b->c) ? 2 : 1;
+  if (n_ways == 2 && (sh0 & bit)) ways[0].split = 1;
+  auto whole = [&](const ckks_batch_plan& p, const Ctx::Sched& sc) {
+    return n_ways == 2 && p.split == 0 && (sc.ntt_shape & bit);
+  };
   // 1) launch plans under the batch's schedule
   for (int B : sizes) {
     const int groups = B ? (b->n_ks + B - 1) / B : 1;
     for (int S = 1; S <= max_streams && e == hipSuccess; ++S) {
       if (S > 1 && S > groups + (b->n_rs ? 1 : 0)) break;
-      for (int split : splits) {
+      for (int w = 0; w < n_ways; ++w) {
         if (e != hipSuccess) break;
-        b->plan = ckks_batch_plan{B, S, split, 0};
+        b->plan = ckks_batch_plan{B, S, ways[w].split, 0};
+        b->sched = start_sched;
+        b->sched.ntt_shape = ways[w].shape;
         float us = 0.f;
         if ((e = time_it(&us)) != hipSuccess) break;
         b->tune_log.emplace_back(b->plan, us);
         if (top_us < 0.f || us < top_us) {
           top_us = us;
           top = b->plan;
+          top_sched = b->sched;
         }
       }
     }
   }
   // 2) kernel schedules under the best plan: a batch's grids are larger than
-  // a single operation's, so the context's schedule need not suit it
-  if (e == hipSuccess) {
+  // a single operation's, so the context's schedule need not suit it (the
+  // whole-limb kernels have none of its other fields)
+  if (e == hipSuccess && !whole(top, top_sched)) {
     b->plan = top;
-    const int sh = start_sched.ntt_shape;
+    const int sh = top_sched.ntt_shape;
     const Ctx::Sched cands[] = {{12, 6, 128, sh}, {6, 4, 128, sh}, {4, 6, 128, sh}, {12, 12, 128, sh}};
     for (const Ctx::Sched& cs : cands) {
       if (e != hipSuccess) break;
@@ -958,17 +970,6 @@ int ckks_batch_tune(ckks_batch* b, int reps, void* stream, ckks_batch_plan* best
       if (us < top_us) {
         top_us = us;
         top_sched = cs;
-      }
-    }
-    // 3) the other of whole limbs and pipeline under the best plan and schedule
-    if (e == hipSuccess && b->c->logN == kSrLog) {
-      b->sched = top_sched;
-      b->sched.ntt_shape = top_sched.ntt_shape ^ kShapeWholeLimb;
-      float us = 0.f;
-      e = time_it(&us);
-      if (e == hipSuccess && us < top_us) {
-        top_us = us;
-        top_sched = b->sched;
       }
     }
   }

@@ -49,6 +49,13 @@ constexpr int kInlineJobs = 16;
 constexpr int kShapeWholeLimb = 8;   // N = 2^kSrLog: two kernels with whole limbs in LDS instead of five
 constexpr int kShapeAll = 15;
 constexpr int kSrGroups = 4;  // whole-limb key-switch: digit groups of its first kernel, at most
+// A whole-limb work-group transforms a digit's limbs, and ModDown's P rows (as
+// many), one after another, 6 us a limb in all, where the five kernels' time
+// hardly depends on their number: HMult at digit size 1 19 us against 29, 2: 25
+// against 31, 3: 32 against 31, 4: 38 against 31, 12: 89 against 36.
+constexpr int kSrDigit = 2;
+// The ring and digit size have the whole-limb kernels (the schedule's bit chooses them).
+inline bool ks_whole_limb_ring(const Ctx& c) { return c.logN == kSrLog && c.alpha <= kSrDigit; }
 
 // Jobs either inline in the kernel arguments (n <= kInlineJobs) or in a device
 // table written only by the host.  get() returns the job by value through

@@ -1298,11 +1298,6 @@ __global__ __launch_bounds__(kWG) void kd_ntt_blks_combine(KsConst K, JobArg<KsJ
 // ============================================================================
 constexpr int kSrN = 1 << kSrLog;
 static_assert(kSrN == kTile, "one 16-row group per limb");
-// A work-group transforms a digit's limbs, and ModDown's P rows (as many), one
-// after another, 6 us a limb in all, where the five kernels' time hardly
-// depends on their number: HMult at digit size 1 19 us against 29, 2: 25
-// against 31, 3: 32 against 31, 4: 38 against 31, 12: 89 against 36.
-constexpr int kSrDigit = 2;
 
 __device__ __forceinline__ int sr_per(int beta) { return (beta + kSrGroups - 1) / kSrGroups; }  // digits per group
 __device__ __forceinline__ int sr_groups(int beta) { return (beta + sr_per(beta) - 1) / sr_per(beta); }
@@ -1681,7 +1676,7 @@ hipError_t ks_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, con
   if constexpr (L1 + kBlockLog == kSrLog) {
     // small ring: two kernels on whole limbs (plain, HMult and HRot jobs), for
     // digits of at most kSrDigit limbs
-    if ((sc.ntt_shape & kShapeWholeLimb) && c.alpha <= kSrDigit && with_modup && !with_hoist && whole_limb) {
+    if ((sc.ntt_shape & kShapeWholeLimb) && ks_whole_limb_ring(c) && with_modup && !with_hoist && whole_limb) {
       // every job splits its own digits into sr_groups(beta) <= min(beta, kSrGroups)
       // groups, so the grid covers min(bmax, kSrGroups) (not the largest job's count)
       const int groups = std::min(c.beta(Lmax), kSrGroups);
