@@ -319,12 +319,14 @@ int ckks_ctx_get_schedule(const ckks_ctx *ctx, ckks_schedule *sched);
 int ckks_ctx_set_schedule(ckks_ctx *ctx, const ckks_schedule *sched);
 /*
  * Schedule autotuner: times an HMult at level L on synthetic inputs (zeros;
- * the arithmetic is data-independent) under every candidate schedule
- * (rows in {2, 4, 6, 12} for both BConvs, small_grid in {0, 128, 1024},
- * ntt_shape 0, and 8 at N = 2^12: 48 or 96 candidates), one
- * warm-up and `reps` calls each between two events on `stream`, four keys in
- * turn (one where there is no room for four), and keeps
- * the fastest.  Allocates its own device buffers (inputs, keys, workspace)
+ * the arithmetic is data-independent) under the default schedule and every
+ * candidate (rows in {2, 4, 6, 12} for both BConvs, small_grid in {0, 128,
+ * 1024}, ntt_shape 0, and 8 at N = 2^12) that launches something else at that
+ * level, each launch sequence once: three rounds of one warm-up and `reps`
+ * calls each between two events on `stream`, four keys in
+ * turn (one where there is no room for four).  Keeps the fastest by its median
+ * round, the default unless that beats it by more than the rounds of either
+ * differ.  Allocates its own device buffers (inputs, keys, workspace)
  * for the duration of the call and synchronises `stream`; not for use while
  * other calls run on the context.  best / best_us (either may be NULL)
  * receive the schedule and its time per HMult in microseconds.
@@ -420,9 +422,9 @@ int ckks_batch_set_schedule(ckks_batch *batch, const ckks_schedule *sched);
  * graph batch); at N = 2^12 and digit sizes 1 and 2 each of them with the
  * whole-limb kernels, split 0 and ntt_shape bit 8, and with the pipeline) under
  * the batch's schedule, then, where the pipeline was faster, under the
- * best plan, up to four other BConv schedules ({12, 6, 128}, {6, 4, 128},
- * {4, 6, 128}, {12, 12, 128}, with the batch's ntt_shape): each candidate
- * as one warm-up
+ * best plan, those of the BConv schedules {12, 6, 128}, {6, 4, 128},
+ * {4, 6, 128} and {12, 12, 128} (with the batch's ntt_shape) that launch
+ * something else for its jobs: each candidate as one warm-up
  * launch then `reps` launches between two events on `stream`; keeps the
  * fastest plan and schedule (graph batches are re-captured and timed as graph
  * launches).  Runs the batch up to 52 x (reps + 1) times and synchronises

@@ -74,6 +74,18 @@ size_t ks_ws_words(const Ctx& c, int L);        // any job kind
 size_t ks_hoist_ws_words(const Ctx& c, int L);  // KS_HOIST jobs only (no ModUp scratch)
 size_t rs_ws_words(const Ctx& c, int L);
 
+// What a schedule launches for njobs jobs up to level Lmax that run ModUp: two
+// schedules with equal grids are one launch sequence.
+struct KsGrids {
+  bool whole;             // the whole-limb kernels, which have none of the fields below
+  int up, down;           // row groups of the column kernels
+  bool small_p, small_q;  // the inner product's kernel for small grids, P and Q rows
+  bool operator==(const KsGrids& o) const {
+    return whole == o.whole && up == o.up && down == o.down && small_p == o.small_p && small_q == o.small_q;
+  }
+};
+KsGrids ks_grids(const Ctx& c, const Ctx::Sched& sc, int njobs, int Lmax, bool whole_limb = true);
+
 // Enqueue the key-switching pipeline for njobs jobs whose largest level is
 // Lmax under kernel schedule sc (the context's, or a batch's own).
 // with_modup: some job is not KS_HOIST (stage 1 runs); with_hoist: some job

@@ -1619,6 +1619,19 @@ int conv_groups(long base, int rows, int cap) {
   return (int)std::max({1l, fill, need});
 }
 
+int up_groups(const Ctx& c, const Ctx::Sched& sc, int njobs, int Lmax) {
+  return conv_groups((long)(c.N / 512) * c.beta(Lmax) * njobs, Lmax + c.k - 1, sc.up_rows);
+}
+// comps: components, two of a key-switch
+int down_groups(const Ctx& c, const Ctx::Sched& sc, int njobs, int Lmax, int comps) {
+  return conv_groups((long)(c.N / 512) * comps * njobs, Lmax, sc.down_rows);
+}
+// The inner product of `rows` rows a job takes the kernel for small grids: too few
+// work-groups to fill the CUs (k5p_ntt_blks_ip has the line's reasons).
+bool small_ip(const Ctx& c, const Ctx::Sched& sc, int njobs, int Lmax, int rows) {
+  return c.beta(Lmax) <= 4 && c.N / kTile * rows * njobs <= sc.small_grid;
+}
+
 template <int L1, int MODE>
 hipError_t conv_launch(const Ctx& c, int stage, int nin, dim3 g, hipStream_t st, const KsConst& K,
                        const JobArg<KsJob>& jobs, int groups) {
@@ -1638,8 +1651,8 @@ template <int L1>
 hipError_t modup_stage_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, const JobArg<KsJob>& jobs,
                          int njobs, int Lmax, hipStream_t st) {
   const int beta = c.beta(Lmax), tiles = c.N / 512;
+  const int groups = up_groups(c, sc, njobs, Lmax);
   klaunch(c, CKKS_STAGE_INTT_BLOCKS, k1_intt_blks, dim3(c.N / kTile, Lmax, njobs), st, K, jobs);
-  const int groups = conv_groups((long)tiles * beta * njobs, Lmax + c.k - 1, sc.up_rows);
   return conv_launch<L1, CONV_UP>(c, CKKS_STAGE_INTT_COLS, c.alpha, dim3(tiles, beta * groups, njobs), st, K, jobs,
                                   groups);
 }
@@ -1659,12 +1672,16 @@ template <int L1>
 hipError_t ks_moddown_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, const JobArg<KsJob>& jobs,
                                int njobs, int Lmax, hipStream_t st) {
   klaunch(c, -1, k1_intt_blks, dim3(c.N / kTile, c.k, njobs), st, K, jobs);
-  const int groups = conv_groups((long)(c.N / 512) * njobs, Lmax, sc.down_rows);
+  const int groups = down_groups(c, sc, njobs, Lmax, 1);
   const hipError_t e =
       conv_launch<L1, CONV_DOWN>(c, -1, c.k, dim3(c.N / 512, groups, njobs), st, K, jobs, groups);
   if (e != hipSuccess) return e;
   klaunch(c, -1, kd_ntt_blks_combine, dim3(c.N / kTile, Lmax, njobs), st, K, jobs);
   return hipGetLastError();
+}
+
+bool takes_whole_limbs(const Ctx& c, const Ctx::Sched& sc, bool whole_limb) {
+  return whole_limb && (sc.ntt_shape & kShapeWholeLimb) && ks_whole_limb_ring(c);
 }
 
 template <int L1>
@@ -1676,7 +1693,7 @@ hipError_t ks_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, con
   if constexpr (L1 + kBlockLog == kSrLog) {
     // small ring: two kernels on whole limbs (plain, HMult and HRot jobs), for
     // digits of at most kSrDigit limbs
-    if ((sc.ntt_shape & kShapeWholeLimb) && ks_whole_limb_ring(c) && with_modup && !with_hoist && whole_limb) {
+    if (with_modup && !with_hoist && takes_whole_limbs(c, sc, whole_limb)) {
       // every job splits its own digits into sr_groups(beta) <= min(beta, kSrGroups)
       // groups, so the grid covers min(bmax, kSrGroups) (not the largest job's count)
       const int groups = std::min(c.beta(Lmax), kSrGroups);
@@ -1701,7 +1718,7 @@ hipError_t ks_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, con
     const bool nt = njobs == 1;
     auto of = [&](auto n) {
       constexpr int NB = decltype(n)::value;
-      if (tiles * rows * njobs <= sc.small_grid)  // too few work-groups to fill the CUs
+      if (small_ip(c, sc, njobs, Lmax, rows))
         klaunch_b(c, stage, k5p_ntt_blks_ip<NB, Q>, g4, 64 * NB, st, K, jobs);
       else if (nt)
         klaunch(c, stage, k5s_ntt_blks_ip<NB, true, Q>, g5, st, K, jobs);
@@ -1727,7 +1744,7 @@ hipError_t ks_launch_t(const Ctx& c, const Ctx::Sched& sc, const KsConst& K, con
   };
   if (with_modup) k5(std::false_type(), CKKS_STAGE_NTT_IP_P, c.k);
   if (with_hoist) k5h(std::false_type(), CKKS_STAGE_NTT_IP_P, c.k);
-  const int groups = conv_groups((long)(c.N / 512) * 2 * njobs, Lmax, sc.down_rows);
+  const int groups = down_groups(c, sc, njobs, Lmax, 2);
   e = conv_launch<L1, CONV_DOWN>(c, CKKS_STAGE_INTT_COLS_P, c.k, dim3(c.N / 512, 2 * groups, njobs), st, K, jobs,
                                  groups);
   if (e != hipSuccess) return e;
@@ -1749,6 +1766,12 @@ hipError_t rs_launch_t(const Ctx& c, const KsConst& K, const JobArg<RsJob>& jobs
   return hipGetLastError();
 }
 }  // namespace
+
+KsGrids ks_grids(const Ctx& c, const Ctx::Sched& sc, int njobs, int Lmax, bool whole_limb) {
+  if (takes_whole_limbs(c, sc, whole_limb)) return KsGrids{true, 0, 0, false, false};
+  return KsGrids{false, up_groups(c, sc, njobs, Lmax), down_groups(c, sc, njobs, Lmax, 2),
+                 small_ip(c, sc, njobs, Lmax, c.k), small_ip(c, sc, njobs, Lmax, Lmax)};
+}
 
 hipError_t ks_launch(const Ctx& c, const Ctx::Sched& sc, const JobArg<KsJob>& jobs, int njobs, int Lmax,
                      bool with_modup, bool with_hoist, hipStream_t st, bool whole_limb) {
