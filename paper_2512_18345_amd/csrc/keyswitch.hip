@@ -606,6 +606,11 @@ __device__ __forceinline__ void q_rows_combine(uint32_t* s, const KsConst& K, co
 // registers.  HOIST selects the variant for hoisted-rotation jobs (gather of
 // sigma(M), no transform; each rotation brings its own key, streamed with the
 // non-temporal hint); the other variant serves every other job kind.
+// Bound: the chain of digits, which the P rows and the Q rows each walk.  Asking
+// for a digit's words only when its turn came made that two latencies a digit:
+// HMult of 24 one-limb digits at N = 2^14 174 us, 148 with them requested ahead
+// (N = 2^13 166 -> 142; ten two-limb digits at N = 2^14 93 -> 83; eight jobs of 24
+// digits at N = 2^14 409 -> 367).
 template <bool HOIST, bool Q>
 __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> JA) {
   const KsJob J = JA.get(blockIdx.z);
@@ -652,8 +657,22 @@ __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> J
     for (int kk = 0; kk < 4; ++kk) aq[kk] = auto_quad(n0 + 64 * kk, J.gal, logN);
     hoist_load(0);
   }
+  // Any other job: a digit's words -- the digit row itself in row order (kept by K1
+  // unless it is the input) or its ModUp row in the row-group layout -- are
+  // requested a digit ahead, its key words before its transform.
+  auto owns = [&](int j) { return r >= j * K.alpha && r < min((j + 1) * K.alpha, V.L); };
+  auto digit_load = [&](int j) {
+    const bool own = owns(j);
+    const uint32_t* src = own ? (J.kind == KS_PLAIN ? J.a : V.de) + (size_t)r * N
+                              : V.z + ((size_t)j * V.R + r) * N + base;
+    const uint32_t at = own ? n0 : (uint32_t)RowGroup<16>::word(threadIdx.x, 0, 0);
+    const uint32_t step = own ? 64 : 1024;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) nv[kk] = ld4(src + at + step * kk);
+  };
+  if (!HOIST) digit_load(0);
+  uint32_t* tile = s;  // two in turn: one barrier a transform
   for (int j = 0; j < V.beta; ++j) {
-    const int lo = j * K.alpha, hi = min(lo + K.alpha, V.L);
     uint4 v[4], e0[4], e1[4];
     if (HOIST) {
 #pragma unroll
@@ -665,31 +684,30 @@ __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> J
       hoist_load(min(j + 1, V.beta - 1));
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) v[kk] = auto_turn(v[kk], aq[kk]);
-    } else if (r >= lo && r < hi) {
-      // digit rows are the switched polynomial itself (kept by K1 unless it is the input)
-      const uint32_t* drow = (J.kind == KS_PLAIN ? J.a : V.de) + (size_t)r * N + n0;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) v[kk] = ld4(drow + 64 * kk);
     } else {
-      const uint32_t* zrow = V.z + ((size_t)j * V.R + r) * N + base;
-      __syncthreads();  // the previous digit's tile has been read
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        RowGroup<16>::to_lds(s, threadIdx.x, kk, ld4(zrow + RowGroup<16>::word(threadIdx.x, kk, 0)));
-      __syncthreads();
-      blk_fwd_a(s, line, lane, tw, m);
-      wave_sync();
-      blk_fwd_b(s, line, lane, tw, m);
-      wave_sync();
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) v[kk] = canon4(blk_quad(s, line, 4 * (lane & 15) + 64 * kk), m.q, m.q2);
-    }
-    if (!HOIST) {
       const uint32_t* k0 = J.key + ((size_t)j * 2 * KR + pi) * N + n0;
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         e0[kk] = ld4(k0 + 64 * kk);
         e1[kk] = ld4(k0 + KR * N + 64 * kk);
+      }
+      const bool own = owns(j);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        v[kk] = nv[kk];
+        if (!own) RowGroup<16>::to_lds(tile, threadIdx.x, kk, v[kk]);
+      }
+      digit_load(min(j + 1, V.beta - 1));
+      if (!own) {
+        __syncthreads();
+        blk_fwd_a(tile, line, lane, tw, m);
+        wave_sync();
+        blk_fwd_b(tile, line, lane, tw, m);
+        wave_sync();
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+          v[kk] = canon4(blk_quad(tile, line, 4 * (lane & 15) + 64 * kk), m.q, m.q2);
+        tile = tile == s ? s + kBlkTile : s;
       }
     }
 #pragma unroll
