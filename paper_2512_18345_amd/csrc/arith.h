@@ -19,25 +19,6 @@ __device__ __forceinline__ uint32_t mul_shoup(uint32_t y, uint32_t w, uint32_t w
   return y * w - qt * q;
 }
 
-// Cooley-Tukey butterfly (x, y) <- (x + w y, x - w y), Harvey's lazy form:
-// inputs and outputs in [0, 4q).
-__device__ __forceinline__ void bfly_ct(uint32_t& x, uint32_t& y, uint32_t w, uint32_t wp,
-                                        uint32_t q, uint32_t q2) {
-  const uint32_t xx = csub(x, q2);
-  const uint32_t t = mul_shoup(y, w, wp, q);
-  x = xx + t;
-  y = xx + q2 - t;
-}
-
-// Gentleman-Sande butterfly (x, y) <- (x + y, w (x - y)): inputs and outputs in [0, 2q).
-__device__ __forceinline__ void bfly_gs(uint32_t& x, uint32_t& y, uint32_t w, uint32_t wp,
-                                        uint32_t q, uint32_t q2) {
-  const uint32_t s = csub(x + y, q2);
-  const uint32_t d = x + q2 - y;
-  x = s;
-  y = mul_shoup(d, w, wp, q);
-}
-
 // Exact x mod q for any 64-bit x, q < 2^30, mu = floor(2^64 / q) split as
 // (mu_hi, mu_lo).  The Barrett quotient floor(x mu / 2^64) is either Q or
 // Q - 1 (Q = floor(x / q)), so x - qh q lies in [0, 2q) and is computed in
@@ -115,9 +96,6 @@ struct OutRow {
 };
 __device__ __forceinline__ uint32_t ld1(const uint32_t* p) {
   return *(const __attribute__((address_space(1))) uint32_t*)p;
-}
-__device__ __forceinline__ void st1(uint32_t* p, uint32_t v) {
-  *(__attribute__((address_space(1))) uint32_t*)p = v;
 }
 
 // [0, 2m) -> [0, m) on each word

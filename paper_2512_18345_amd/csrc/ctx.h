@@ -77,8 +77,6 @@ struct Ctx {
   int logN, N;
   int L_max, k, dnum, alpha;
   std::vector<uint32_t> primes;  // q_0..q_{L_max-1}, p_0..p_{k-1}
-  // host copies used to build launches
-  std::vector<ModC> h_mod;
 
   // device tables
   ModC* d_mod = nullptr;
@@ -109,11 +107,11 @@ struct Ctx {
   mutable Trace trace;
 
   // Kernel schedule of the key-switching pipeline (ckks_ctx_set_schedule /
-  // ckks_ctx_tune): BConv output rows per work-group for ModUp and ModDown
-  // (2, 4, 6 or 12), and the largest inner-product grid that uses one thread
-  // group per digit (0: never).  Results do not depend on it.
-  // Kernel schedule: launch shapes only, results are bitwise the same under
-  // every schedule.  ntt_shape bits: kShapeWholeLimb (keyswitch.h).
+  // ckks_ctx_tune): a work-group of ModUp's or ModDown's column kernel takes at
+  // most eight times this many output rows (2, 4, 6 or 12; conv_groups), and the
+  // largest inner-product grid that uses one thread group per digit (0: never).
+  // Launch shapes only: results are bitwise the same under every schedule.
+  // ntt_shape bits: kShapeWholeLimb (keyswitch.h).
   struct Sched {
     int up_rows = 12, down_rows = 6, small_grid = 128, ntt_shape = 0;
   };

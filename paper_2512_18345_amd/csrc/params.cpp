@@ -157,7 +157,6 @@ std::string build_tables(Ctx& c, const uint32_t* q, const uint32_t* p, int* code
       }
     }
   }
-  c.h_mod = mod;
 
   // ModUp: pre-multiply constants and BConv tables for every level and digit.
   const int bmax = c.beta_max();
