@@ -390,8 +390,10 @@ int ckks_batch_launch(ckks_batch *batch, void *stream);
  * Rescale jobs run on the last branch.  Every plan gives bitwise the same
  * results.  Default {0, 1, 1}; {0, 1, 0} for a batch of one key-switching
  * job, and at N = 2^12 under the whole-limb schedule (ntt_shape bit 8) while
- * (L + k) * min(beta, 4) * jobs <= 800 for its largest level L (the
- * five-kernel pipeline pays off only past that).  A batch created with use_graph runs one
+ * (L + k) * min(beta, 4) * jobs <= 800 for its largest level L (where the
+ * five-kernel pipeline pays off depends on the digits, from about 500 of these
+ * work-groups at two-limb digits to 2000 at four one-limb digits; the autotuner
+ * below measures both).  A batch created with use_graph runs one
  * branch (streams = 1): a multi-branch launch sequence is not captured.
  */
 typedef struct ckks_batch_plan {

@@ -787,11 +787,17 @@ int ckks_batch_create(const ckks_ctx* ctx, const ckks_job* h_jobs, int n, int us
   b->Lmax_rs = Lrs;
   b->use_graph = use_graph != 0;
   b->sched = ctx->c.sched;
-  // split: on a small ring with the whole-limb schedule the unsplit launch (two
-  // kernels) is the faster one until its first kernel needs about 800
-  // work-groups: HMults at N = 2^12, L = 4 (20 work-groups each) measured
-  // 1.4-2.3x faster unsplit for 2-32 jobs and even at 48.  Elsewhere the flag
-  // changes nothing.
+  // split: on a small ring with the whole-limb schedule the two whole-limb kernels
+  // (0) are the faster ones up to some number of work-groups of their first kernel,
+  // the pipeline (1) past it.  Where they cross depends on the digits; 800 lies
+  // between.  HMults, whole limbs / pipeline, microseconds (work-groups):
+  //   one-limb digits, four of them, L = 4: 41.5 / 49.4 (800), 74.6 / 75.9 (1920),
+  //     86 / 83 (2240);
+  //   one-limb digits, L = 10: 80 / 86 (792), 101 / 91 (1056); L = 24: 93 / 142
+  //     (400), 172 / 155 (800);
+  //   two-limb digits, L = 6: 37.0 / 42.0 (480), 48.9 / 44.3 (576); L = 20:
+  //     80.2 / 80.7 (528), 115 / 84 (704).
+  // Elsewhere the flag changes nothing.
   const int Lks = ks.empty() ? 0 : ks[order[0]].L;
   const bool whole_limb = c.logN == kSrLog && (b->sched.ntt_shape & kShapeWholeLimb);
   const long sr_wgs = (long)(Lks + c.k) * std::min(c.beta(std::max(Lks, 1)), kSrGroups) * b->n_ks;

@@ -18,7 +18,9 @@ namespace ckks {
 // block pass needs none at all.  Bound: the loads, transform and stores of one
 // round of work-groups follow one another.  N = 2^16, 48 rows: forward 12.3 +
 // 13.0 -> 8.6 + 7.4 us, inverse 10.6 + 15.5 -> 7.0 + 9.1 (radix-16 tiles of 256
-// threads with barriers and twiddles in LDS before).
+// threads with barriers and twiddles in LDS before).  Few rows: a call of up to 16
+// rows (36 at N = 2^15) takes the 10.4 us of its two launches back to back, before
+// as now, but for N = 2^16 (11.1 .. 14.4).
 // ============================================================================
 template <int LOGN1>
 struct ColTile {

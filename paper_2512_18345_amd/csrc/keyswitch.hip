@@ -53,9 +53,12 @@ KsConst make_const(const Ctx& c) {
   return KsConst{c.tab(), c.k, c.alpha, c.beta_max(), c.d_modup_T_off, c.d_pinv, c.d_rescale_inv, c.mont};
 }
 
-// Scratch layout of one job (rows of N words): acc [2][R], [2][k] unused, w [2][L],
-// then, for jobs that run ModUp, y [L], z [beta][R] and de [L] (the eval-domain
-// polynomial being switched, kept by K1 for the digit rows of K5); R = L + k.
+// Scratch layout of one job (rows of N words): acc [2][R] (its P rows alone are
+// used), [2][k] that the pipeline leaves alone, w [2][L], then, for jobs that run
+// ModUp, y [L], z [beta][R] and de [L] (the eval-domain polynomial being switched,
+// kept by K1 for the digit rows of K5); R = L + k.  The whole-limb kernels lay
+// [groups][2][R] over the same rows, groups = min(beta, kSrGroups) at most: a
+// layout with fewer rows would have to keep 2 groups R of them.
 struct KsView {
   uint32_t *y, *z, *de, *acc, *w;
   const uint32_t* p;  // the P rows after their INTT block pass (row-group layout), component c at p + c ps N
@@ -230,8 +233,10 @@ __global__ __launch_bounds__(kWG) void k1_intt_blks(KsConst K, JobArg<KsJob> JA)
 // words, and the word's sum mod q is these times 1, 2^8, 2^16 and 2^24: eight
 // vector instructions a word instead of a multiply-add per limb and four.  At
 // four limbs or fewer the multiply-adds are no more than that.
-// Bound: vector arithmetic, 570 instructions a wave for a pair of rows (half a
-// transform a word is 450 of them) and 650 for a pair of inputs.
+// Bound: in batches vector arithmetic, 570 instructions a wave for a pair of rows
+// (half a transform a word is 450 of them) and 650 for a pair of inputs; with the
+// 384 and 256 work-groups of a single key-switch at L = 36, one or two a CU, also
+// the chain of load, input transforms and rows (44 and 47% of the issue rate).
 // N = 2^16, L = 36, 12 + 12 limbs: ModUp 43.5 us in three kernels -> 28.4 with
 // multiply-adds -> 26.3, ModDown 32.1 -> 18.0 -> 16.9; HMult and rescale
 // together 234.8 -> 226.9 us by the matrix cores, 16 rotations 633 -> 620.  Two
@@ -759,8 +764,9 @@ __global__ __launch_bounds__(kWG) void k5_ntt_blks_ip(KsConst K, JobArg<KsJob> J
 // Bound: Q rows, memory (HMult at N = 2^16, L = 36: 160 MB in 33 us, 4.8 TB/s;
 // with a combine kernel of its own, all rows 29.6 + 19.1 us); P rows, the
 // chain of one round of work-groups (17 us for a quarter of the rows).  16
-// hoisted rotations: 316 + 183 us in two kernels -> 86 + 311.  At most 168
-// registers, so that three work-groups share a CU: at 191 the Q rows took 37.9.
+// hoisted rotations: 316 + 183 us in two kernels -> 86 + 311.  Up to three digits
+// at most 168 registers, so that three work-groups share a CU: at 191 the Q rows
+// took 37.9.  (Four digits: two, by their 69 KiB of LDS as by the Q rows' 189.)
 // NT: the key words are read with the non-temporal hint (a launch of one
 // job reads its key once; batches whose jobs share a key keep it cached).
 template <int NB, bool NT, bool Q>
@@ -1311,8 +1317,8 @@ __global__ __launch_bounds__(kWG) void kd_ntt_blks_combine(KsConst K, JobArg<KsJ
 // Bound: the chain of one work-group, four transforms of about 800 instructions
 // a wave with one barrier each.  With 1024 threads in radix-4 phases, six
 // barriers a transform and both 32 KiB twiddle tables staged in LDS, HMult at
-// L = 4 took 12.0 + 14.6 us, and 16 of them 23.4 + 14.8; now 10.2 + 10.3 and
-// 15.5 + 11.2.
+// L = 4 took 12.0 + 14.6 us, and 16 of them 23.4 + 14.8; now 9.3 + 9.9 and
+// 15.4 + 10.9.
 // ============================================================================
 constexpr int kSrN = 1 << kSrLog;
 static_assert(kSrN == kTile, "one 16-row group per limb");
@@ -1403,7 +1409,9 @@ struct SrRaw {
 // S1.  The work-group's items are its digits' limbs in order (a digit row of
 // the switched polynomial is one item without transforms).  Two tiles in turn,
 // so that one barrier a transform is enough.
-// ONE: a single digit per group, so no accumulators.
+// ONE: a single digit per group, so no accumulators.  With several the sums and the
+// transform's words fill a wave's registers (one work-group a CU): 41 us for HMult
+// at L = 24 with one-limb digits, a group's six one after another.
 template <bool ONE>
 __global__ __launch_bounds__(kWG, ONE ? 2 : 1) void s1_modup_ip(KsConst K, JobArg<KsJob> JA) {
   const KsJob J = JA.get(blockIdx.z);
