@@ -236,7 +236,7 @@ __global__ __launch_bounds__(kWG) void k1_intt_blks(KsConst K, JobArg<KsJob> JA)
 // Bound: in batches vector arithmetic, 570 instructions a wave for a pair of rows
 // (half a transform a word is 450 of them) and 650 for a pair of inputs; with the
 // 384 and 256 work-groups of a single key-switch at L = 36, one or two a CU, also
-// the chain of load, input transforms and rows (44 and 47% of the issue rate).
+// the chain of load, input transforms and rows (46 and 48% of the issue rate).
 // N = 2^16, L = 36, 12 + 12 limbs: ModUp 43.5 us in three kernels -> 28.4 with
 // multiply-adds -> 26.3, ModDown 32.1 -> 18.0 -> 16.9; HMult and rescale
 // together 234.8 -> 226.9 us by the matrix cores, 16 rotations 633 -> 620.  Two
