@@ -692,8 +692,9 @@ int ckks_ctx_tune(ckks_ctx* ctx, int L, int reps, void* stream, ckks_schedule* b
     cand[n] = s;
     grids[n++] = g;
   };
-  add(default_schedule(c));
-  for (int shape : {0, kShapeWholeLimb})  // (the other bits have no effect)
+  const Ctx::Sched def = default_schedule(c);
+  add(def);
+  for (int shape : {def.ntt_shape, def.ntt_shape ^ kShapeWholeLimb})  // (the other bits have no effect)
     for (int up : {12, 6, 4, 2})
       for (int down : {6, 12, 4, 2})
         for (int small : {128, 0, 1024}) add(Ctx::Sched{up, down, small, shape});
